@@ -54,6 +54,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "stream_sum.h"
 
 namespace epic {
 
@@ -67,6 +68,7 @@ constexpr int kPartialFloats = kTM * 256;               // fp32 partial sums of 
 constexpr int kMaxSplitTiles = 2 * kMaxWorkers;
 constexpr int kCounters = kMaxSplitTiles * (kThreads / 64);   // one per (cut tile, wavefront)
 constexpr int kMinUnits = 4;                            // K stages per workgroup, at least
+constexpr int kStreamRows = 512;                        // rows up to which weight streaming beats cut tiles
 
 template <int TM, int TN>
 struct Shape {
@@ -645,7 +647,17 @@ void launch_tn(const GemmArgs& g, bool whole_tiles, hipStream_t stream) {
 }
 
 template <int EPI>
-void launch_epi(const GemmArgs& g, hipStream_t stream) {
+void launch_epi(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
+  if (r == GemmRoute::kWhole192) launch_tn<EPI, 192, 256>(g, true, stream);
+  else if (r == GemmRoute::kWhole256) launch_tn<EPI, 256, 256>(g, true, stream);
+  else if (r == GemmRoute::kWhole96) launch_tn<EPI, 96, 128>(g, true, stream);
+  else if (r == GemmRoute::kWhole128) launch_tn<EPI, 128, 128>(g, true, stream);
+  else launch_tn<EPI, 256, 128>(g, false, stream);
+}
+
+}  // namespace
+
+GemmRoute gemm_route(const GemmArgs& g, int epi) {
   // At least a round of 256 x 256 tiles: whole tiles only (measured: cutting tiles
   // along K costs about one tile time in partial traffic, more than a short last
   // round).  The tiles are 256 or 192 rows high, whichever takes less time: a round
@@ -654,13 +666,13 @@ void launch_epi(const GemmArgs& g, hipStream_t stream) {
   // they save a round or more of the short last round: at 736 rows, 448 tiles of
   // 192 rows in 2 rounds of 224 workgroups instead of 336 of 256 rows in 2 rounds
   // of 168.
+  const bool swiglu = epi == kSwiGLU;
   const int m_tiles = cdiv(g.M, kTM);
-  const int n256 = EPI == kSwiGLU ? (g.ffn % 128 == 0 ? g.ffn / 128 : 0) : cdiv(g.N, 256);
+  const int n256 = swiglu ? (g.ffn % 128 == 0 ? g.ffn / 128 : 0) : cdiv(g.N, 256);
   if (int64_t(m_tiles) * n256 >= kMaxWorkers) {
     const int64_t r256 = (int64_t(m_tiles) * n256 + kMaxWorkers - 1) / kMaxWorkers;
     const int64_t r192 = (int64_t(cdiv(g.M, 192)) * n256 + kMaxWorkers - 1) / kMaxWorkers;
-    if (r192 * 15 < r256 * 16) return launch_tn<EPI, 192, 256>(g, true, stream);
-    return launch_tn<EPI, 256, 256>(g, true, stream);
+    return r192 * 15 < r256 * 16 ? GemmRoute::kWhole192 : GemmRoute::kWhole256;
   }
   // Fewer: with a short K and one round of 96 x 128 or 128 x 128 tiles that fills at
   // least 3/4 of the CUs, those tiles whole (96 rows where they make such a round: more
@@ -670,21 +682,29 @@ void launch_epi(const GemmArgs& g, hipStream_t stream) {
   // 15 us of partial traffic and fixup, so whole tiles win up to about 100 stages (W_O,
   // K = 4096: 48.0 -> 40.2 us; W_down, K = 14336: 103.8 -> 127.7 us).  96 x 128 tiles on
   // 256 CUs took W_O about 1 us further (the c3 link step 0.3% faster on one box).
-  const int64_t n128 = EPI == kSwiGLU ? g.ffn / 64 : cdiv(g.N, 128);
+  const int64_t n128 = swiglu ? g.ffn / 64 : cdiv(g.N, 128);
   const int64_t t128 = int64_t(cdiv(g.M, 128)) * n128, t96 = int64_t(cdiv(g.M, 96)) * n128;
   auto one_round = [](int64_t t) { return t >= 3 * kMaxWorkers / 4 && t <= kMaxWorkers; };
   if (g.K / kBK <= 96) {
-    if (one_round(t96)) return launch_tn<EPI, 96, 128>(g, true, stream);
-    if (one_round(t128)) return launch_tn<EPI, 128, 128>(g, true, stream);
+    if (one_round(t96)) return GemmRoute::kWhole96;
+    if (one_round(t128)) return GemmRoute::kWhole128;
   }
-  launch_tn<EPI, 256, 128>(g, false, stream);
+  // What is left would cut 256 x 128 tiles.  Up to kStreamRows rows, and where those
+  // tiles are fewer than the CUs (else most are whole and the cut ones few), streaming
+  // the weights into partial sums is faster (epic_gemm, one box, cut -> streamed, us):
+  //   K = 4096, N = 4096:    32 rows 21.2 -> 12.8, 128 29.1 -> 15.6, 256 47.4 -> 23.4, 448 43.2 -> 29.7
+  //   K = 4096, N = 6144:    32 rows 19.7 -> 14.9, 128 25.9 -> 19.1, 256 42.8 -> 31.9
+  //   K = 14336, N = 4096:   32 rows 36.1 -> 26.8, 128 47.5 -> 34.4, 256 75.6 -> 50.5, 512 94.6 -> 86.1,
+  //                          640 117.4 -> 118.8
+  //   K = 4096, N = 2 x 14336, SwiGLU (448 tiles): 256 rows 83.1 -> 110.6
+  const int64_t cut_tiles = int64_t(m_tiles) * n128;
+  if (g.M <= kStreamRows && cut_tiles < kMaxWorkers && stream_fits(g.M, g.N, g.K)) return GemmRoute::kStream;
+  return GemmRoute::kCut;
 }
 
-}  // namespace
+size_t gemm_partial_floats() { return size_t(2 * kMaxWorkers) * kPartialFloats; }
 
-size_t gemm_workspace_bytes() {
-  return size_t(2 * kMaxWorkers) * kPartialFloats * sizeof(float) + kCounters * sizeof(int);
-}
+size_t gemm_workspace_bytes() { return gemm_partial_floats() * sizeof(float) + kCounters * sizeof(int); }
 
 void gemm_workspace(void* base, float** partial, int** tile_count) {
   *partial = static_cast<float*>(base);
@@ -697,14 +717,17 @@ void launch_gemm_clear(int* tile_count, hipStream_t stream) {
 
 void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream) {
   if (g.M == 0) return;
-  if (epi == kStoreF32)
-    launch_epi<kStoreF32>(g, stream);
+  const GemmRoute r = gemm_route(g, epi);
+  if (r == GemmRoute::kStream)
+    launch_stream_finish(launch_gemm_stream(g, stream), g, epi, stream);
+  else if (epi == kStoreF32)
+    launch_epi<kStoreF32>(g, r, stream);
   else if (epi == kRope)
-    launch_epi<kRope>(g, stream);
+    launch_epi<kRope>(g, r, stream);
   else if (epi == kResidual)
-    launch_epi<kResidual>(g, stream);
+    launch_epi<kResidual>(g, r, stream);
   else
-    launch_epi<kSwiGLU>(g, stream);
+    launch_epi<kSwiGLU>(g, r, stream);
 }
 
 }  // namespace epic

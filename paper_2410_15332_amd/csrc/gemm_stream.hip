@@ -1,0 +1,313 @@
+// Weight-streaming GEMMs of short row sets: partial sums of C[M x N] = A[M x K] . W[N x K]^T.
+//
+// With few rows the projection's cost is reading W once.  What has to be hidden is
+// memory latency, and every CU has to stream the same share of W.  So:
+//   - tiles are TM x TN (TM = 32, 64 or 128 rows, several row tiles past 128; TN = 64 or
+//     128), K in stages of 64, and the tiles' K stages in tile order are dealt in G equal
+//     contiguous shares, whatever N and K are;
+//   - a share's part of a tile goes to memory as an fp32 partial in a plane of its own
+//     (plane p = p-th worker of the tile), and the kernel that consumes C sums the
+//     planes in K order (stream_sum.h): no counters, no waiting on another workgroup,
+//     and the sum is fused into the pass that reads C anyway (residual + RMSNorm,
+//     SwiGLU, rotary embedding);
+//   - LDS is a ring of NS stages, loads issued NS - 1 stages ahead of their use (144 KB
+//     in flight per CU), and a wavefront reads a stage's fragments while the previous
+//     stage is on the matrix cores.
+// Measured with its finishing pass (K = 4096, N = 4096; the cut 256 x 128 tiles before):
+// 32 rows 21.2 -> 12.8 us, 128 rows 29.1 -> 15.6; K = 14336: 36.1 -> 26.8 and 47.5 -> 34.4,
+// where the kernel alone reads W at 5.0 and 4.0 TB/s (a plain read probe: 5.5).  At 128
+// rows the LDS (fragment reads and stage writes, about 700 cycles a 64-column stage)
+// comes within a factor of two of the pace; 128-column tiles need 500.
+//
+// Stage layout: (TM + TN) rows of 128 bytes, A rows then W rows, in groups of 8 rows
+// (1 KB, one load instruction); the eight 16-byte chunks of row r are XOR-swizzled by
+// (r / 2) % 8, so the 16 lanes of each ds_read_b128 group touch distinct banks.
+// Rows past M are read as row M - 1 and never stored.
+#include <algorithm>
+
+#include "device_common.h"
+#include "gemm.h"
+#include "stream_sum.h"
+
+namespace epic {
+
+namespace {
+
+constexpr int kBK = 64;
+constexpr int kMinUnits = 4;                            // K stages per worker, at least
+constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+__device__ __forceinline__ void stream_dma16(__amdgpu_buffer_rsrc_t rs, char* dst, int voff, int soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, soff, 0, 0);
+}
+// workgroup barrier ordering LDS accesses only (buffer->LDS loads stay in flight)
+__device__ __forceinline__ void stream_barrier() {
+  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+template <int N>
+__device__ __forceinline__ void stream_wait() {
+  static_assert(N >= 0 && N < 64, "vmcnt field");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
+}
+
+struct StreamArgs {
+  const uint16_t* A;
+  const uint16_t* W;
+  float* partial;       // [planes][M][N]
+  int M, N, K;
+  StreamSum s;
+};
+
+template <int TM, int TN, int NW, int CT, int NS, int OCC>
+__global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g) {
+  constexpr int NG = (TM + TN) / 8;                    // 1 KB row groups per stage
+  constexpr int NL = NG / NW;                           // ... per wavefront
+  static_assert(NG % NW == 0, "row groups per wavefront");
+  constexpr int NT = (TM / 32) * (TN / 32 / CT);       // wavefront tiles of 32 rows x 32 CT columns
+  constexpr int KH = NW / NT;                           // wavefronts that share one, by k-slices
+  static_assert(KH * NT == NW && 4 % KH == 0, "wavefronts per tile");
+  constexpr int SB = (TM + TN) * 128;                  // bytes per stage
+  __shared__ __attribute__((aligned(1024))) char lds[NS][SB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int w = blockIdx.x, G = g.s.G;
+  const int wr = G % 8 == 0 ? (w % 8) * (G / 8) + w / 8 : w;   // XCD-contiguous worker index
+  const int ks = g.s.ks, m_tiles = g.s.m_tiles;
+  const int u0 = g.s.begin(wr), u1 = g.s.begin(wr + 1);
+  if (u0 >= u1) return;
+
+  // ---- loads: row group gi of a stage, A rows first
+  const int row_bytes = g.K * 2;
+  const int lrow = lane >> 3;
+  __amdgpu_buffer_rsrc_t rs[NL];
+  int vo[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const bool is_a = wv * NL + i < TM / 8;
+    rs[i] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(is_a ? g.A : g.W), 0,
+                                              (is_a ? g.M : g.N) * row_bytes, kBufWord3);
+  }
+  auto setup = [&](int tile) __attribute__((always_inline)) {
+    const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int gi = wv * NL + i;
+      const bool is_a = gi < TM / 8;
+      const int row = (is_a ? gi : gi - TM / 8) * 8 + lrow;
+      const int gr = is_a ? min(mt * TM + row, g.M - 1) : nt * TN + row;
+      vo[i] = gr * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+    }
+  };
+  int du = u0, dtile = u0 / ks, dkt = u0 - dtile * ks;   // next unit to load
+  setup(dtile);
+  auto dma_next = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) stream_dma16(rs[i], lds[buf] + (wv * NL + i) * 1024, vo[i], dkt * (kBK * 2));
+    if (du + 1 < u1) {                                  // past the last unit: that one again
+      ++du;
+      if (++dkt == ks) {
+        dkt = 0;
+        setup(++dtile);
+      }
+    }
+  };
+
+  // ---- compute: wavefront -> tile (rt, ct) and its share of the stage's four k-slices
+  const int mt_ = wv % NT, kh = wv / NT;
+  constexpr int WC = TN / 32 / CT;                      // wavefront tiles along N
+  const int rt = mt_ / WC, ct = mt_ % WC * CT;
+  const int lbase = (lane & 31) * 128, lsw = (lane >> 1) & 7, half = lane >> 5;
+  const int abase = rt * 4096 + lbase, bbase = (TM / 32 + ct) * 4096 + lbase;
+
+#pragma unroll
+  for (int b = 0; b < NS - 1; ++b) dma_next(b);
+  int buf = 0, u = u0, tile = u0 / ks;
+  while (u < u1) {
+    const int ue = min(u1, (tile + 1) * ks);
+    f32x16 acc[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) acc[j] = f32x16{};
+    // the k-slices of unit u are read while unit u - 1 is on the matrix cores
+    struct Frags {
+      bf16x8 a[4 / KH], b[4 / KH][CT];
+    } f0, f1;
+    auto fetch = [&](Frags& f) __attribute__((always_inline)) {
+      stream_wait<(NS - 2) * NL>();                     // this wavefront's loads of unit u
+      stream_barrier();                                 // everyone's; and unit u - 1 is read
+      dma_next(buf == 0 ? NS - 1 : buf - 1);            // unit u + NS - 1, where u - 1 was
+      const char* p = lds[buf];
+#pragma unroll
+      for (int i = 0; i < 4 / KH; ++i) {
+        const int c = ((2 * (kh * (4 / KH) + i) + half) ^ lsw) * 16;
+        f.a[i] = *reinterpret_cast<const bf16x8*>(p + abase + c);
+#pragma unroll
+        for (int j = 0; j < CT; ++j) f.b[i][j] = *reinterpret_cast<const bf16x8*>(p + bbase + j * 4096 + c);
+      }
+      buf = buf + 1 == NS ? 0 : buf + 1;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mma = [&](const Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 4 / KH; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j) acc[j] = mfma_32x32x16(f.a[i], f.b[i][j], acc[j]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(f0);
+    for (++u; u + 1 < ue; u += 2) {
+      fetch(f1);
+      mma(f0);
+      fetch(f0);
+      mma(f1);
+    }
+    if (u < ue) {
+      ++u;
+      fetch(f1);
+      mma(f0);
+      mma(f1);
+    } else {
+      mma(f0);
+    }
+    // this worker's part of the tile: plane (worker - first worker of the tile) * KH + kh
+    const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
+    const int plane = (wr - g.s.owner(tile * ks)) * KH + kh;
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+        g.partial + size_t(plane) * g.M * g.N, 0, g.M * g.N * 4, kBufWord3);   // rows past M: dropped
+    const int m0 = mt * TM + rt * 32 + half * 4, n = nt * TN + ct * 32 + (lane & 31);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) {
+        const float x = acc[j][r];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), ro,
+                                              ((m0 + (r >> 2) * 8 + (r & 3)) * g.N + n + j * 32) * 4, 0, 0);
+      }
+    ++tile;
+  }
+  stream_wait<0>();                                     // no load may land in LDS after the workgroup ends
+}
+
+// C = sum of the planes, stored (kStoreF32) or added (kResidual): four columns per thread.
+template <int EPI>
+__global__ __launch_bounds__(256) void stream_finish_kernel(StreamSum s, float* __restrict__ c, uint16_t* __restrict__ act,
+                                                            int ffn) {
+  const int n4 = (EPI == kSwiGLU ? ffn : s.N) / 4;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  const int m = idx / n4, n = (idx - m * n4) * 4;
+  if (m >= s.M) return;
+  float4 v = s.sum4(m, n);
+  if constexpr (EPI == kSwiGLU) {
+    const float4 up = s.sum4(m, ffn + n);
+    auto silu = [](float x) { return x * __builtin_amdgcn_rcpf(1.0f + fast_exp2(-x * kLog2e)); };
+    *reinterpret_cast<uint2*>(act + size_t(m) * ffn + n) =
+        make_uint2(pack_bf16x2(silu(v.x) * up.x, silu(v.y) * up.y), pack_bf16x2(silu(v.z) * up.z, silu(v.w) * up.w));
+  } else {
+    float4* p = reinterpret_cast<float4*>(c + size_t(m) * s.N + n);
+    if constexpr (EPI == kResidual) {
+      const float4 o = *p;
+      v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
+    }
+    *p = v;
+  }
+}
+
+// q, k, v of the fused Q|K|V projection: q and k heads rotated at each row's linked
+// position (pairs (i, i + D/2)), v heads as they are; bf16.  A thread takes four pairs.
+__global__ __launch_bounds__(256) void stream_rope_kernel(StreamSum s, GemmArgs g) {
+  const int D = g.head_dim, hd2 = D / 2, per_row = s.N / 8;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  const int m = idx / per_row, r = idx - m * per_row;
+  if (m >= s.M) return;
+  const int head = r / (hd2 / 4), i = (r - head * (hd2 / 4)) * 4;
+  const float4 a = s.sum4(m, head * D + i), b = s.sum4(m, head * D + hd2 + i);
+  uint16_t* base;
+  int heads, hd;
+  if (head < g.hq) base = g.q, heads = g.hq, hd = head;
+  else if (head < g.hq + g.hkv) base = g.k, heads = g.hkv, hd = head - g.hq;
+  else base = g.v, heads = g.hkv, hd = head - g.hq - g.hkv;
+  float x1[4] = {a.x, a.y, a.z, a.w}, x2[4] = {b.x, b.y, b.z, b.w};
+  if (head < g.hq + g.hkv) {
+    const float4* cs = reinterpret_cast<const float4*>(g.cs + size_t(m) * hd2 + i);
+    const float4 t0 = cs[0], t1 = cs[1];
+    const float c[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float y1 = x1[e] * c[e] - x2[e] * sn[e], y2 = x2[e] * c[e] + x1[e] * sn[e];
+      x1[e] = y1;
+      x2[e] = y2;
+    }
+  }
+  uint16_t* o = base + (size_t(m) * heads + hd) * D + i;
+  *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16x2(x1[0], x1[1]), pack_bf16x2(x1[2], x1[3]));
+  *reinterpret_cast<uint2*>(o + hd2) = make_uint2(pack_bf16x2(x2[0], x2[1]), pack_bf16x2(x2[2], x2[3]));
+}
+
+int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+StreamSum make_sum(int M, int N, int K, int TM, int TN, int workers, int kh, const float* partial) {
+  StreamSum s{};
+  s.partial = partial;
+  s.M = M, s.N = N;
+  s.tm = TM, s.tn = TN;
+  s.m_tiles = cdiv(M, TM);
+  s.ks = K / kBK;
+  s.kh = kh;
+  s.units = s.m_tiles * (N / TN) * s.ks;
+  s.G = s.units < workers * kMinUnits ? cdiv(s.units, kMinUnits) : workers;
+  return s;
+}
+
+// Rows past 64: 128-column tiles where every worker then still gets kWideUnits stages.
+// They read and stage two thirds of the operand bytes of 64-column tiles per product,
+// but cut each tile into twice the planes (128 rows, K = 14336: 39.3 -> 35.7 us; K = 4096,
+// 8 stages per worker: 18.1 -> 19.9).
+constexpr int kWideUnits = 16;
+bool wide_tiles(int M, int N, int K) {
+  return int64_t(cdiv(M, 128)) * (N / 128) * (K / kBK) >= int64_t(kWideUnits) * 256;
+}
+
+template <int TM, int TN, int NW, int CT, int NS, int OCC>
+StreamSum launch_tm(const GemmArgs& g, hipStream_t stream) {
+  StreamArgs a{};
+  a.A = g.A, a.W = g.W, a.partial = g.partial, a.M = g.M, a.N = g.N, a.K = g.K;
+  a.s = make_sum(g.M, g.N, g.K, TM, TN, 256 * OCC, NW / (TM / 32 * (TN / 32) / CT), g.partial);
+  gemm_stream_kernel<TM, TN, NW, CT, NS, OCC><<<a.s.G, NW * 64, 0, stream>>>(a);
+  return a.s;
+}
+
+}  // namespace
+
+// planes of a tile: at most ceil(ks / stages per worker) + 1 workers, two wavefronts each
+bool stream_fits(int M, int N, int K) {
+  const int tm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
+  const int64_t units = int64_t(cdiv(M, tm)) * (N / 64) * (K / kBK);
+  if (units >= (1 << 23)) return false;                 // 32-bit arithmetic of StreamSum::owner
+  const int64_t per = std::max<int64_t>(units / 2 / 256, 1);   // of either tile width
+  const int64_t planes = (K / kBK + per - 1) / per + 1;
+  return 2 * planes * M * N <= int64_t(gemm_partial_floats());
+}
+
+StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream) {
+  // Wavefronts: as few as cover the tile, so a 32- or 64-row stage costs few barriers and
+  // LDS reads (W_down of 32 rows: 2 wavefronts 29.2 us, 4 sharing k-slices 32.7; of 64
+  // rows: 4 wavefronts 31.8, 8 33.0).
+  if (g.M <= 32) return launch_tm<32, 64, 2, 1, 12, 1>(g, stream);
+  if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9, 1>(g, stream);
+  if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4, 1>(g, stream);
+  return launch_tm<128, 64, 8, 1, 6, 1>(g, stream);
+}
+
+void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStream_t stream) {
+  if (epi == kRope) {
+    stream_rope_kernel<<<cdiv(s.M * (s.N / 8), 256), 256, 0, stream>>>(s, g);
+    return;
+  }
+  const int grid = cdiv(s.M * ((epi == kSwiGLU ? g.ffn : s.N) / 4), 256);
+  if (epi == kStoreF32) stream_finish_kernel<kStoreF32><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
+  else if (epi == kResidual) stream_finish_kernel<kResidual><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
+  else stream_finish_kernel<kSwiGLU><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
+}
+
+}  // namespace epic

@@ -12,6 +12,7 @@
 
 #include "device_common.h"
 #include "kernels.h"
+#include "stream_sum.h"
 
 namespace epic {
 
@@ -29,6 +30,55 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
 #pragma unroll
   for (int w = 0; w < kNormThreads / 64; ++w) s += red[w];
   return s;
+}
+
+// The residual stream's pass between a weight-streaming GEMM and the next norm:
+// h += the GEMM's partial sums, then y = RMSNorm(h) w, the row kept in registers
+// between the two.  One workgroup of 1024 threads per row: there are few rows, and a
+// row's planes are many independent loads, so what bounds it is load latency.
+constexpr int kSumThreads = 1024;
+constexpr int kSumKeep = 2;                             // float4 per thread: hidden <= 8192
+__global__ __launch_bounds__(kSumThreads) void rmsnorm_sum_kernel(StreamSum s, float* __restrict__ x,
+                                                                  const uint16_t* __restrict__ w,
+                                                                  uint16_t* __restrict__ out_bf16,
+                                                                  float* __restrict__ out_f32, float eps) {
+  __shared__ float red[kSumThreads / 64];
+  const int row = blockIdx.x, hidden = s.N, n4 = hidden / 4;
+  float4* xr = reinterpret_cast<float4*>(x + size_t(row) * hidden);
+  float4 keep[kSumKeep];
+  float ss = 0.0f;
+#pragma unroll
+  for (int k = 0; k < kSumKeep; ++k) {
+    const int i = threadIdx.x + k * kSumThreads;
+    if (i >= n4) break;
+    const float4 o = xr[i], d = s.sum4(row, 4 * i);
+    keep[k] = make_float4(o.x + d.x, o.y + d.y, o.z + d.z, o.w + d.w);
+    xr[i] = keep[k];
+    ss += keep[k].x * keep[k].x + keep[k].y * keep[k].y + keep[k].z * keep[k].z + keep[k].w * keep[k].w;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float total = 0.0f;
+#pragma unroll
+  for (int v = 0; v < kSumThreads / 64; ++v) total += red[v];
+  const float inv = 1.0f / sqrtf(total / float(hidden) + eps);
+#pragma unroll
+  for (int k = 0; k < kSumKeep; ++k) {
+    const int i = threadIdx.x + k * kSumThreads;
+    if (i >= n4) break;
+    const uint2 wb = *reinterpret_cast<const uint2*>(w + 4 * i);
+    const float y0 = keep[k].x * inv * bf16_to_f32(uint16_t(wb.x & 0xFFFFu));
+    const float y1 = keep[k].y * inv * bf16_to_f32(uint16_t(wb.x >> 16));
+    const float y2 = keep[k].z * inv * bf16_to_f32(uint16_t(wb.y & 0xFFFFu));
+    const float y3 = keep[k].w * inv * bf16_to_f32(uint16_t(wb.y >> 16));
+    if (out_bf16)
+      *reinterpret_cast<uint2*>(out_bf16 + size_t(row) * hidden + 4 * i) =
+          make_uint2(pack_bf16x2(y0, y1), pack_bf16x2(y2, y3));
+    else
+      *reinterpret_cast<float4*>(out_f32 + size_t(row) * hidden + 4 * i) = make_float4(y0, y1, y2, y3);
+  }
 }
 
 // One workgroup per row; hidden % 4 == 0.  out_bf16 or out_f32 receives the row.
@@ -105,6 +155,18 @@ void launch_rmsnorm(const float* x, const uint16_t* w, uint16_t* out_bf16, float
                     float eps, hipStream_t stream) {
   if (rows == 0) return;
   rmsnorm_kernel<<<rows, kNormThreads, 0, stream>>>(x, w, out_bf16, out_f32, hidden, eps);
+}
+
+void launch_rmsnorm_sum(const StreamSum& s, float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, float eps,
+                        hipStream_t stream) {
+  if (s.N <= 4 * kSumKeep * kSumThreads) {
+    rmsnorm_sum_kernel<<<s.M, kSumThreads, 0, stream>>>(s, x, w, out_bf16, out_f32, eps);
+    return;
+  }
+  GemmArgs g{};                                         // longer rows: two passes
+  g.C = x;
+  launch_stream_finish(s, g, kResidual, stream);
+  launch_rmsnorm(x, w, out_bf16, out_f32, s.M, s.N, eps, stream);
 }
 
 void launch_rope_table(const int32_t* s_pos, float2* cs, int rows, int head_dim, double theta, hipStream_t stream) {

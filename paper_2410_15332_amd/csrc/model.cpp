@@ -18,6 +18,7 @@
 #include "link_write.h"
 #include "kernels.h"
 #include "plan_internal.h"
+#include "stream_sum.h"
 #include "status.h"
 
 using namespace epic;
@@ -96,65 +97,77 @@ epic_status hip_ok(const char* what) {
   return EPIC_OK;
 }
 
-// One layer; the rotary table ws.cs is already filled.
-epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s,
-                      const epic_plan* p, float* h, uint16_t* kc, uint16_t* vc, const LayerWs& ws,
-                      hipStream_t stream) {
-  const int n = s->n_s, H = c->hidden, F = c->ffn;
+// A layer's GEMMs (Q|K|V with its rotary epilogue, W_O, gate|up, W_down).
+struct LayerGemms {
+  GemmArgs qkv, wo, gate_up, down;
+};
+
+LayerGemms layer_gemms(const epic_model_cfg* c, const epic_layer_weights* w, int n, float* h, const LayerWs& ws) {
+  const int H = c->hidden, F = c->ffn;
   const int hq = c->attn.num_q_heads, hkv = c->attn.num_kv_heads, D = c->attn.head_dim;
-  launch_rmsnorm(h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
-  GemmArgs g{};
-  g.A = ws.x;
-  g.W = w->wqkv;
-  g.M = n;
-  g.N = (hq + 2 * hkv) * D;
-  g.K = H;
-  g.q = ws.q;
-  g.k = ws.k;
-  g.v = ws.v;
-  g.cs = ws.cs;
-  g.hq = hq;
-  g.hkv = hkv;
-  g.head_dim = D;
-  g.partial = ws.gemm_partial;
-  g.tile_count = ws.gemm_count;
-  launch_gemm(g, kRope, stream);
+  LayerGemms l{};
+  auto set = [&](GemmArgs& g, const uint16_t* a, const uint16_t* wt, int N, int K) {
+    g.A = a, g.W = wt, g.M = n, g.N = N, g.K = K;
+    g.partial = ws.gemm_partial, g.tile_count = ws.gemm_count;
+  };
+  set(l.qkv, ws.x, w->wqkv, (hq + 2 * hkv) * D, H);
+  l.qkv.q = ws.q, l.qkv.k = ws.k, l.qkv.v = ws.v, l.qkv.cs = ws.cs;
+  l.qkv.hq = hq, l.qkv.hkv = hkv, l.qkv.head_dim = D;
+  set(l.wo, ws.o, w->wo, H, hq * D);
+  l.wo.C = h;
+  set(l.gate_up, ws.x, w->w_gate_up, 2 * F, H);
+  l.gate_up.act = ws.act, l.gate_up.ffn = F;
+  set(l.down, ws.act, w->w_down, H, F);
+  l.down.C = h;
+  return l;
+}
+
+// Before a call's first layer: the rotary table, and cleared arrival counters where a
+// GEMM of these shapes uses them (every layer has the same shapes).
+void start_layers(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s, const epic_plan* p,
+                  const LayerWs& ws, hipStream_t stream) {
+  launch_rope_table(p->s_pos, ws.cs, s->n_s, c->attn.head_dim, c->rope_theta, stream);
+  const LayerGemms l = layer_gemms(c, w, s->n_s, nullptr, ws);
+  if (gemm_route(l.qkv, kRope) == GemmRoute::kCut || gemm_route(l.wo, kResidual) == GemmRoute::kCut ||
+      gemm_route(l.gate_up, kSwiGLU) == GemmRoute::kCut || gemm_route(l.down, kResidual) == GemmRoute::kCut)
+    launch_gemm_clear(ws.gemm_count, stream);
+}
+
+// x = RMSNorm(h) w of the n rows, after h += the pending product's partial sums, if any.
+void add_norm(StreamSum* pending, float* h, const uint16_t* w, uint16_t* x, float* out, int n, int H, float eps,
+              hipStream_t stream) {
+  if (pending->partial != nullptr)
+    launch_rmsnorm_sum(*pending, h, w, x, out, eps, stream);
+  else
+    launch_rmsnorm(h, w, x, out, n, H, eps, stream);
+  pending->partial = nullptr;
+}
+
+// h += the product g; a streamed product stays pending until the next norm (add_norm).
+void residual_gemm(const GemmArgs& g, StreamSum* pending, hipStream_t stream) {
+  if (gemm_route(g, kResidual) == GemmRoute::kStream)
+    *pending = launch_gemm_stream(g, stream);
+  else
+    launch_gemm(g, kResidual, stream);
+}
+
+// One layer; the rotary table ws.cs is already filled.  pending: the last layer's
+// W_down product on entry, this layer's on return, where it is still to be added to h.
+epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s,
+                      const epic_plan* p, float* h, uint16_t* kc, uint16_t* vc, const LayerWs& ws, StreamSum* pending,
+                      hipStream_t stream) {
+  const int n = s->n_s, H = c->hidden;
+  const LayerGemms l = layer_gemms(c, w, n, h, ws);
+  add_norm(pending, h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
+  launch_gemm(l.qkv, kRope, stream);
   epic_attn_cfg ac = c->attn;
   ac.rope_theta = c->rope_theta;            // cached K was rotated with the model's base
   epic_status st = run_link_attention(&ac, s, p, ws.q, ws.k, ws.v, kc, vc, ws.o, nullptr, ws.attn, stream);
   if (st != EPIC_OK) return st;
-  g = GemmArgs{};
-  g.A = ws.o;
-  g.W = w->wo;
-  g.C = h;
-  g.M = n;
-  g.N = H;
-  g.K = hq * D;
-  g.partial = ws.gemm_partial;
-  g.tile_count = ws.gemm_count;
-  launch_gemm(g, kResidual, stream);
-  launch_rmsnorm(h, w->mlp_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
-  g = GemmArgs{};
-  g.A = ws.x;
-  g.W = w->w_gate_up;
-  g.act = ws.act;
-  g.M = n;
-  g.N = 2 * F;
-  g.K = H;
-  g.ffn = F;
-  g.partial = ws.gemm_partial;
-  g.tile_count = ws.gemm_count;
-  launch_gemm(g, kSwiGLU, stream);
-  g = GemmArgs{};
-  g.A = ws.act;
-  g.W = w->w_down;
-  g.C = h;
-  g.M = n;
-  g.N = H;
-  g.K = F;
-  g.partial = ws.gemm_partial;
-  g.tile_count = ws.gemm_count;
-  launch_gemm(g, kResidual, stream);
+  residual_gemm(l.wo, pending, stream);
+  add_norm(pending, h, w->mlp_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
+  launch_gemm(l.gate_up, kSwiGLU, stream);
+  residual_gemm(l.down, pending, stream);
   return hip_ok("decoder layer launch");
 }
 
@@ -212,9 +225,14 @@ extern "C" epic_status epic_link_layer(const epic_model_cfg* cfg, const epic_lay
   EPIC_CHECK_ARG(k_cache && v_cache, "KV cache pointers are NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const LayerWs ws = carve(cfg, sizes, static_cast<char*>(workspace));
-  launch_rope_table(plan_dev->s_pos, ws.cs, sizes->n_s, cfg->attn.head_dim, cfg->rope_theta, s);
-  launch_gemm_clear(ws.gemm_count, s);
-  return run_layer(cfg, w, sizes, plan_dev, hidden_s, k_cache, v_cache, ws, s);
+  start_layers(cfg, w, sizes, plan_dev, ws, s);
+  StreamSum pending{};
+  st = run_layer(cfg, w, sizes, plan_dev, hidden_s, k_cache, v_cache, ws, &pending, s);
+  if (st != EPIC_OK || pending.partial == nullptr) return st;
+  GemmArgs g{};
+  g.C = hidden_s;
+  launch_stream_finish(pending, g, kResidual, s);
+  return hip_ok("decoder layer launch");
 }
 
 extern "C" epic_status epic_link_model(const epic_model_cfg* cfg, const epic_layer_weights* layers,
@@ -244,13 +262,13 @@ extern "C" epic_status epic_link_model(const epic_model_cfg* cfg, const epic_lay
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const LayerWs ws = carve(cfg, sizes, static_cast<char*>(workspace));
-  launch_rope_table(plan_dev->s_pos, ws.cs, sizes->n_s, cfg->attn.head_dim, cfg->rope_theta, s);
-  launch_gemm_clear(ws.gemm_count, s);
+  start_layers(cfg, &layers[0], sizes, plan_dev, ws, s);
+  StreamSum pending{};
   for (int l = 0; l < cfg->n_layers; ++l) {
-    st = run_layer(cfg, &layers[l], sizes, plan_dev, hidden_s, k_caches[l], v_caches[l], ws, s);
+    st = run_layer(cfg, &layers[l], sizes, plan_dev, hidden_s, k_caches[l], v_caches[l], ws, &pending, s);
     if (st != EPIC_OK) return st;
   }
-  launch_rmsnorm(hidden_s, final_norm, nullptr, out_hidden, sizes->n_s, cfg->hidden, cfg->rms_eps, s);
+  add_norm(&pending, hidden_s, final_norm, nullptr, out_hidden, sizes->n_s, cfg->hidden, cfg->rms_eps, s);
   return hip_ok("final norm launch");
 }
 
@@ -293,7 +311,7 @@ extern "C" epic_status epic_gemm(int32_t epilogue, const uint16_t* a, const uint
   }
   gemm_workspace(workspace, &g.partial, &g.tile_count);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  launch_gemm_clear(g.tile_count, s);
+  if (gemm_route(g, epilogue) == GemmRoute::kCut) launch_gemm_clear(g.tile_count, s);
   launch_gemm(g, epilogue, s);
   return hip_ok("projection GEMM launch");
 }

@@ -1,0 +1,60 @@
+// The result of a weight-streaming GEMM before its consumer: fp32 partial sums of C in
+// planes [M][N], dealt as gemm_stream.hip describes.  A tile (TM rows x 64 columns) has
+// (last worker - first worker + 1) * kh planes, worker-major, i.e. in K order.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "gemm.h"
+
+namespace epic {
+
+struct StreamSum {
+  const float* partial;
+  int M, N;
+  int tm, tn, m_tiles, ks;   // rows and columns per tile, row tiles, K stages per tile (tile t = column tile * m_tiles + row tile)
+  int kh;                // wavefronts of a workgroup that share an MFMA tile by k-slices: a plane each
+  int units, G;          // K stages over all tiles, workers; units * G < 2^31
+
+  // worker w runs units [begin(w), begin(w + 1)); owner(v): the worker of unit v
+  __host__ __device__ int begin(int w) const { return int(int64_t(w) * units / G); }
+  __host__ __device__ int owner(int v) const {
+    return int((uint32_t(v + 1) * uint32_t(G) + uint32_t(units) - 1) / uint32_t(units)) - 1;
+  }
+  __host__ __device__ int planes(int tile) const { return (owner((tile + 1) * ks - 1) - owner(tile * ks) + 1) * kh; }
+
+  // columns n .. n + 3 of row m (n % 4 == 0), the planes added in K order; four planes'
+  // loads in flight at a time, the ones past the last repeating it and adding 0
+  __device__ __forceinline__ float4 sum4(int m, int n) const {
+    const int np = planes(n / tn * m_tiles + m / tm);
+    const size_t plane = size_t(M) * N;
+    const float* p = partial + size_t(m) * N + n;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int i = 0; i < np; i += 4) {
+      float4 x[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const float4*>(p + (i + j < np ? i + j : np - 1) * plane);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool ok = i + j < np;
+        v.x += ok ? x[j].x : 0.0f;
+        v.y += ok ? x[j].y : 0.0f;
+        v.z += ok ? x[j].z : 0.0f;
+        v.w += ok ? x[j].w : 0.0f;
+      }
+    }
+    return v;
+  }
+};
+
+// Enqueue the partial sums of g's product (g.partial: the GEMM workspace); returns how to sum them.
+StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream);
+// Whether the partial sums of a product of these sizes fit the GEMM workspace.
+bool stream_fits(int M, int N, int K);
+// Enqueue the pass that sums the planes and runs g's epilogue.
+void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStream_t stream);
+// Enqueue x += the summed planes, then RMSNorm of x's rows into out_bf16 or out_f32.
+void launch_rmsnorm_sum(const StreamSum& s, float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, float eps,
+                        hipStream_t stream);
+
+}  // namespace epic

@@ -193,3 +193,21 @@ def test_empty_and_rejected_shapes():
     with pytest.raises(el.EpicError) as e:                         # workspace too small
         el.epic_gemm(el.GEMM_STORE, a, w, c=torch.zeros((4, 128), device="cuda"), workspace=ws[:1024])
     assert e.value.status == 4
+
+
+STREAM = [  # weight streaming (up to 512 rows, fewer 256 x 128 tiles than CUs): edges of its row tiles
+    (32, 640, 1024, "store"),           # one full 32-row tile, 10 column tiles
+    (33, 640, 1024, "residual"),        # 64-row tiles from here
+    (64, 384, 4160, "swiglu"),          # 65 K stages, a 64-column split of 192
+    (65, 4096, 1088, "store"),          # 128-row tiles, 64 columns wide
+    (128, 2048, 14336, "residual"),     # ... 128 columns wide (at least 16 stages per worker)
+    (129, 4096, 8192, "store"),         # two row tiles, the second with one row
+    (512, 1024, 4096, "swiglu"),        # most rows
+    (5, 128, 64, "swiglu"),             # one stage per tile
+    (513, 128, 14336, "residual"),      # one row more: tiles cut along K, 37 parts
+]
+
+
+@pytest.mark.parametrize("m,n,k,epi", STREAM, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in STREAM])
+def test_weight_streaming(m, n, k, epi):
+    _run(m, n, k, epi, tag=80 + STREAM.index((m, n, k, epi)))

@@ -254,3 +254,14 @@ def test_compile_and_link_with_rerotation(wl):
             got = _f64(K[[offs[j] + t for t in rows]])
             assert np.abs(got - rot[j][rows]).max() <= ATOL, f"layer {layer} chunk {j}: re-rotated K"
     print(f"[gpu-test] {wl.name} re-rotated: final hidden max|err| {err:.3e}", flush=True)
+
+
+def test_streamed_residual_of_long_rows():
+    """Rows longer than the fused residual + norm pass keeps in registers (8192): the
+    W_O and W_down sums and the norm run as two passes.  Same bar as the other models."""
+    wl = _small("long_rows", [40, 33], 9, 4, hidden=8320, ffn=256, hq=4, hkv=2, d=64, layers=2)
+    st = _stage(wl, caches="synthetic")
+    st.run()
+    caches = [tuple([_f64(synth.chunk_cache(wl.seed, j, n, wl.num_kv_heads, wl.head_dim, 0.5, layer=l)[i])
+                     for j, n in enumerate(wl.chunk_lens)] for i in (0, 1)) for l in range(wl.n_layers)]
+    _check(st, wl.n_layers, caches)
