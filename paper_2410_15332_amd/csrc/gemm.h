@@ -43,5 +43,6 @@ GemmRoute gemm_route(const GemmArgs& g, int epi);
 // Zero the arrival counters (a kernel, so it can sit in a captured stream).
 void launch_gemm_clear(int* tile_count, hipStream_t stream);
 void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream);
+void launch_gemm_wide(const GemmArgs& g, int epi, int tm, hipStream_t stream);
 
 }  // namespace epic

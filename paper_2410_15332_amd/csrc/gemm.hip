@@ -9,18 +9,23 @@
 //   kRope     : the fused Q|K|V projection: q and k heads rotated at each row's linked
 //               position (rotary pairs (i, i + D/2)), v heads as they are; bf16 q, k, v
 //
-// Tiling: workgroup tile TM x TN (256 x 256, 192 x 256, 256 x 128, 128 x 128 or
-// 96 x 128), 8 wavefronts of 64 columns each (TN = 256: 2 x 4 wavefronts of TM/2 x 64,
-// i.e. 4 x 2 or 3 x 2 v_mfma_f32_32x32x16_bf16 tiles; TN = 128: 4 x 2 wavefronts of
-// TM/4 x 64, and at TM = 96 3 x 2 of 32 x 64 while the other two only stage
-// operands).  K runs in stages of 64 staged in LDS by direct buffer->LDS loads, NS
-// stages in LDS (2 at TN = 256, 3 at TN = 128; loads issued NS - 1 stages ahead of
-// use).  An operand stage is groups of 8 rows of 128 bytes
+// Three families of kernels, chosen by gemm_route below:
+//   - many rows: whole 256- or 192-row tiles of 256 columns (gemm_wide.hip);
+//   - short row sets: small tiles, K dealt in equal shares, sums in the consumer
+//     (gemm_stream.hip);
+//   - in between (this file): 128-column tiles, whole where one round of them fills the
+//     chip, else cut along K.
+//
+// Tiling here: workgroup tile TM x 128 (TM = 256, 128 or 96), 8 wavefronts of 64 columns
+// each (4 x 2 wavefronts of TM/4 x 64, and at TM = 96 3 x 2 of 32 x 64 while the other
+// two only stage operands).  K runs in stages of 64 staged in LDS by direct buffer->LDS
+// loads, three stages in LDS (loads issued two stages ahead of use).  An operand stage is
+// groups of 8 rows of 128 bytes
 // (one whole cache line per row: a load instruction that covers 16 half lines moves
 // about 0.6x the bytes per cycle of one that covers 8 whole lines); row r sits at byte
 // 128 r with its eight 16-byte chunks XOR-swizzled by (r / 2) % 8, so one load
 // instruction fills one group (1 KB) and the 16 lanes of each ds_read_b128 group
-// touch distinct banks.  For kSwiGLU the TN weight rows of a tile are gate/up in
+// touch distinct banks.  For kSwiGLU the weight rows of a tile are gate/up in
 // 32-row groups (gate j.., up j.., gate j+32.., ...), so a wavefront's two
 // 32-column MFMA tiles hold gate and up of the same 32 outputs.  For kRope the two
 // 32-column MFMA tiles of a wavefront hold the two halves of rotary pairs: with
@@ -29,14 +34,10 @@
 // 32-row groups, i = 0.., so lane column c of tile 0 and tile 1 are head
 // columns ip and ip + 64.
 //
-// Scheduling: at most one workgroup per CU (G of them), persistent.  With at least
-// a round of 256 x 256 tiles, whole 256-wide tiles (256 or 192 rows) are dealt in
-// rounds of G, G chosen so the rounds are (nearly) full; 256-wide tiles are never
-// cut.  With fewer tiles (short row sets): whole 96 x 128 or 128 x 128 tiles in one
-// round where they fill at least 3/4 of the CUs and K is short; else 256 x 128 tiles,
-// and the ones that do not fill whole rounds
-// (the last partial round plus one full round, or all of them) are cut along K into
-// G equal shares of K stages, one per workgroup, so every CU gets the same work.  A
+// Scheduling: at most one workgroup per CU (G of them), persistent.  Whole 96 x 128 or
+// 128 x 128 tiles run in one round; of the 256 x 128 tiles the ones that do not fill
+// whole rounds (the last partial round plus one full round, or all of them) are cut along
+// K into G equal shares of K stages, one per workgroup, so every CU gets the same work.  A
 // share runs its last segment (the one that starts a tile) first.
 // A tile cut across workgroups: each wavefront part of it has an arrival counter.
 // The owner of the tile's last K stage polls it (a bounded number of times) until
@@ -64,21 +65,21 @@ constexpr int kTM = 256, kBK = 64;
 constexpr int kThreads = 512;
 constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
 constexpr int kMaxWorkers = 256;                        // one workgroup per CU
-constexpr int kPartialFloats = kTM * 256;               // fp32 partial sums of the largest tile
+constexpr int kPartialFloats = kTM * 256;               // per partial slot (twice a 256 x 128 tile)
 constexpr int kMaxSplitTiles = 2 * kMaxWorkers;
 constexpr int kCounters = kMaxSplitTiles * (kThreads / 64);   // one per (cut tile, wavefront)
 constexpr int kMinUnits = 4;                            // K stages per workgroup, at least
 constexpr int kStreamRows = 512;                        // rows up to which weight streaming beats cut tiles
 
-template <int TM, int TN>
+constexpr int TN = 128;                                 // columns of a workgroup tile
+
+template <int TM>
 struct Shape {
-  static_assert((TM == 256 && (TN == 128 || TN == 256)) || (TM == 192 && TN == 256) ||
-                    ((TM == 128 || TM == 96) && TN == 128),
-                "tile shape");
-  static constexpr int NS = TN == 256 ? 2 : 3;          // LDS stages (128 / 112 / 144 / 96 / 84 KB)
+  static_assert(TM == 256 || TM == 128 || TM == 96, "tile shape");
+  static constexpr int NS = 3;                          // LDS stages (144 / 96 / 84 KB)
   // wavefronts along M (TM = 96: 3 x 2 wavefronts compute, the other two only stage
   // operands and meet the barriers)
-  static constexpr int WAVES_M = TN == 256 ? 2 : TM >= 128 ? 4 : TM / 32;
+  static constexpr int WAVES_M = TM >= 128 ? 4 : TM / 32;
   static constexpr int WM = TM / WAVES_M;               // rows per wavefront
   static constexpr int I = WM / 32;                     // 32-row MFMA tiles per wavefront
   static constexpr int J = 2;                           // 32-column MFMA tiles per wavefront
@@ -98,10 +99,10 @@ struct GemmPlan {
   int polls;                   // counter polls of a cut tile's last-stage owner before it falls back
 };
 
-template <int TM, int TN>
+template <int TM>
 struct GemmLds {
-  char a[Shape<TM, TN>::NS][Shape<TM, TN>::A_STAGE];
-  char b[Shape<TM, TN>::NS][Shape<TM, TN>::B_STAGE];
+  char a[Shape<TM>::NS][Shape<TM>::A_STAGE];
+  char b[Shape<TM>::NS][Shape<TM>::B_STAGE];
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -132,20 +133,20 @@ struct Cursor {
   int u, tile, kt, kbeg, kend;
 };
 
-template <int EPI, int TM, int TN>
+template <int EPI, int TM>
 __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan p) {
-  using SH = Shape<TM, TN>;
+  using SH = Shape<TM>;
   constexpr int NS = SH::NS, I = SH::I, J = SH::J, NLA = SH::NLA, NLB = SH::NLB, NL = SH::NL;
-  __shared__ __attribute__((aligned(1024))) GemmLds<TM, TN> lds;
+  __shared__ __attribute__((aligned(1024))) GemmLds<TM> lds;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // wavefront tile: rows wm*WM.., columns wn*64..  At TN = 128 the two wavefronts of
+  // wavefront tile: rows wm*WM.., columns wn*64..  The two wavefronts of
   // each SIMD (wavefronts w and w + 4) take different row halves, so a tile whose
   // rows past M leave half the wavefronts idle still keeps every SIMD busy.  Wavefronts
   // with wm >= WAVES_M (TM = 96: wavefronts 6 and 7) compute and store nothing.
-  const int wm = TN == 128 ? wv >> 1 : wv % SH::WAVES_M;
-  const int wn = TN == 128 ? wv & 1 : wv / SH::WAVES_M;
+  const int wm = wv >> 1;
+  const int wn = wv & 1;
   const int w = blockIdx.x;
   const int wr = p.G % 8 == 0 ? (w % 8) * (p.G / 8) + w / 8 : w;   // XCD-contiguous worker index
   const int64_t su = p.sk_units;
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan 
   const bool a_wave = wv < 4;
   // With M <= 128 (one row tile) the A row groups 16..31 hold no row of A: their
   // loading wavefronts issue nothing (none of their waits then has anything to wait for).
-  const bool dma_idle = TM == 256 && TN == 128 && a_wave && g.M <= 128 && wv >= 2;
+  const bool dma_idle = TM == 256 && a_wave && g.M <= 128 && wv >= 2;
   const int nl = a_wave ? NLA : NLB;                   // loads per stage of this wavefront
   const int grp0 = nl * (wv & 3);
   const int lrow = lane >> 3;                              // row within an 8-row group
@@ -402,7 +403,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan 
     int mt, nt;
     tile_mn(c.tile, mt, nt);
     // no rows of this part (past the tile, or every row past M): nothing to write
-    if (TN == 128 && (wm >= SH::WAVES_M || mt * TM + wm * SH::WM >= g.M)) return;
+    if (wm >= SH::WAVES_M || mt * TM + wm * SH::WM >= g.M) return;
     if (c.kbeg == 0 && c.kend == p.ks) {
 #pragma unroll
       for (int h = 0; h < NCH; ++h) {
@@ -413,9 +414,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan 
       }
       return;
     }
-    // Only 128-wide tiles are ever cut (the planner deals 256-wide tiles whole), so the
-    // 256-wide instantiations carry no partial protocol (and its registers).
-    if constexpr (TN == 256) return;
+    // Only 256-row tiles are ever cut, so the others carry no partial protocol (and its registers).
+    if constexpr (TM != 256) return;
     const int q = c.tile - p.dp_tiles;
     const int64_t U = p.sk_units;
     auto owner = [&](int64_t v) __attribute__((always_inline)) { return int(((v + 1) * p.G + U - 1) / U - 1); };
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan 
   // loads of u + 1 visible, every read of buffer u % NS done) refills that buffer
   // with unit u + NS and reads the first k-slice of u + 1.  Loads past the last
   // unit repeat it, so every step leaves the same number in flight.  (One barrier
-  // per two units measured slower at TN = 128.)
+  // per two units measured slower.)
   Cursor cc, dc;
   seek(cc, 0);
   dc = cc;
@@ -554,10 +554,8 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs g, GemmPlan 
   read(f0, 0, 0);
   zero_acc();
   // rows of this wavefront's part of the current tile exist (else it only stages and
-  // syncs); only the 128-column tiles of short row sets skip (256-column tiles run
-  // when there are many row tiles, where the saving is small)
+  // syncs)
   auto live_in = [&](int tile) __attribute__((always_inline)) {
-    if constexpr (TN != 128) return true;
     int mt, nt;
     tile_mn(tile, mt, nt);
     return __builtin_amdgcn_readfirstlane(int(wm < SH::WAVES_M && mt * TM + wm * SH::WM < g.M)) != 0;
@@ -617,10 +615,8 @@ int finish_polls() {
   return int(std::min<long>(std::max<long>(v, 0), 1 << 20));
 }
 
-template <int EPI, int TM, int TN>
+template <int EPI, int TM>
 void launch_tn(const GemmArgs& g, bool whole_tiles, hipStream_t stream) {
-  static_assert(TN == 128 || TN == 256, "tile width");
-  if (TN == 256) whole_tiles = true;                 // the 256-wide kernels finish whole tiles only
   GemmPlan p{};
   p.m_tiles = cdiv(g.M, TM);
   p.n_tiles = EPI == kSwiGLU ? g.ffn / (TN / 2) : cdiv(g.N, TN);
@@ -628,10 +624,9 @@ void launch_tn(const GemmArgs& g, bool whole_tiles, hipStream_t stream) {
   p.gm = p.m_tiles < 8 ? p.m_tiles : 8;
   const int64_t tiles = int64_t(p.m_tiles) * p.n_tiles;
   if (whole_tiles) {
-    // rounds of whole tiles, as few workgroups as keep the rounds full
-    const int64_t rounds = (tiles + kMaxWorkers - 1) / kMaxWorkers;
-    p.G = int((tiles + rounds - 1) / rounds);
-    p.dp_rounds = int(rounds);
+    // one round of whole tiles (a multiple of 8 workgroups, for the XCD-contiguous order)
+    p.G = int((tiles + 7) / 8 * 8);
+    p.dp_rounds = 1;
     p.dp_tiles = int(tiles);                         // a short last round leaves some workgroups idle
     p.sk_units = 0;
   } else {
@@ -643,16 +638,14 @@ void launch_tn(const GemmArgs& g, bool whole_tiles, hipStream_t stream) {
     p.sk_units = int((tiles - p.dp_tiles) * p.ks);
   }
   p.polls = finish_polls();
-  gemm_kernel<EPI, TM, TN><<<dim3(p.G), kThreads, 0, stream>>>(g, p);
+  gemm_kernel<EPI, TM><<<dim3(p.G), kThreads, 0, stream>>>(g, p);
 }
 
 template <int EPI>
 void launch_epi(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
-  if (r == GemmRoute::kWhole192) launch_tn<EPI, 192, 256>(g, true, stream);
-  else if (r == GemmRoute::kWhole256) launch_tn<EPI, 256, 256>(g, true, stream);
-  else if (r == GemmRoute::kWhole96) launch_tn<EPI, 96, 128>(g, true, stream);
-  else if (r == GemmRoute::kWhole128) launch_tn<EPI, 128, 128>(g, true, stream);
-  else launch_tn<EPI, 256, 128>(g, false, stream);
+  if (r == GemmRoute::kWhole96) launch_tn<EPI, 96>(g, true, stream);
+  else if (r == GemmRoute::kWhole128) launch_tn<EPI, 128>(g, true, stream);
+  else launch_tn<EPI, 256>(g, false, stream);
 }
 
 }  // namespace
@@ -661,18 +654,18 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
   // At least a round of 256 x 256 tiles: whole tiles only (measured: cutting tiles
   // along K costs about one tile time in partial traffic, more than a short last
   // round).  The tiles are 256 or 192 rows high, whichever takes less time: a round
-  // of 192-row tiles takes about 15/16 of the time of one of 256-row tiles
-  // (measured; a stage streams the same 256 weight rows), so 192 rows win where
-  // they save a round or more of the short last round: at 736 rows, 448 tiles of
-  // 192 rows in 2 rounds of 224 workgroups instead of 336 of 256 rows in 2 rounds
-  // of 168.
+  // of 192-row tiles takes 0.77-0.84 of one of 256-row tiles (gate|up, W_down, W_O and
+  // Q|K|V of 20 560 rows), counted as 13/16.  So W_down and W_O of 20 560 rows run 7 rounds
+  // of 192 rows (1925 and 618 us) instead of 6 of 256 (1961 and 634), gate|up 36 rounds
+  // of 256 (3607 us) instead of 48 of 192 (3755), and gate|up of 736 rows 2 rounds of
+  // 192 rows on 224 CUs instead of 2 of 256 on 168.
   const bool swiglu = epi == kSwiGLU;
   const int m_tiles = cdiv(g.M, kTM);
   const int n256 = swiglu ? (g.ffn % 128 == 0 ? g.ffn / 128 : 0) : cdiv(g.N, 256);
   if (int64_t(m_tiles) * n256 >= kMaxWorkers) {
     const int64_t r256 = (int64_t(m_tiles) * n256 + kMaxWorkers - 1) / kMaxWorkers;
     const int64_t r192 = (int64_t(cdiv(g.M, 192)) * n256 + kMaxWorkers - 1) / kMaxWorkers;
-    return r192 * 15 < r256 * 16 ? GemmRoute::kWhole192 : GemmRoute::kWhole256;
+    return r192 * 13 < r256 * 16 ? GemmRoute::kWhole192 : GemmRoute::kWhole256;
   }
   // Fewer: with a short K and one round of 96 x 128 or 128 x 128 tiles that fills at
   // least 3/4 of the CUs, those tiles whole (96 rows where they make such a round: more
@@ -720,6 +713,8 @@ void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream) {
   const GemmRoute r = gemm_route(g, epi);
   if (r == GemmRoute::kStream)
     launch_stream_finish(launch_gemm_stream(g, stream), g, epi, stream);
+  else if (r == GemmRoute::kWhole256 || r == GemmRoute::kWhole192)
+    launch_gemm_wide(g, epi, r == GemmRoute::kWhole256 ? 256 : 192, stream);
   else if (epi == kStoreF32)
     launch_epi<kStoreF32>(g, r, stream);
   else if (epi == kRope)

@@ -211,3 +211,17 @@ STREAM = [  # weight streaming (up to 512 rows, fewer 256 x 128 tiles than CUs):
 @pytest.mark.parametrize("m,n,k,epi", STREAM, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in STREAM])
 def test_weight_streaming(m, n, k, epi):
     _run(m, n, k, epi, tag=80 + STREAM.index((m, n, k, epi)))
+
+
+WIDE = [  # whole 256-column tiles: one K stage, an odd number, several tiles per workgroup, tails
+    (2100, 8192, 64, "store"),          # 9 x 32 tiles of one stage each
+    (2100, 8320, 192, "residual"),      # 3 stages; the last column tile is 128 wide
+    (3000, 11520, 448, "swiglu"),       # 7 stages, ffn 5760
+]
+
+
+@pytest.mark.parametrize("m,n,k,epi", WIDE, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in WIDE])
+def test_wide_tiles(m, n, k, epi):
+    rng = np.random.default_rng(11)
+    sample = sorted(set([0, 1, 127, 128, 191, 192, 255, 256, m - 2, m - 1] + rng.integers(0, m, 90).tolist()))
+    _run(m, n, k, epi, tag=100 + WIDE.index((m, n, k, epi)), sample=sample)

@@ -265,3 +265,20 @@ def test_streamed_residual_of_long_rows():
     caches = [tuple([_f64(synth.chunk_cache(wl.seed, j, n, wl.num_kv_heads, wl.head_dim, 0.5, layer=l)[i])
                      for j, n in enumerate(wl.chunk_lens)] for i in (0, 1)) for l in range(wl.n_layers)]
     _check(st, wl.n_layers, caches)
+
+
+MANY_ROWS = [  # compile plans of at least 256 tiles of 256 x 256: wide whole tiles, their rotary and SwiGLU epilogues
+    _small("many_rows_d64", [65] * 128, 9, 3, hidden=256, ffn=1024, hq=16, hkv=8, d=64, layers=1),
+    # 21 heads of 128: the last column tile is half past the end
+    _small("many_rows_d128", [50] * 128, 9, 3, hidden=256, ffn=1024, hq=7, hkv=7, d=128, layers=1),
+]
+
+
+@pytest.mark.parametrize("wl", MANY_ROWS, ids=[w.name for w in MANY_ROWS])
+def test_compile_of_many_rows(wl):
+    st = _stage(wl, caches="compile")
+    st.run()
+    torch.cuda.synchronize()
+    ref = _oracle_compiled_caches(wl, wl.n_layers)
+    _check_chunk_caches(st, ref)
+    _check(st, wl.n_layers, ref)
