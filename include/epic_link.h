@@ -136,7 +136,11 @@ typedef struct {
  *                         re-rotated (K only), or 0
  *   tiles[n_tiles * 4]    (first S row, S rows, first partial or -1, splits)
  *   work[n_work * 8]      (tile, first linked block, end linked block, partial or -1,
- *                         leading 4-block KV tiles that need no mask, 0, 0, 0)
+ *                         leading 4-block KV tiles that need no mask, 0, 0, 0).
+ *                         Decode plans of requests that share chunk blocks also have items
+ *                         that carry rows of several requests (last int 1: n listed S rows
+ *                         over blocks all of them link) or a list of blocks (last int 2),
+ *                         and list entries (first int -1)
  */
 typedef struct {
   int32_t* s_pos;

@@ -596,9 +596,267 @@ struct DecodeReq {
   int extra = 0;           // new blocks
 };
 
+// ---- Decode over shared chunk caches.  Requests that link the same cached blocks each
+// read them for the sake of a few rows.  Where that repeats enough, the plan lets one
+// work item carry the rows of several requests over the blocks they have in common: the
+// blocks are read once per 16-row tile instead of once per request.  Each row still
+// gets one partial per item, in the slots of its own request's tile, so the combine is
+// the ordinary one.
+//
+// Item kinds (work[7]): kItemRange as ever; kItemShared: blocks [work[1], work[2]) of one
+// request's table with no causal mask, work[5] S rows listed as pairs (S row, partial * 16 +
+// row within its tile); kItemList: work[2] blocks (work[1] = 0) of the tile's own request
+// listed by index, with the mask.  Lists sit in extension entries from entry work[6] on:
+// work[0] = -1, work[2..7] six int32 of the list.
+
+struct SharedWork {
+  std::vector<int32_t> tiles, work;        // plan arrays
+  int n_partials = 0;
+};
+
+struct SharedRun {                          // blocks [i, i + n) of request b's table, and who else links them
+  int b, i, n;
+  std::vector<std::pair<int, int>> members; // (request, first block in its table)
+};
+
+// Longest-first makespan of items (cost each) on the slots one head gets.
+double makespan(std::vector<double> cost, int slots) {
+  std::sort(cost.begin(), cost.end(), std::greater<double>());
+  std::vector<double> heap(static_cast<size_t>(slots), 0.0);
+  double end = 0.0;
+  for (const double c : cost) {
+    std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+    heap.back() += c;
+    end = std::max(end, heap.back());
+    std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+  }
+  return end;
+}
+
+// Work items over shared blocks for 16-row tiles; false where sharing does not pay.
+// A block is shared if several requests link it with the same valid length, none twice,
+// and all of it precedes their new rows (so it needs no causal mask).
+bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::vector<DecodeReq>& dr,
+                   const epic_attn_cfg* cfg, SharedWork* out) {
+  const int G = cfg->num_q_heads / cfg->num_kv_heads, R = kTileRowsTiny / G;
+  const int batch = static_cast<int>(dr.size());
+  if (R < 2) return false;
+  int max_id = -1;
+  for (int i = 0; i < ps->n_linked_blocks; ++i) {
+    const int id = prev->linked_blocks[i];
+    if (id < 0 || id > (1 << 26)) return false;           // (validated later)
+    max_id = std::max(max_id, id);
+  }
+  struct Ref {
+    uint64_t sig = 0;
+    int count = 0, last = -1, len = 0;
+    bool bad = false;
+  };
+  std::vector<Ref> ref(static_cast<size_t>(max_id + 1));
+  int64_t total = 0;
+  auto frozen = [&](int b) { return dr[b].e - dr[b].a - (dr[b].room > 0 ? 1 : 0); };   // blocks that take no new row
+  for (int b = 0; b < batch; ++b) {
+    if (dr[b].t == 0) continue;
+    total += dr[b].e - dr[b].a + dr[b].extra;
+    const uint64_t h = (uint64_t(b) + 1) * 0x9E3779B97F4A7C15ull;
+    for (int i = 0; i < frozen(b); ++i) {
+      Ref& x = ref[prev->linked_blocks[dr[b].a + i]];
+      const int len = prev->block_len[dr[b].a + i];
+      x.bad = x.bad || x.last == b || (x.count > 0 && x.len != len);
+      x.sig += (h ^ (h >> 29)) * 0xBF58476D1CE4E5B9ull;
+      x.last = b;
+      x.len = len;
+      ++x.count;
+    }
+  }
+  auto sig_of = [&](int b, int i) {
+    const Ref& x = ref[prev->linked_blocks[dr[b].a + i]];
+    return x.count > 1 && !x.bad ? x.sig : 0;
+  };
+  // runs of blocks with the same set of requests; a run of one request is its own
+  std::vector<SharedRun> runs;
+  std::vector<int> run_at(static_cast<size_t>(max_id + 1), -1);   // by the run's first block
+  std::vector<std::vector<std::pair<int, int>>> own(batch);       // [i0, i1) of each request, unshared
+  auto add_own = [&](int b, int i, int n) {
+    if (!own[b].empty() && own[b].back().second == i) own[b].back().second = i + n;
+    else own[b].emplace_back(i, i + n);
+  };
+  for (int b = 0; b < batch; ++b) {
+    if (dr[b].t == 0) continue;
+    const int fz = frozen(b), nb = dr[b].e - dr[b].a + dr[b].extra;
+    for (int i = 0; i < nb;) {
+      const uint64_t sig = i < fz ? sig_of(b, i) : 0;
+      int j = i + 1;
+      while (j < nb && (j < fz ? sig_of(b, j) : 0) == sig) ++j;
+      if (sig == 0) {
+        add_own(b, i, j - i);
+      } else {
+        const int32_t* ids = prev->linked_blocks + dr[b].a + i;
+        int& r = run_at[ids[0]];
+        if (r < 0) {
+          r = static_cast<int>(runs.size());
+          runs.push_back(SharedRun{b, i, j - i, {{b, i}}});
+        } else if (runs[r].n == j - i &&
+                   std::equal(ids, ids + (j - i), prev->linked_blocks + dr[runs[r].b].a + runs[r].i)) {
+          runs[r].members.emplace_back(b, i);
+        } else {
+          add_own(b, i, j - i);                           // the same blocks in another order
+        }
+      }
+      i = j;
+    }
+  }
+  // groups of at most R rows over a run, about equal
+  struct Group {
+    int run;
+    std::vector<std::pair<int, int>> members;
+  };
+  std::vector<Group> groups;
+  int64_t read = 0;
+  for (size_t r = 0; r < runs.size(); ++r) {
+    int rows = 0;
+    for (const auto& m : runs[r].members) rows += dr[m.first].t;
+    const int parts = cdiv(rows, R), each = cdiv(rows, parts);
+    Group g{static_cast<int>(r), {}};
+    int fill = 0;
+    for (const auto& m : runs[r].members) {
+      const int t = dr[m.first].t;
+      if (fill > 0 && (fill + t > R || fill >= each)) {
+        groups.push_back(g);
+        g.members.clear();
+        fill = 0;
+      }
+      g.members.push_back(m);
+      fill += t;
+    }
+    groups.push_back(g);
+  }
+  for (const Group& g : groups) read += runs[g.run].n;
+  for (const auto& o : own)
+    for (const auto& x : o) read += x.second - x.first;
+  if (read * 4 > total * 3) return false;                 // fewer than a quarter of the block reads saved
+  // Unshared blocks: ranges of at least kListBelow blocks as items of their own, the
+  // rest of a request's listed together.
+  constexpr int kListBelow = 48, kListMost = 96;
+  struct Item {
+    int kind, group, b, i0, i1;                           // blocks [i0, i1) of b's table, or of its list
+    int parts;
+  };
+  std::vector<std::vector<int>> lists(batch);
+  std::vector<Item> whole;
+  for (size_t k = 0; k < groups.size(); ++k) {
+    const SharedRun& r = runs[groups[k].run];
+    whole.push_back(Item{kItemShared, static_cast<int>(k), r.b, r.i, r.i + r.n, static_cast<int>(groups[k].members.size())});
+  }
+  for (int b = 0; b < batch; ++b) {
+    for (const auto& x : own[b]) {
+      if (x.second - x.first >= kListBelow) whole.push_back(Item{kItemRange, -1, b, x.first, x.second, 1});
+      else
+        for (int i = x.first; i < x.second; ++i) lists[b].push_back(i);
+    }
+    for (int i = 0; i < static_cast<int>(lists[b].size()); i += kListMost)
+      whole.push_back(Item{kItemList, -1, b, i, std::min<int>(i + kListMost, static_cast<int>(lists[b].size())), 1});
+  }
+  // split: pieces of at most `split` blocks, by the estimated launch as in split_blocks
+  const int slots = std::max(1, kShapeTiny.slots / cfg->num_kv_heads);
+  auto pieces = [](const Item& it, int split) { return cdiv(it.i1 - it.i0, split); };
+  int longest = 1, best = 1;
+  for (const Item& it : whole) longest = std::max(longest, it.i1 - it.i0);
+  double best_time = 0.0;
+  for (const int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
+    const int split = std::max(16, cdiv(longest, parts));
+    std::vector<double> cost;
+    for (const Item& it : whole)
+      for (int p = pieces(it, split), k = 0; k < p; ++k)
+        cost.push_back(cdiv(cdiv(it.i1 - it.i0, p), kKvTileBlocks) + kShapeTiny.item_overhead +
+                       kShapeTiny.partial_cost * (it.kind == kItemShared ? 1 + 0.25 * it.parts : 1));
+    if (cost.size() > 16u * static_cast<size_t>(slots)) break;
+    const double t = makespan(cost, slots);
+    if (parts == 1 || t < best_time * 0.97) best_time = t, best = split;
+    if (split == 16) break;
+  }
+  // tiles: one per request with rows; partials of a tile are consecutive
+  std::vector<int> tile_of(batch, -1), n_part(batch, 0), row0(batch, 0), base(batch, 0);
+  int n_tiles = 0, rows = 0, lb = 0;
+  for (int b = 0; b < batch; ++b) {
+    row0[b] = rows;
+    base[b] = lb;
+    rows += dr[b].t;
+    lb += dr[b].e - dr[b].a + dr[b].extra;
+    if (dr[b].t > 0) tile_of[b] = n_tiles++;
+  }
+  std::vector<Item> items;
+  for (const Item& it : whole) {
+    const int p = pieces(it, best), n = it.i1 - it.i0;
+    for (int k = 0; k < p; ++k)
+      items.push_back(Item{it.kind, it.group, it.b, it.i0 + int(int64_t(n) * k / p), it.i0 + int(int64_t(n) * (k + 1) / p),
+                           it.parts});
+  }
+  // longest first; equal lengths keep their order, so the groups of one run stay together
+  std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.i1 - x.i0 > y.i1 - y.i0; });
+  for (const Item& it : items) {
+    if (it.kind == kItemShared)
+      for (const auto& m : groups[it.group].members) ++n_part[m.first];
+    else
+      ++n_part[it.b];
+  }
+  int part = 0;
+  std::vector<int> next(batch, 0);
+  out->tiles.clear();
+  for (int b = 0; b < batch; ++b) {
+    if (tile_of[b] < 0) continue;
+    const bool split_tile = n_part[b] > 1;
+    out->tiles.insert(out->tiles.end(), {row0[b], dr[b].t, split_tile ? part : -1, n_part[b]});
+    next[b] = split_tile ? part : -1;
+    if (split_tile) part += n_part[b];
+  }
+  out->n_partials = part;
+  auto take = [&](int b) { return next[b] < 0 ? -1 : next[b]++; };
+  const int n_items = static_cast<int>(items.size());
+  std::vector<int32_t> ext;
+  auto extend = [&](const std::vector<int32_t>& list) {   // returns the first extension entry's index
+    const int at = n_items + static_cast<int>(ext.size()) / kWorkInts;
+    for (size_t i = 0; i < list.size(); i += kExtInts) {
+      ext.insert(ext.end(), {-1, 0});
+      for (size_t j = i; j < i + kExtInts; ++j) ext.push_back(j < list.size() ? list[j] : 0);
+    }
+    return at;
+  };
+  out->work.clear();
+  for (const Item& it : items) {
+    int32_t wk[kWorkInts] = {tile_of[it.b], base[it.b] + it.i0, base[it.b] + it.i1, -1, 0, 0, 0, it.kind};
+    std::vector<int32_t> list;
+    if (it.kind == kItemShared) {
+      for (const auto& m : groups[it.group].members) {
+        const int p = take(m.first);
+        for (int t = 0; t < dr[m.first].t; ++t) {
+          list.push_back(row0[m.first] + t);
+          list.push_back(p < 0 ? -1 : p * kTileRowsTiny + t);
+        }
+      }
+      wk[5] = static_cast<int32_t>(list.size()) / 2;
+      wk[6] = extend(list);
+    } else {
+      wk[3] = take(it.b);
+      if (it.kind == kItemList) {
+        for (int i = it.i0; i < it.i1; ++i) list.push_back(base[it.b] + lists[it.b][i]);
+        wk[1] = 0;
+        wk[2] = wk[5] = static_cast<int32_t>(list.size());
+        wk[6] = extend(list);
+      }
+    }
+    out->work.insert(out->work.end(), wk, wk + kWorkInts);
+  }
+  out->work.insert(out->work.end(), ext.begin(), ext.end());
+  // a caller with the fixed scratch array must not lose a plan that fitted it
+  const int64_t bytes = (int64_t(part) * cfg->num_kv_heads * kTileRowsTiny + 64) * (cfg->head_dim + 1) * 4;
+  return bytes <= int64_t(EPIC_NOALLOC_SCRATCH_BYTES);
+}
+
 epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const int32_t* new_tokens,
                          const epic_attn_cfg* cfg, int32_t n_free, epic_plan_sizes* out,
-                         std::vector<Tile>* tiles_out, int* split_out, std::vector<DecodeReq>* dr_out) {
+                         std::vector<Tile>* tiles_out, int* split_out, std::vector<DecodeReq>* dr_out,
+                         SharedWork* shared) {
   EPIC_CHECK_ARG(ps && prev && out, "NULL previous plan, sizes or output");
   EPIC_CHECK_ARG(n_free >= 0, "n_free %d < 0", n_free);
   epic_status st = validate_attn_cfg(cfg);
@@ -644,7 +902,23 @@ epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const
     return fail(EPIC_ERR_NO_PRIVATE_BLOCKS, "plan needs %lld new blocks, %d free", (long long)n_take, n_free);
   epic_plan_sizes s{};
   s.batch = batch;
-  choose_tiles(rr, cfg, &s, tiles_out, split_out);
+  // plans for the decode kernel, one tile per request: perhaps over shared blocks
+  const int G = cfg->num_q_heads / cfg->num_kv_heads;
+  bool tiny = (cfg->tile_rows == 0 || cfg->tile_rows == kTileRowsTiny) && cfg->kv_split_blocks == 0 && G <= kTileRowsTiny;
+  int n_tiles = 0;
+  for (const DecodeReq& d : dr) {
+    tiny = tiny && d.t <= kTileRowsTiny / G;
+    n_tiles += d.t > 0;
+  }
+  if (tiny && n_tiles > 1 && shared_decode(ps, prev, dr, cfg, shared)) {
+    s.tile_rows = kTileRowsTiny;
+    s.n_tiles = n_tiles;
+    s.n_work = static_cast<int32_t>(shared->work.size()) / kWorkInts;
+    s.n_partials = shared->n_partials;
+  } else {
+    shared->work.clear();
+    choose_tiles(rr, cfg, &s, tiles_out, split_out);
+  }
   s.n_s = static_cast<int32_t>(n_s);
   s.n_linked_blocks = static_cast<int32_t>(n_lb);
   s.n_private = static_cast<int32_t>(n_priv);
@@ -662,8 +936,9 @@ extern "C" epic_status epic_plan_decode_sizes(const epic_plan_sizes* prev_sizes,
   clear_error();
   std::vector<Tile> tiles;
   std::vector<DecodeReq> dr;
+  SharedWork shared;
   int split = 0;
-  return decode_shape(prev_sizes, prev, new_tokens, cfg, n_free, out, &tiles, &split, &dr);
+  return decode_shape(prev_sizes, prev, new_tokens, cfg, n_free, out, &tiles, &split, &dr, &shared);
 }
 
 extern "C" epic_status epic_plan_decode(const epic_plan_sizes* prev_sizes, const epic_plan* prev,
@@ -674,8 +949,9 @@ extern "C" epic_status epic_plan_decode(const epic_plan_sizes* prev_sizes, const
   epic_plan_sizes chk;
   std::vector<Tile> tiles;
   std::vector<DecodeReq> dr;
+  SharedWork shared;
   int split = 0;
-  epic_status st = decode_shape(prev_sizes, prev, new_tokens, cfg, n_free, &chk, &tiles, &split, &dr);
+  epic_status st = decode_shape(prev_sizes, prev, new_tokens, cfg, n_free, &chk, &tiles, &split, &dr, &shared);
   if (st != EPIC_OK) return st;
   EPIC_CHECK_ARG(sizes && plan, "NULL sizes or plan");
   EPIC_CHECK_ARG(std::memcmp(&chk, sizes, sizeof(chk)) == 0, "sizes do not match this previous plan");
@@ -739,6 +1015,11 @@ extern "C" epic_status epic_plan_decode(const epic_plan_sizes* prev_sizes, const
   plan->blk_off[chk.batch] = lb;
   if (row != chk.n_s || lb != chk.n_linked_blocks || pv != chk.n_private || fl != n_take)
     return fail(EPIC_ERR_INVALID_ARG, "internal planner inconsistency (decode)");
+  if (!shared.work.empty()) {
+    std::copy(shared.tiles.begin(), shared.tiles.end(), plan->tiles);
+    std::copy(shared.work.begin(), shared.work.end(), plan->work);
+    return EPIC_OK;
+  }
   return write_work(tiles, split, chk, plan);
 }
 

@@ -15,6 +15,9 @@ constexpr int kTileRowsTiny = 16;
 inline bool valid_tile_rows(int r) { return r == kTileRowsTiny || r == kTileRowsSmall || r == kTileRowsLarge; }
 constexpr int kKvTileBlocks = 4;   // KV blocks staged per attention iteration (64 keys)
 constexpr int kWorkInts = 8;       // int32 per attention work item
+constexpr int kExtInts = 6;        // list entries per extension entry of the work array
+// kinds of work items (work[7]); the last two only in decode plans of shared caches
+constexpr int kItemRange = 0, kItemShared = 1, kItemList = 2;
 constexpr float kLog2eHost = 1.442695040888963407f;
 
 epic_status validate_attn_cfg(const epic_attn_cfg* cfg);

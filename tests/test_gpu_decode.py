@@ -16,7 +16,7 @@ torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
 import synth  # noqa: E402
-from synth.configs import get_config  # noqa: E402
+from synth.configs import AttnWorkload, get_config  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -113,3 +113,19 @@ def test_decode_batched_c4():
 def test_decode_after_c5_long_context():
     """One request of 131 328 linked tokens (LegoLink-32): a token, then four more."""
     _run_decode(get_config("c5", k=32), [[1], [4]])
+
+
+SHARED = [  # (query heads, KV heads, head dim): 16, 4, 2 and 1 S rows per 16-row tile
+    (8, 8, 64), (32, 8, 128), (16, 2, 64), (16, 1, 128),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,d", SHARED)
+def test_decode_over_shared_chunks(hq, hkv, d):
+    """Requests that link the same chunks (in different orders, one twice in a request,
+    partial last blocks): work items carry rows of several requests over shared blocks."""
+    rows = 16 // (hq // hkv)
+    reqs = [[0, 1, 2], [1, 0, 2], [2, 2, 3], [0, 3], [3, 1, 0], [1, 2], [0, 1, 2]]
+    wl = AttnWorkload(f"shared_{hq}_{hkv}_{d}", 77, hq, hkv, d, 16, reqs, [533, 800, 47, 1200],
+                      [5, 16, 31, 1, 9, 20, 64], 16)
+    _run_decode(wl, [[1] * 7, [min(rows, x) for x in (2, 0, 1, 3, 1, 2, 1)], [1] * 7], spare_blocks=64)

@@ -489,3 +489,115 @@ def test_work_items_longest_first(lens, suffix, k, split):
         ranges.sort()
         assert all(a[1] == b[0] for a, b in zip(ranges, ranges[1:])), f"tile {t}: segments not contiguous"
         assert len(ranges) == int(tiles[t, 3])
+
+
+def _items_of_rows(sizes, d):
+    """Blocks that each S row's work items cover, from the plan's own item format, and the
+    partial slots they write: {row: [(linked block index, ...), ...]}, {(tile, partial)}."""
+    work = d["work"].reshape(-1, 8)
+    tiles = d["tiles"].reshape(-1, 4)
+
+    def listed(wk, n):
+        return [int(work[wk[6] + i // 6, 2 + i % 6]) for i in range(n)]
+
+    tile_of = {int(r0) + i: t for t, (r0, n, _, _) in enumerate(tiles) for i in range(n)}
+    cover, parts = {r: [] for r in range(sizes.n_s)}, []
+    for wk in work:
+        kind = int(wk[7])
+        if wk[0] < 0:
+            continue
+        row0, n = int(tiles[wk[0], 0]), int(tiles[wk[0], 1])
+        if kind == 1:
+            flat = listed(wk, 2 * int(wk[5]))
+            rows = flat[0::2]
+            assert 1 <= len(rows) <= 16
+            for r, to in zip(rows, flat[1::2]):
+                if to >= 0:
+                    t = tile_of[r]
+                    assert to % 16 == r - int(tiles[t, 0])
+                    parts.append((t, to // 16, r))
+                else:
+                    assert tiles[tile_of[r], 2] == -1
+            blocks = list(range(int(wk[1]), int(wk[2])))
+        else:
+            rows = range(row0, row0 + n)
+            blocks = listed(wk, int(wk[5])) if kind == 2 else list(range(int(wk[1]), int(wk[2])))
+            assert wk[1] == 0 or kind == 0
+            if wk[3] >= 0:
+                parts += [(int(wk[0]), int(wk[3]), r) for r in rows]
+            else:
+                assert tiles[wk[0], 2] == -1
+        assert blocks
+        for r in rows:
+            cover[r].append((kind, blocks))
+    return cover, parts
+
+
+@pytest.mark.parametrize("seed", range(8))
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (32, 8), (16, 2), (16, 1)])
+def test_shared_decode_items_cover_each_row_once(seed, hq, hkv):
+    """Decode plans over shared chunk caches, against the definition: each new row's items
+    cover exactly the blocks of its own request, each once (a shared item by the same
+    physical block and length, all of it before the row), and write each of its tile's
+    partials once.  Chunks repeat inside requests, stand in different orders, and are cut
+    to another length by some requests; token counts are uneven."""
+    rng = np.random.default_rng(900 + seed)
+    cfg = el.attn_cfg(hq, hkv, 64)
+    R = 16 // (hq // hkv)
+    pool = [int(x) for x in rng.integers(1, 900, 8)]
+    blocks, nxt = [], 0
+    for n in pool:
+        blocks.append(list(range(nxt, nxt + -(-n // 16))))
+        nxt += -(-n // 16)
+    reqs = []
+    for _ in range(int(rng.integers(2, 14))):
+        ids = [int(x) for x in rng.integers(0, 8, int(rng.integers(1, 7)))]
+        lens = [pool[c] - (1 if rng.random() < 0.1 and pool[c] % 16 > 1 else 0) for c in ids]
+        reqs.append(el.Request(lens, [blocks[c] for c in ids], int(rng.integers(1, 40)), int(rng.choice([0, 4, 32]))))
+    need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
+    total = nxt + need + 64
+    sizes, buf, v = el.epic_plan_link(reqs, cfg, list(range(nxt, nxt + need)), total)
+    new = [int(rng.integers(0, R + 1)) for _ in reqs]
+    new[0] = 1
+    ds, _, d = el.epic_plan_decode(sizes, buf, new, cfg, list(range(nxt + need, total)), total)
+    assert ds.tile_rows == 16
+    cover, parts = _items_of_rows(ds, d)
+    key = lambda b: (int(d["linked_blocks"][b]), int(d["block_len"][b]))  # noqa: E731
+    for r in range(ds.n_s):
+        b = int(d["s_req"][r])
+        mine = range(int(d["blk_off"][b]), int(d["blk_off"][b + 1]))
+        want = sorted(key(i) for i in mine if d["block_pos0"][i] <= d["s_pos"][r])
+        first = int(d["s_pos"][int(d["s_off"][b])])
+        got = []
+        for kind, bl in cover[r]:
+            got += [key(i) for i in bl if kind == 1 or d["block_pos0"][i] <= d["s_pos"][r]]
+            if kind == 1:                                  # unmasked: wholly before the request's new rows
+                ends = {key(i): int(d["block_pos0"][i] + d["block_len"][i]) for i in mine}
+                assert all(ends[key(i)] <= first for i in bl)
+            else:
+                assert all(i in mine for i in bl)
+        assert sorted(got) == want
+    tiles = d["tiles"].reshape(-1, 4)
+    expect = [(t, p, int(r0) + i) for t, (r0, n, p0, ns) in enumerate(tiles) if p0 >= 0
+              for p in range(p0, p0 + ns) for i in range(n)]
+    assert sorted(parts) == sorted(expect)
+    assert sorted({p for _, p, _ in parts}) == list(range(ds.n_partials))
+
+
+def test_shared_decode_rule():
+    """Sharing is taken where it saves a quarter of the block reads, and not with a forced
+    split, for one request, or when nothing is common."""
+    cfg = el.attn_cfg(32, 8, 128)
+    ids = list(range(64))
+
+    def kinds(reqs, cfg):
+        need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
+        sizes, buf, _ = el.epic_plan_link(reqs, cfg, list(range(500, 500 + need)), 900)
+        _, _, d = el.epic_plan_decode(sizes, buf, [1] * len(reqs), cfg, list(range(700, 740)), 900)
+        return set(d["work"].reshape(-1, 8)[:, 7].tolist())
+
+    same = [el.Request([1024], [ids], 20, 0) for _ in range(4)]
+    assert 1 in kinds(same, cfg)
+    assert kinds(same, el.attn_cfg(32, 8, 128, 0.0, 16)) == {0}
+    assert kinds(same[:1], cfg) == {0}
+    assert kinds([el.Request([1024], [[64 * r + i for i in ids]], 20, 0) for r in range(4)], cfg) == {0}
