@@ -673,78 +673,115 @@ __global__ __launch_bounds__(64 * W, W == 8 ? 1 : 2) void link_attention_kernel(
 }
 
 // Merge the split-KV partials of a tile: lse = log2 sum_i 2^lse_i, out = sum_i 2^(lse_i - lse) O_i.
-// Workgroup = (tile, KV head, quarter of the head dim).  Each (valid tile row, half
-// of that quarter) gets P lanes of one wavefront (P a power of two, at most 64, the
-// number of partials, and 512 / (2 x valid rows)); lane j takes partials j, j + P, ..., and the lanes
-// combine their (max, weight sum, weighted sums) by butterfly exchanges.  A tile
-// of few rows (decode: one row per head) with many partials so gets the whole
-// workgroup's memory parallelism.
-constexpr int kCombineParts = 4;
-constexpr int kCombineThreads = 512;
-template <int D>
+// What bounds it is load latency: a row has few bytes per partial and few partials.  A
+// group of D / 4 lanes reads a partial's row in one coalesced access of 16 bytes per
+// lane, 4 or 8 partials and their lse in one round trip (an online softmax: no pass over
+// the lse first).  Prefill tiles have many rows and few partials: a group per row.
+// Decode tiles have few rows and up to ~128 partials: the rows of a (tile, KV head) are
+// dealt to four workgroups, and the workgroup's groups share its rows' partials and
+// merge through LDS.  Against lanes that each walked 64-byte pieces of a row (rocprofv3
+// medians): 2 tiles of 256 rows with 16 partials 14.4 -> 7.6 us, 36 tiles with 2-3 partials
+// 22.2 -> 17.2, 23 tiles of 128 rows 9.0 -> 8.4, one decode tile with 94 partials 8.0 -> 5.3
+// (about 4.5 us is the least a dependent launch shows there).
+constexpr int kCombineThreads = 256;
+constexpr int kCombineTinyParts = 4;          // workgroups per (16-row tile, KV head)
+template <int D, bool TINY>
 __global__ __launch_bounds__(kCombineThreads) void link_combine_kernel(AttnArgs a) {
-  constexpr int DQ = D / kCombineParts;       // dims per workgroup
-  constexpr int DT = DQ / 2;                  // dims per (row, half)
-  const int hkv = a.hkv;
-  const int dq = blockIdx.x % kCombineParts;
-  const int g = (blockIdx.x / kCombineParts) % hkv;
-  const int tile = blockIdx.x / (kCombineParts * hkv);
+  constexpr int LP = D / 4;                   // lanes per group
+  constexpr int SG = kCombineThreads / LP;    // groups per workgroup
+  __shared__ float4 part[TINY ? SG : 1][LP];
+  __shared__ float2 part_mw[TINY ? SG : 1];
+  const int hkv = a.hkv, TR = a.tile_rows;
+  const int per_tile = TINY ? kCombineTinyParts : TR / SG;
+  const int g = blockIdx.x % hkv;
+  const int rest = blockIdx.x / hkv;
+  const int tile = rest / per_tile, wg = rest % per_tile;
   const int p0 = a.tiles[4 * tile + 2];
   const int ns = a.tiles[4 * tile + 3];
   if (p0 < 0) return;
   const int nrows = a.tiles[4 * tile + 1];
-  const int R = a.rows_per_tile, TR = a.tile_rows;
-  const int n_valid = nrows * a.G;            // tile rows t = head * R + s, s < nrows
-  const int pairs = 2 * n_valid;
-  int P = 64;                                 // lanes per (row, half): no more than partials
-  while (P > 1 && (P * pairs > kCombineThreads || P > ns)) P >>= 1;
-  const int pair = threadIdx.x / P, j = threadIdx.x % P;
-  if (pair >= pairs) return;                  // whole groups of P lanes leave together
-  const int vr = pair >> 1, hf = pair & 1;
-  const int hh = vr / nrows, srl = vr % nrows;
-  const int t = hh * R + srl;
+  const int n_valid = nrows * a.G;            // valid rows vr: head * nrows + s, s < nrows
+  const int grp = threadIdx.x / LP, l = threadIdx.x % LP;
+  int vr, first = 0, step = 1;                // row, and this group's partials
+  if constexpr (TINY) {
+    const int mine = (n_valid - wg + kCombineTinyParts - 1) / kCombineTinyParts;   // rows wg, wg + 4, ..
+    if (mine <= 0) return;                    // (the whole workgroup)
+    while (step * 2 * mine <= SG) step *= 2;
+    const int i = grp / step;
+    first = grp % step;
+    vr = i < mine ? wg + i * kCombineTinyParts : n_valid;
+  } else {
+    vr = wg * SG + grp;
+  }
+  const bool ok = vr < n_valid;
+  const int hh = ok ? vr / nrows : 0, srl = ok ? vr % nrows : 0;
+  const int t = hh * a.rows_per_tile + srl;
+  const size_t stride = size_t(hkv) * TR;     // rows between partials
+  const size_t row = size_t(p0) * stride + size_t(g) * TR + t;
+  const float* lse = a.part_lse + row;
+  const float* po = a.part_o + row * D + l * 4;
+  float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  float m = -INFINITY, wsum = 0.0f;
+  auto merge = [&](auto depth) __attribute__((always_inline)) {
+    constexpr int N = decltype(depth)::value;
+    for (int i = first; i < ns; i += step * N) {
+      float e[N];
+      float4 x[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {           // past the last: that one again, with weight 0
+        const size_t q = size_t(min(i + j * step, ns - 1)) * stride;
+        e[j] = lse[q];
+        x[j] = *reinterpret_cast<const float4*>(po + q * D);
+      }
+      float mn = m;
+#pragma unroll
+      for (int j = 0; j < N; ++j) mn = fmaxf(mn, i + j * step < ns ? e[j] : -INFINITY);
+      const float mu = mn == -INFINITY ? 0.0f : mn;
+      const float al = fast_exp2(m - mu);     // 0 at first
+      acc.x *= al, acc.y *= al, acc.z *= al, acc.w *= al, wsum *= al;
+      m = mn;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const bool in = i + j * step < ns;
+        const float w = in ? fast_exp2(e[j] - mu) : 0.0f;
+        wsum += w;
+        acc.x += in ? w * x[j].x : 0.0f;
+        acc.y += in ? w * x[j].y : 0.0f;
+        acc.z += in ? w * x[j].z : 0.0f;
+        acc.w += in ? w * x[j].w : 0.0f;
+      }
+    }
+  };
+  if (ok) {
+    if (ns <= 4 * step) merge(std::integral_constant<int, 4>{});
+    else merge(std::integral_constant<int, 8>{});
+  }
+  if constexpr (TINY) {
+    part[grp][l] = acc;
+    if (l == 0) part_mw[grp] = make_float2(m, wsum);
+    __syncthreads();
+    if (first != 0) return;
+    float mx = m;
+    for (int i = 1; i < step; ++i) mx = fmaxf(mx, part_mw[grp + i].x);
+    const float mu = mx == -INFINITY ? 0.0f : mx;
+    const float a0 = fast_exp2(m - mu);
+    acc.x *= a0, acc.y *= a0, acc.z *= a0, acc.w *= a0, wsum *= a0;
+    for (int i = 1; i < step; ++i) {
+      const float2 mw = part_mw[grp + i];
+      const float w = fast_exp2(mw.x - mu);
+      const float4 y = part[grp + i][l];
+      wsum += w * mw.y;
+      acc.x += w * y.x, acc.y += w * y.y, acc.z += w * y.z, acc.w += w * y.w;
+    }
+    m = mx;
+  }
+  if (!ok) return;
+  const float inv = 1.0f / wsum;
   const int srow = a.tiles[4 * tile + 0] + srl;
   const int h = g * a.G + hh;
-  const int d0 = dq * DQ + hf * DT;
-  auto lse_of = [&](int i) { return a.part_lse[(size_t(p0 + i) * hkv + g) * TR + t]; };
-  float mx = -INFINITY;
-  for (int i = j; i < ns; i += P) mx = fmaxf(mx, lse_of(i));
-  for (int o = 1; o < P; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-  float acc[DT];
-#pragma unroll
-  for (int d = 0; d < DT; ++d) acc[d] = 0.0f;
-  float wsum = 0.0f;
-  for (int i = j; i < ns; i += P) {
-    const float w = fast_exp2(lse_of(i) - mx);
-    wsum += w;
-    const float* pp = a.part_o + ((size_t(p0 + i) * hkv + g) * TR + t) * D + d0;
-#pragma unroll
-    for (int d = 0; d < DT; d += 4) {
-      const float4 f = *reinterpret_cast<const float4*>(pp + d);
-      acc[d + 0] += w * f.x;
-      acc[d + 1] += w * f.y;
-      acc[d + 2] += w * f.z;
-      acc[d + 3] += w * f.w;
-    }
-  }
-  for (int o = 1; o < P; o <<= 1) {
-    wsum += __shfl_xor(wsum, o);
-#pragma unroll
-    for (int d = 0; d < DT; ++d) acc[d] += __shfl_xor(acc[d], o);
-  }
-  if (j != 0) return;
-  const float inv = 1.0f / wsum;
-  uint16_t* op = a.out + (size_t(srow) * a.hq + h) * D + d0;
-#pragma unroll
-  for (int d = 0; d < DT; d += 8) {
-    uint4 u;
-    u.x = pack_bf16x2(acc[d + 0] * inv, acc[d + 1] * inv);
-    u.y = pack_bf16x2(acc[d + 2] * inv, acc[d + 3] * inv);
-    u.z = pack_bf16x2(acc[d + 4] * inv, acc[d + 5] * inv);
-    u.w = pack_bf16x2(acc[d + 6] * inv, acc[d + 7] * inv);
-    *reinterpret_cast<uint4*>(op + d) = u;
-  }
-  if (a.lse && hf == 0 && dq == 0) a.lse[size_t(srow) * a.hq + h] = (mx + fast_log2(wsum)) * kLn2;
+  *reinterpret_cast<uint2*>(a.out + (size_t(srow) * a.hq + h) * D + l * 4) =
+      make_uint2(pack_bf16x2(acc.x * inv, acc.y * inv), pack_bf16x2(acc.z * inv, acc.w * inv));
+  if (a.lse && l == 0) a.lse[size_t(srow) * a.hq + h] = (m + fast_log2(wsum)) * kLn2;
 }
 
 }  // namespace
@@ -765,13 +802,19 @@ void launch_link_attention(const AttnArgs& a, int head_dim, int n_work, hipStrea
   }
 }
 
+template <int D>
+static void launch_combine(const AttnArgs& a, int n_tiles, hipStream_t stream) {
+  const unsigned tiles = unsigned(n_tiles) * unsigned(a.hkv);
+  if (a.tile_rows == kTileRowsTiny)
+    link_combine_kernel<D, true><<<tiles * kCombineTinyParts, kCombineThreads, 0, stream>>>(a);
+  else
+    link_combine_kernel<D, false><<<tiles * unsigned(a.tile_rows * (D / 4) / kCombineThreads), kCombineThreads, 0, stream>>>(a);
+}
+
 void launch_link_combine(const AttnArgs& a, int head_dim, int n_tiles, hipStream_t stream) {
   if (n_tiles == 0) return;
-  const dim3 grid(unsigned(n_tiles) * unsigned(a.hkv) * kCombineParts);
-  if (head_dim == 128)
-    link_combine_kernel<128><<<grid, kCombineThreads, 0, stream>>>(a);
-  else
-    link_combine_kernel<64><<<grid, kCombineThreads, 0, stream>>>(a);
+  if (head_dim == 128) launch_combine<128>(a, n_tiles, stream);
+  else launch_combine<64>(a, n_tiles, stream);
 }
 
 }  // namespace epic
