@@ -279,7 +279,9 @@ epic_status epic_link_attention_noalloc(const epic_attn_cfg* cfg, const epic_pla
  * next call on the same thread, every device entry point records, on its
  * stream, events[0] before the link write, events[1] before the attention
  * kernel, events[2] after it and events[3] after the split-KV combine (per
- * layer for the model entry points; each record overwrites the previous one).
+ * layer for the model entry points; each record overwrites the previous one;
+ * with few rows their Q|K|V projection writes the private blocks itself, so
+ * nothing runs between events[0] and events[1]).
  * Never fails. */
 epic_status epic_set_profile_events(void* const* events);
 

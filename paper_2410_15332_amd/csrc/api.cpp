@@ -74,12 +74,15 @@ epic_status run_link_attention(const epic_attn_cfg* cfg, const epic_plan_sizes* 
                                uint16_t* k_cache, uint16_t* v_cache, uint16_t* out, float* lse,
                                void* workspace, void* stream_ptr) {
   hipStream_t stream = static_cast<hipStream_t>(stream_ptr);
+  const bool written = k_s == nullptr && s->n_s > 0;
   record_event(0, stream);
-  if (s->n_rerotated > 0)
-    launch_link_write_rotated(p, s->n_private, cfg->num_kv_heads, cfg->head_dim, cfg->rope_theta, k_s, v_s, k_cache,
-                              v_cache, stream);
-  else
-    launch_link_write(p, s->n_private, cfg->num_kv_heads, cfg->head_dim, k_s, v_s, k_cache, v_cache, stream);
+  if (!written) {
+    if (s->n_rerotated > 0)
+      launch_link_write_rotated(p, s->n_private, cfg->num_kv_heads, cfg->head_dim, cfg->rope_theta, k_s, v_s, k_cache,
+                                v_cache, stream);
+    else
+      launch_link_write(p, s->n_private, cfg->num_kv_heads, cfg->head_dim, k_s, v_s, k_cache, v_cache, stream);
+  }
   if (s->n_s == 0) return hip_status("link write launch");   // re-rotated copies only
   AttnArgs a{};
   a.s_pos = p->s_pos;

@@ -35,6 +35,7 @@ size_t gemm_workspace_bytes();
 // Carve the workspace: partials first, then the counters.
 void gemm_workspace(void* base, float** partial, int** tile_count);
 size_t gemm_partial_floats();
+int gemm_counters();          // arrival counters at tile_count
 // How a GEMM runs: whole 256-wide tiles, one round of whole narrow tiles, narrow tiles
 // cut along K (the only route that uses the arrival counters), or weight streaming
 // (gemm_stream.hip: partial sums, then a pass that adds them up).

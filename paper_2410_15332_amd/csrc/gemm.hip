@@ -697,6 +697,8 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
 
 size_t gemm_partial_floats() { return size_t(2 * kMaxWorkers) * kPartialFloats; }
 
+int gemm_counters() { return kCounters; }
+
 size_t gemm_workspace_bytes() { return gemm_partial_floats() * sizeof(float) + kCounters * sizeof(int); }
 
 void gemm_workspace(void* base, float** partial, int** tile_count) {

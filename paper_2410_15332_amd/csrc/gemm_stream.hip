@@ -27,6 +27,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "link_tile.h"
 #include "stream_sum.h"
 
 namespace epic {
@@ -213,24 +214,16 @@ __global__ __launch_bounds__(256) void stream_finish_kernel(StreamSum s, float* 
   }
 }
 
-// q, k, v of the fused Q|K|V projection: q and k heads rotated at each row's linked
-// position (pairs (i, i + D/2)), v heads as they are; bf16.  A thread takes four pairs.
-__global__ __launch_bounds__(256) void stream_rope_kernel(StreamSum s, GemmArgs g) {
-  const int D = g.head_dim, hd2 = D / 2, per_row = s.N / 8;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  const int m = idx / per_row, r = idx - m * per_row;
-  if (m >= s.M) return;
-  const int head = r / (hd2 / 4), i = (r - head * (hd2 / 4)) * 4;
-  const float4 a = s.sum4(m, head * D + i), b = s.sum4(m, head * D + hd2 + i);
-  uint16_t* base;
-  int heads, hd;
-  if (head < g.hq) base = g.q, heads = g.hq, hd = head;
-  else if (head < g.hq + g.hkv) base = g.k, heads = g.hkv, hd = head - g.hq;
-  else base = g.v, heads = g.hkv, hd = head - g.hq - g.hkv;
+// Four rotary pairs (i .. i + 3, i + D/2 ..) of a head of a row, summed and
+// perhaps rotated by the row's table.
+__device__ __forceinline__ void sum_pairs(const StreamSum& s, const float2* cs, int m, int col, int D, int i, bool rotate,
+                                          uint2& lo, uint2& hi) {
+  const int hd2 = D / 2;
+  const float4 a = s.sum4(m, col + i), b = s.sum4(m, col + hd2 + i);
   float x1[4] = {a.x, a.y, a.z, a.w}, x2[4] = {b.x, b.y, b.z, b.w};
-  if (head < g.hq + g.hkv) {
-    const float4* cs = reinterpret_cast<const float4*>(g.cs + size_t(m) * hd2 + i);
-    const float4 t0 = cs[0], t1 = cs[1];
+  if (rotate) {
+    const float4* p = reinterpret_cast<const float4*>(cs + size_t(m) * hd2 + i);
+    const float4 t0 = p[0], t1 = p[1];
     const float c[4] = {t0.x, t0.z, t1.x, t1.z}, sn[4] = {t0.y, t0.w, t1.y, t1.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -239,9 +232,78 @@ __global__ __launch_bounds__(256) void stream_rope_kernel(StreamSum s, GemmArgs 
       x2[e] = y2;
     }
   }
+  lo = make_uint2(pack_bf16x2(x1[0], x1[1]), pack_bf16x2(x1[2], x1[3]));
+  hi = make_uint2(pack_bf16x2(x2[0], x2[1]), pack_bf16x2(x2[2], x2[3]));
+}
+
+// q, k, v of the fused Q|K|V projection: q and k heads rotated at each row's linked
+// position (pairs (i, i + D/2)), v heads as they are; bf16.  A thread takes four pairs.
+__global__ __launch_bounds__(256) void stream_rope_kernel(StreamSum s, GemmArgs g) {
+  const int D = g.head_dim, hd2 = D / 2, per_row = s.N / 8;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  const int m = idx / per_row, r = idx - m * per_row;
+  if (m >= s.M) return;
+  const int head = r / (hd2 / 4), i = (r - head * (hd2 / 4)) * 4;
+  uint16_t* base;
+  int heads, hd;
+  if (head < g.hq) base = g.q, heads = g.hq, hd = head;
+  else if (head < g.hq + g.hkv) base = g.k, heads = g.hkv, hd = head - g.hq;
+  else base = g.v, heads = g.hkv, hd = head - g.hq - g.hkv;
+  uint2 lo, hi;
+  sum_pairs(s, g.cs, m, head * D, D, i, head < g.hq + g.hkv, lo, hi);
   uint16_t* o = base + (size_t(m) * heads + hd) * D + i;
-  *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16x2(x1[0], x1[1]), pack_bf16x2(x1[2], x1[3]));
-  *reinterpret_cast<uint2*>(o + hd2) = make_uint2(pack_bf16x2(x2[0], x2[1]), pack_bf16x2(x2[2], x2[3]));
+  *reinterpret_cast<uint2*>(o) = lo;
+  *reinterpret_cast<uint2*>(o + hd2) = hi;
+}
+
+// The same fused with the link write: k and v go straight to the private blocks of the
+// linked cache, which a launch of their own wrote before (about 5 us of a 155 us decode
+// layer, as long as any dependent launch takes).  The first n_private * hkv workgroups
+// build a (block, KV head) each, as link_write_kernel does; the rest write q.
+template <int D>
+__global__ __launch_bounds__(2 * D) void stream_rope_write_kernel(StreamSum s, GemmArgs g, StreamWrite w) {
+  __shared__ VTile<D> vt;
+  const int tid = threadIdx.x;
+  const int n_kv = w.n_private * g.hkv;
+  if (int(blockIdx.x) >= n_kv) {              // q: four pairs per thread
+    const int per_row = g.hq * (D / 8);
+    const int idx = (blockIdx.x - n_kv) * 2 * D + tid;
+    const int m = idx / per_row, r = idx - m * per_row;
+    if (m >= s.M) return;
+    const int head = r / (D / 8), i = (r - head * (D / 8)) * 4;
+    uint2 lo, hi;
+    sum_pairs(s, g.cs, m, head * D, D, i, true, lo, hi);
+    uint16_t* o = g.q + (size_t(m) * g.hq + head) * D + i;
+    *reinterpret_cast<uint2*>(o) = lo;
+    *reinterpret_cast<uint2*>(o + D / 2) = hi;
+    return;
+  }
+  const int pv = blockIdx.x / g.hkv, h = blockIdx.x % g.hkv;
+  const int dst = w.priv_block[pv], src = w.priv_src[pv];
+  const int o = tid / (D / 8), c = tid % (D / 8);          // slot; K pairs 4 c .., V dims 8 c ..
+  const int r = w.priv_rows[pv * 16 + o];
+  const size_t at = ((size_t(src < 0 ? 0 : src) * g.hkv + h) * 16) * D;
+  uint2 lo = make_uint2(0, 0), hi = lo;
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (r >= 0) {
+    sum_pairs(s, g.cs, r, (g.hq + h) * D, D, c * 4, true, lo, hi);
+    const int col = (g.hq + g.hkv + h) * D + c * 8;
+    const float4 x = s.sum4(r, col), y = s.sum4(r, col + 4);
+    v = make_uint4(pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w), pack_bf16x2(y.x, y.y), pack_bf16x2(y.z, y.w));
+  } else if (src >= 0) {
+    lo = *reinterpret_cast<const uint2*>(w.k_cache + at + o * D + c * 4);
+    hi = *reinterpret_cast<const uint2*>(w.k_cache + at + o * D + D / 2 + c * 4);
+  }
+  if (src >= 0) {
+    vt.load(w.v_cache + at, tid);
+    __syncthreads();
+  }
+  if (r >= 0 || src < 0) vt.put(o, c * 8, v);
+  __syncthreads();
+  const size_t to = ((size_t(dst) * g.hkv + h) * 16) * D;
+  *reinterpret_cast<uint2*>(w.k_cache + to + o * D + c * 4) = lo;
+  *reinterpret_cast<uint2*>(w.k_cache + to + o * D + D / 2 + c * 4) = hi;
+  vt.store(w.v_cache + to, tid);
 }
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -308,6 +370,13 @@ void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStr
   if (epi == kStoreF32) stream_finish_kernel<kStoreF32><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
   else if (epi == kResidual) stream_finish_kernel<kResidual><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
   else stream_finish_kernel<kSwiGLU><<<grid, 256, 0, stream>>>(s, g.C, g.act, g.ffn);
+}
+
+void launch_stream_rope_write(const StreamSum& s, const GemmArgs& g, const StreamWrite& w, hipStream_t stream) {
+  const int D = g.head_dim;
+  const int grid = w.n_private * g.hkv + cdiv(s.M * g.hq * (D / 8), 2 * D);
+  if (D == 128) stream_rope_write_kernel<128><<<grid, 256, 0, stream>>>(s, g, w);
+  else stream_rope_write_kernel<64><<<grid, 128, 0, stream>>>(s, g, w);
 }
 
 }  // namespace epic

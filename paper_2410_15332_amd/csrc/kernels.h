@@ -40,6 +40,10 @@ void launch_link_combine(const AttnArgs& a, int head_dim, int n_tiles, hipStream
 
 void launch_rmsnorm(const float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, int rows, int hidden,
                     float eps, hipStream_t stream);
-void launch_rope_table(const int32_t* s_pos, float2* cs, int rows, int head_dim, double theta, hipStream_t stream);
+// The first norm of a call: also the rotary table cs [rows][head_dim / 2] at the rows'
+// positions, and n_cnt counters cleared.
+void launch_rmsnorm_start(const float* x, const uint16_t* w, uint16_t* out_bf16, int rows, int hidden, float eps,
+                          const int32_t* s_pos, float2* cs, int head_dim, double theta, int* cnt, int n_cnt,
+                          hipStream_t stream);
 
 }  // namespace epic

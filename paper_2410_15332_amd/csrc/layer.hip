@@ -8,6 +8,7 @@
 // concatenated sequence), so recomputed chunk tokens see their non-initial
 // positions (Sec. 4.2).  Angles are formed in float64: in float32,
 // pos * inv_freq at pos ~ 1e5 would be off by ~1e-2 rad.
+#include <algorithm>
 #include <cmath>
 
 #include "device_common.h"
@@ -19,6 +20,13 @@ namespace epic {
 namespace {
 
 constexpr int kNormThreads = 256;
+
+struct RopeTable {
+  const int32_t* s_pos;
+  float2* cs;                // [n_rows][half_dim]
+  int n_rows, half_dim;
+  double log2_theta;
+};
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
 #pragma unroll
@@ -81,10 +89,35 @@ __global__ __launch_bounds__(kSumThreads) void rmsnorm_sum_kernel(StreamSum s, f
   }
 }
 
+// cs[row][i] = (cos, sin)(s_pos[row] * theta^(-2i/D)), float64 angle.
+__device__ __forceinline__ void rope_entry(const RopeTable& t, int idx) {
+  if (idx >= t.n_rows * t.half_dim) return;
+  const int row = idx / t.half_dim, i = idx % t.half_dim;
+  const double inv_freq = exp2(-double(2 * i) / double(2 * t.half_dim) * t.log2_theta);
+  const double ang = double(t.s_pos[row]) * inv_freq;
+  double s, c;
+  sincos(ang, &s, &c);
+  t.cs[idx] = make_float2(float(c), float(s));
+}
+
 // One workgroup per row; hidden % 4 == 0.  out_bf16 or out_f32 receives the row.
+// START: the first norm of a call also fills the rotary table and clears the GEMM's
+// counters, in workgroups past the rows' (each would be a dependent launch of its own,
+// about 5 us in front of a layer).
+template <bool START>
 __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const float* __restrict__ x, const uint16_t* __restrict__ w,
                                                                uint16_t* __restrict__ out_bf16,
-                                                               float* __restrict__ out_f32, int hidden, float eps) {
+                                                               float* __restrict__ out_f32, int hidden, float eps,
+                                                               RopeTable table, int* __restrict__ cnt, int n_cnt) {
+  if constexpr (START) {
+    const int extra = int(blockIdx.x) - table.n_rows;
+    if (extra >= 0) {
+      const int idx = extra * kNormThreads + threadIdx.x;
+      rope_entry(table, idx);
+      if (idx < n_cnt) cnt[idx] = 0;
+      return;
+    }
+  }
   // The row stays in registers between the two passes (up to kKeep float4 per
   // thread, hidden <= 8192 at 256 threads); a longer row is read again.  The kept
   // part's loads, and its weights, are issued together from clamped indices (no
@@ -136,25 +169,22 @@ __global__ __launch_bounds__(kNormThreads) void rmsnorm_kernel(const float* __re
     put(i, xr[i], *reinterpret_cast<const uint2*>(w + 4 * i));
 }
 
-// cs[row][i] = (cos, sin)(s_pos[row] * theta^(-2i/D)), float64 angle.
-__global__ void rope_table_kernel(const int32_t* __restrict__ s_pos, float2* __restrict__ cs, int n_rows, int half_dim,
-                                  double log2_theta) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_rows * half_dim) return;
-  const int row = idx / half_dim, i = idx % half_dim;
-  const double inv_freq = exp2(-double(2 * i) / double(2 * half_dim) * log2_theta);
-  const double ang = double(s_pos[row]) * inv_freq;
-  double s, c;
-  sincos(ang, &s, &c);
-  cs[idx] = make_float2(float(c), float(s));
-}
-
 }  // namespace
 
 void launch_rmsnorm(const float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, int rows, int hidden,
                     float eps, hipStream_t stream) {
   if (rows == 0) return;
-  rmsnorm_kernel<<<rows, kNormThreads, 0, stream>>>(x, w, out_bf16, out_f32, hidden, eps);
+  rmsnorm_kernel<false><<<rows, kNormThreads, 0, stream>>>(x, w, out_bf16, out_f32, hidden, eps, RopeTable{}, nullptr, 0);
+}
+
+void launch_rmsnorm_start(const float* x, const uint16_t* w, uint16_t* out_bf16, int rows, int hidden, float eps,
+                          const int32_t* s_pos, float2* cs, int head_dim, double theta, int* cnt, int n_cnt,
+                          hipStream_t stream) {
+  if (rows == 0) return;
+  const RopeTable t{s_pos, cs, rows, head_dim / 2, std::log2(theta)};
+  const int extra = std::max(rows * (head_dim / 2), n_cnt);
+  rmsnorm_kernel<true><<<rows + (extra + kNormThreads - 1) / kNormThreads, kNormThreads, 0, stream>>>(
+      x, w, out_bf16, nullptr, hidden, eps, t, cnt, n_cnt);
 }
 
 void launch_rmsnorm_sum(const StreamSum& s, float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, float eps,
@@ -167,12 +197,6 @@ void launch_rmsnorm_sum(const StreamSum& s, float* x, const uint16_t* w, uint16_
   g.C = x;
   launch_stream_finish(s, g, kResidual, stream);
   launch_rmsnorm(x, w, out_bf16, out_f32, s.M, s.N, eps, stream);
-}
-
-void launch_rope_table(const int32_t* s_pos, float2* cs, int rows, int head_dim, double theta, hipStream_t stream) {
-  const int n = rows * (head_dim / 2);
-  if (n == 0) return;
-  rope_table_kernel<<<(n + 255) / 256, 256, 0, stream>>>(s_pos, cs, rows, head_dim / 2, std::log2(theta));
 }
 
 }  // namespace epic

@@ -12,10 +12,14 @@
 
 #include "device_common.h"
 #include "kernels.h"
+#include "link_tile.h"
 #include "link_write.h"
 
 namespace epic {
 
+// The V slab of a block goes through LDS (VTile, link_tile.h): a row's 16 dims come in one
+// 16-byte load and leave transposed, where gathering 2-byte elements took eight loads per
+// thread.
 template <int D>
 __global__ __launch_bounds__(2 * D) void link_write_kernel(const int32_t* __restrict__ priv_block,
                                                           const int32_t* __restrict__ priv_src,
@@ -24,46 +28,32 @@ __global__ __launch_bounds__(2 * D) void link_write_kernel(const int32_t* __rest
                                                           const uint16_t* __restrict__ v_s,
                                                           uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
                                                           int hkv) {
+  __shared__ VTile<D> vt;
   const int pv = blockIdx.x / hkv;
   const int g = blockIdx.x % hkv;
   const int tid = threadIdx.x;
   const int dst = priv_block[pv];
   const int src = priv_src[pv];
-  const int32_t* rows = priv_rows + pv * 16;
-
-  // K: thread -> (slot, 8-wide chunk of the head dim); 16 slots x D/8 chunks = 2D threads.
-  {
-    const int o = tid / (D / 8), dc = tid % (D / 8);
-    const int r = rows[o];
-    uint4 val = make_uint4(0, 0, 0, 0);
-    if (r >= 0)
-      val = *reinterpret_cast<const uint4*>(k_s + (size_t(r) * hkv + g) * D + dc * 8);
-    else if (src >= 0)
-      val = *reinterpret_cast<const uint4*>(kc + ((size_t(src) * hkv + g) * 16 + o) * D + dc * 8);
-    *reinterpret_cast<uint4*>(kc + ((size_t(dst) * hkv + g) * 16 + o) * D + dc * 8) = val;
+  // thread -> (slot, 8-wide chunk of the head dim); 16 slots x D/8 chunks = 2D threads
+  const int o = tid / (D / 8), dc = tid % (D / 8);
+  const int r = priv_rows[pv * 16 + o];
+  const size_t at = ((size_t(src < 0 ? 0 : src) * hkv + g) * 16) * D;
+  uint4 k = make_uint4(0, 0, 0, 0), v = k;
+  if (r >= 0) {
+    k = *reinterpret_cast<const uint4*>(k_s + (size_t(r) * hkv + g) * D + dc * 8);
+    v = *reinterpret_cast<const uint4*>(v_s + (size_t(r) * hkv + g) * D + dc * 8);
+  } else if (src >= 0) {
+    k = *reinterpret_cast<const uint4*>(kc + at + o * D + dc * 8);
   }
-  // V: thread -> (dim d, 8 consecutive slots); D dims x 2 halves = 2D threads.
-  {
-    const int d = tid >> 1, hf = tid & 1;
-    uint16_t e[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int o = hf * 8 + i;
-      const int r = rows[o];
-      uint16_t x = 0;
-      if (r >= 0)
-        x = v_s[(size_t(r) * hkv + g) * D + d];
-      else if (src >= 0)
-        x = vc[((size_t(src) * hkv + g) * D + d) * 16 + o];
-      e[i] = x;
-    }
-    uint4 val;
-    val.x = uint32_t(e[0]) | (uint32_t(e[1]) << 16);
-    val.y = uint32_t(e[2]) | (uint32_t(e[3]) << 16);
-    val.z = uint32_t(e[4]) | (uint32_t(e[5]) << 16);
-    val.w = uint32_t(e[6]) | (uint32_t(e[7]) << 16);
-    *reinterpret_cast<uint4*>(vc + ((size_t(dst) * hkv + g) * D + d) * 16 + hf * 8) = val;
+  if (src >= 0) {                             // the source's slab first, then the fresh rows over it
+    vt.load(vc + at, tid);
+    __syncthreads();
   }
+  if (r >= 0 || src < 0) vt.put(o, dc * 8, v);
+  __syncthreads();
+  const size_t to = ((size_t(dst) * hkv + g) * 16) * D;
+  *reinterpret_cast<uint4*>(kc + to + o * D + dc * 8) = k;
+  vt.store(vc + to, tid);
 }
 
 // The same write for plans that re-rotate cached rows: a block with priv_rot = off

@@ -122,15 +122,16 @@ LayerGemms layer_gemms(const epic_model_cfg* c, const epic_layer_weights* w, int
   return l;
 }
 
-// Before a call's first layer: the rotary table, and cleared arrival counters where a
-// GEMM of these shapes uses them (every layer has the same shapes).
+// Start of a call: the first layer's norm with the rotary table, and cleared arrival
+// counters where a GEMM of these shapes uses them (every layer has the same shapes).
 void start_layers(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s, const epic_plan* p,
-                  const LayerWs& ws, hipStream_t stream) {
-  launch_rope_table(p->s_pos, ws.cs, s->n_s, c->attn.head_dim, c->rope_theta, stream);
+                  const float* h, const LayerWs& ws, hipStream_t stream) {
   const LayerGemms l = layer_gemms(c, w, s->n_s, nullptr, ws);
-  if (gemm_route(l.qkv, kRope) == GemmRoute::kCut || gemm_route(l.wo, kResidual) == GemmRoute::kCut ||
-      gemm_route(l.gate_up, kSwiGLU) == GemmRoute::kCut || gemm_route(l.down, kResidual) == GemmRoute::kCut)
-    launch_gemm_clear(ws.gemm_count, stream);
+  const bool cut = gemm_route(l.qkv, kRope) == GemmRoute::kCut || gemm_route(l.wo, kResidual) == GemmRoute::kCut ||
+                   gemm_route(l.gate_up, kSwiGLU) == GemmRoute::kCut ||
+                   gemm_route(l.down, kResidual) == GemmRoute::kCut;
+  launch_rmsnorm_start(h, w->attn_norm, ws.x, s->n_s, c->hidden, c->rms_eps, p->s_pos, ws.cs, c->attn.head_dim,
+                       c->rope_theta, ws.gemm_count, cut ? gemm_counters() : 0, stream);
 }
 
 // x = RMSNorm(h) w of the n rows, after h += the pending product's partial sums, if any.
@@ -153,16 +154,25 @@ void residual_gemm(const GemmArgs& g, StreamSum* pending, hipStream_t stream) {
 
 // One layer; the rotary table ws.cs is already filled.  pending: the last layer's
 // W_down product on entry, this layer's on return, where it is still to be added to h.
+// normed: its first norm has run (start_layers).
 epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s,
                       const epic_plan* p, float* h, uint16_t* kc, uint16_t* vc, const LayerWs& ws, StreamSum* pending,
-                      hipStream_t stream) {
+                      bool normed, hipStream_t stream) {
   const int n = s->n_s, H = c->hidden;
   const LayerGemms l = layer_gemms(c, w, n, h, ws);
-  add_norm(pending, h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
-  launch_gemm(l.qkv, kRope, stream);
+  if (!normed) add_norm(pending, h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
+  // a streamed Q|K|V product is summed straight into the private blocks
+  const bool write = s->n_rerotated == 0 && gemm_route(l.qkv, kRope) == GemmRoute::kStream;
+  if (write) {
+    const StreamWrite sw{p->priv_block, p->priv_src, p->priv_rows, s->n_private, kc, vc};
+    launch_stream_rope_write(launch_gemm_stream(l.qkv, stream), l.qkv, sw, stream);
+  } else {
+    launch_gemm(l.qkv, kRope, stream);
+  }
   epic_attn_cfg ac = c->attn;
   ac.rope_theta = c->rope_theta;            // cached K was rotated with the model's base
-  epic_status st = run_link_attention(&ac, s, p, ws.q, ws.k, ws.v, kc, vc, ws.o, nullptr, ws.attn, stream);
+  epic_status st = run_link_attention(&ac, s, p, ws.q, write ? nullptr : ws.k, write ? nullptr : ws.v, kc, vc, ws.o,
+                                      nullptr, ws.attn, stream);
   if (st != EPIC_OK) return st;
   residual_gemm(l.wo, pending, stream);
   add_norm(pending, h, w->mlp_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
@@ -225,9 +235,9 @@ extern "C" epic_status epic_link_layer(const epic_model_cfg* cfg, const epic_lay
   EPIC_CHECK_ARG(k_cache && v_cache, "KV cache pointers are NULL");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const LayerWs ws = carve(cfg, sizes, static_cast<char*>(workspace));
-  start_layers(cfg, w, sizes, plan_dev, ws, s);
+  start_layers(cfg, w, sizes, plan_dev, hidden_s, ws, s);
   StreamSum pending{};
-  st = run_layer(cfg, w, sizes, plan_dev, hidden_s, k_cache, v_cache, ws, &pending, s);
+  st = run_layer(cfg, w, sizes, plan_dev, hidden_s, k_cache, v_cache, ws, &pending, true, s);
   if (st != EPIC_OK || pending.partial == nullptr) return st;
   GemmArgs g{};
   g.C = hidden_s;
@@ -262,10 +272,10 @@ extern "C" epic_status epic_link_model(const epic_model_cfg* cfg, const epic_lay
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const LayerWs ws = carve(cfg, sizes, static_cast<char*>(workspace));
-  start_layers(cfg, &layers[0], sizes, plan_dev, ws, s);
+  start_layers(cfg, &layers[0], sizes, plan_dev, hidden_s, ws, s);
   StreamSum pending{};
   for (int l = 0; l < cfg->n_layers; ++l) {
-    st = run_layer(cfg, &layers[l], sizes, plan_dev, hidden_s, k_caches[l], v_caches[l], ws, &pending, s);
+    st = run_layer(cfg, &layers[l], sizes, plan_dev, hidden_s, k_caches[l], v_caches[l], ws, &pending, l == 0, s);
     if (st != EPIC_OK) return st;
   }
   add_norm(&pending, hidden_s, final_norm, nullptr, out_hidden, sizes->n_s, cfg->hidden, cfg->rms_eps, s);

@@ -23,6 +23,7 @@ constexpr float kLog2eHost = 1.442695040888963407f;
 epic_status validate_attn_cfg(const epic_attn_cfg* cfg);
 
 // Link write + attention (+ split-KV combine) for one layer, arguments already validated.
+// k_s NULL: the caller has written the private blocks.
 epic_status run_link_attention(const epic_attn_cfg* cfg, const epic_plan_sizes* s, const epic_plan* p,
                                const uint16_t* q_s, const uint16_t* k_s, const uint16_t* v_s,
                                uint16_t* k_cache, uint16_t* v_cache, uint16_t* out, float* lse,

@@ -53,6 +53,14 @@ StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream);
 bool stream_fits(int M, int N, int K);
 // Enqueue the pass that sums the planes and runs g's epilogue.
 void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStream_t stream);
+// The link write of a streamed Q|K|V product: the plan's private blocks and the layer's caches.
+struct StreamWrite {
+  const int32_t *priv_block, *priv_src, *priv_rows;
+  int n_private;
+  uint16_t *k_cache, *v_cache;
+};
+// Enqueue the rotary epilogue with k and v written to the private blocks (no re-rotation).
+void launch_stream_rope_write(const StreamSum& s, const GemmArgs& g, const StreamWrite& w, hipStream_t stream);
 // Enqueue x += the summed planes, then RMSNorm of x's rows into out_bf16 or out_f32.
 void launch_rmsnorm_sum(const StreamSum& s, float* x, const uint16_t* w, uint16_t* out_bf16, float* out_f32, float eps,
                         hipStream_t stream);

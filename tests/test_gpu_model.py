@@ -282,3 +282,55 @@ def test_compile_of_many_rows(wl):
     ref = _oracle_compiled_caches(wl, wl.n_layers)
     _check_chunk_caches(st, ref)
     _check(st, wl.n_layers, ref)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 2, 64), (4, 2, 128)])
+def test_decode_layer_writes_into_the_linked_cache(hq, hkv, d):
+    """A decode plan through epic_link_layer: the projection's pass writes k and v of the
+    new tokens into the private blocks.  Earlier rows of an appended block (its own copy
+    source) and every other block keep their bits, a block opened by the step is zero past
+    its rows, and the new rows are the projection in float64 (rotary at the row's position).
+    Bound: k and v are rounded to bf16 (at most 2^-8 of the value); each of the 512 terms of
+    a sum carries the rounding of x, at most 2^-8 and about 2^-9.8 of it (uniform in the
+    half step, over a binade), independent, so the sum is off by sigma = 2^-9.8 rms: 2^-7 rms
+    is 7 sigma over the some thousand values compared."""
+    from paper_2410_15332_amd import epic_link as el
+    wl = _small("decode_layer", [37, 100, 16], 25, 5, hidden=512, ffn=512, hq=hq, hkv=hkv, d=d, layers=1)
+    st = _stage(wl, caches="synthetic")
+    st.run()
+    torch.cuda.synchronize()
+    pool = st.k_caches[0].shape[0]
+    extra = 3
+    kc = torch.cat([st.k_caches[0], torch.full((extra, hkv, 16, d), 7.0, dtype=torch.bfloat16, device="cuda")])
+    vc = torch.cat([st.v_caches[0], torch.full((extra, hkv, d, 16), 7.0, dtype=torch.bfloat16, device="cuda")])
+    n_new = 10                                            # 7 free slots, then a block of its own
+    sizes, host, v = el.epic_plan_decode(st.sizes, st.dplan.host, [n_new], st.cfg.attn, list(range(pool, pool + extra)),
+                                         pool + extra)
+    before_k, before_v = kc.clone(), vc.clone()
+    h = torch.randn(n_new, 512, generator=torch.Generator().manual_seed(5)).cuda()
+    emb = h.clone()
+    ws = torch.empty(el.epic_model_workspace_bytes(st.cfg, sizes), dtype=torch.uint8, device="cuda")
+    el.epic_link_layer(st.cfg, st.layers[0], el.DevicePlan(sizes, host), h, kc, vc, ws)
+    torch.cuda.synchronize()
+    w = st.weights[0]
+    x = emb.double()
+    x = x * torch.rsqrt(x.square().mean(-1, keepdim=True) + wl.rms_eps) * w["attn_norm"].double()
+    qkv = (x @ w["wqkv"].double().t().contiguous()).view(n_new, hq + 2 * hkv, d)
+    k, vv = qkv[:, hq:hq + hkv], qkv[:, hq + hkv:]
+    pos = torch.as_tensor(v["s_pos"].copy(), dtype=torch.float64, device="cuda")
+    ang = pos[:, None] * wl.rope_theta ** (-torch.arange(d // 2, dtype=torch.float64, device="cuda") / (d // 2))
+    c, s = ang.cos()[:, None], ang.sin()[:, None]
+    a, b = k[..., :d // 2], k[..., d // 2:]
+    k = torch.cat((a * c - b * s, b * c + a * s), -1)
+    blocks, slots = v["s_slot"] // 16, v["s_slot"] % 16
+    assert len(set(blocks.tolist())) == 2
+    for got, ref in ((kc[blocks, :, slots], k), (vc[blocks, :, :, slots], vv)):
+        err = (got.double() - ref).abs()
+        assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * ref.pow(2).mean().sqrt()).all()), err.max()
+    opened = int(blocks[-1])
+    before_k[opened] = 0
+    before_v[opened] = 0
+    before_k[blocks, :, slots] = kc[blocks, :, slots]
+    before_v[blocks, :, :, slots] = vc[blocks, :, :, slots]
+    assert torch.equal(kc.view(torch.int16), before_k.view(torch.int16))
+    assert torch.equal(vc.view(torch.int16), before_v.view(torch.int16))
