@@ -69,7 +69,7 @@ constexpr int kPartialFloats = kTM * 256;               // per partial slot (twi
 constexpr int kMaxSplitTiles = 2 * kMaxWorkers;
 constexpr int kCounters = kMaxSplitTiles * (kThreads / 64);   // one per (cut tile, wavefront)
 constexpr int kMinUnits = 4;                            // K stages per workgroup, at least
-constexpr int kStreamRows = 512;                        // rows up to which weight streaming beats cut tiles
+constexpr int kStreamRows = 512;                        // most rows of a streamed product
 
 constexpr int TN = 128;                                 // columns of a workgroup tile
 
@@ -682,16 +682,39 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
     if (one_round(t96)) return GemmRoute::kWhole96;
     if (one_round(t128)) return GemmRoute::kWhole128;
   }
-  // What is left would cut 256 x 128 tiles.  Up to kStreamRows rows, and where those
-  // tiles are fewer than the CUs (else most are whole and the cut ones few), streaming
-  // the weights into partial sums is faster (epic_gemm, one box, cut -> streamed, us):
-  //   K = 4096, N = 4096:    32 rows 21.2 -> 12.8, 128 29.1 -> 15.6, 256 47.4 -> 23.4, 448 43.2 -> 29.7
-  //   K = 4096, N = 6144:    32 rows 19.7 -> 14.9, 128 25.9 -> 19.1, 256 42.8 -> 31.9
-  //   K = 14336, N = 4096:   32 rows 36.1 -> 26.8, 128 47.5 -> 34.4, 256 75.6 -> 50.5, 512 94.6 -> 86.1,
-  //                          640 117.4 -> 118.8
-  //   K = 4096, N = 2 x 14336, SwiGLU (448 tiles): 256 rows 83.1 -> 110.6
+  // Else the least estimated time (us), each line fitted to epic_gemm on one box; w: MB
+  // of weights, u: K stages per workgroup.  Measured examples (K x N, rows: us):
+  //   streamed weights  4096 x 4096, 128: 15.6, 448: 29.7; 14336 x 4096, 128: 34, 384: 75, 512: 86
+  //   whole wide tiles  4096 x 28672, 300: 87.6 (cut 115), 512: 103 (139); 4096 x 6144, 1500: 70 (88);
+  //                     8192 x 4096, 2600: 155 (246); 8192 x 57344, 100: 192 (217)
+  //   split wide tiles  14336 x 4096, 363: 57 (streamed 75), 736: 97 (cut 120), 2000: 206 (249);
+  //                     8192 x 2048, 600: 42 (53); 4096 x 28672, 192: 74 (99)
+  //   cut tiles         4096 x 4096, 1472: 61-66 (split 66-69), 2000: 73-80 (split 80-83)
+  // In a layer the pass that sums partials replaces a norm or a link write (bonus).
+  constexpr double kNever = 1e30;
+  const double bonus = epi == kResidual ? 5.0 : epi == kRope ? 10.0 : 0.0;
+  const double w = double(g.K) * g.N * 2e-6, plane = double(g.M) * g.N * 4e-6;
+  const int64_t ks = g.K / kBK;
+  const int t128r = cdiv(g.M, 128);
+  const double stream = g.M <= kStreamRows && stream_fits(g.M, g.N, g.K)
+                            ? 12.0 + w * (t128r <= 1 ? 0.2 : t128r == 2 ? 0.32 : t128r == 3 ? 0.5 : 0.6) +
+                                  std::max(plane - 8.0, 0.0) * 0.4 - bonus
+                            : kNever;
+  const WideSplit sp = wide_split(g.M, g.N, g.K);
+  const double split = sp.parts >= 2 ? sp.time + 4.0 + sp.parts * plane / 5.0 - bonus : kNever;
+  auto whole = [&](int tm) {                            // one round; a stage takes longer the more CUs run
+    const int64_t tiles = int64_t(cdiv(g.M, tm)) * n256;
+    if (n256 == 0 || tiles > kMaxWorkers) return kNever;
+    return 10.0 + ks * (tm == 256 ? 0.85 + 0.65 * tiles / kMaxWorkers : 0.7 + 0.55 * tiles / kMaxWorkers);
+  };
+  const double whole256 = whole(256), whole192 = whole(192);
   const int64_t cut_tiles = int64_t(m_tiles) * n128;
-  if (g.M <= kStreamRows && cut_tiles < kMaxWorkers && stream_fits(g.M, g.N, g.K)) return GemmRoute::kStream;
+  const double cut = 10.0 + 1.06 * double(cut_tiles * ks) / kMaxWorkers + 2.5 * kMaxWorkers / double(cut_tiles);
+  const double best = std::min({stream, split, whole256, whole192, cut});
+  if (best == stream) return GemmRoute::kStream;
+  if (best == split) return GemmRoute::kSplit;
+  if (best == whole192) return GemmRoute::kWhole192;
+  if (best == whole256) return GemmRoute::kWhole256;
   return GemmRoute::kCut;
 }
 
@@ -713,8 +736,8 @@ void launch_gemm_clear(int* tile_count, hipStream_t stream) {
 void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream) {
   if (g.M == 0) return;
   const GemmRoute r = gemm_route(g, epi);
-  if (r == GemmRoute::kStream)
-    launch_stream_finish(launch_gemm_stream(g, stream), g, epi, stream);
+  if (is_partial(r))
+    launch_stream_finish(launch_gemm_partial(g, r, stream), g, epi, stream);
   else if (r == GemmRoute::kWhole256 || r == GemmRoute::kWhole192)
     launch_gemm_wide(g, epi, r == GemmRoute::kWhole256 ? 256 : 192, stream);
   else if (epi == kStoreF32)

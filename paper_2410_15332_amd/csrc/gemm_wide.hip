@@ -21,6 +21,13 @@
 // K 4096) 3752 -> 3580 us, W_down (K 14336) 2110 -> 1929, Q|K|V 861 -> 809, W_O 668 -> 628;
 // 736 rows, gate|up 202 -> 167.  MFMA busy 79% of cycles (73% before).
 //
+// With few tiles and a long K the same kernel runs equal parts of K of every tile, one
+// workgroup each, into fp32 planes that the consumer adds (stream_sum.h): the part index
+// is the slow one, so the workgroups of an XCD are at the same K and share operands
+// (shares cut anywhere in the tile order, and thus at as many K offsets as workgroups:
+// 736 rows, N = K = 4096 43 -> 48 us, Q|K|V 59 -> 67).  W_down of 736 rows, against cut 256 x 128 tiles with
+// arrival counters: 117 -> 93 us with the pass that sums.
+//
 // Half-stage layout: rows of 128 bytes in groups of 8 (1 KB, one load instruction); the
 // eight 16-byte chunks of row r are XOR-swizzled by (r / 2) % 8, so the 16 lanes of each
 // ds_read_b128 group touch distinct banks.  For kSwiGLU the W rows of a tile are gate and
@@ -32,6 +39,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "stream_sum.h"
 
 namespace epic {
 
@@ -59,7 +67,9 @@ struct WidePlan {
   int ks;                      // K stages per tile
   int gm;                      // row tiles per ordering group
   int G;                       // workgroups, a multiple of 8
+  int parts;                   // kPlanes: equal parts of K per tile, a workgroup each
 };
+constexpr int kPlanes = 4;     // epilogue: fp32 partial sums into planes (stream_sum.h)
 
 template <int EPI, int TM>
 __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan p) {
@@ -72,9 +82,21 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   const int wm = wv >> 1, wn = wv & 1;
   const int w = blockIdx.x;
   const int wr = (w % 8) * (p.G / 8) + w / 8;           // XCD-contiguous worker index (G % 8 == 0)
-  if (wr >= p.tiles) return;
+  // This worker's K stages: whole tiles wr, wr + G, ..; with kPlanes part wr / tiles of
+  // tile wr % tiles, so that the workgroups of an XCD are at the same K.
+  constexpr bool SPLIT = EPI == kPlanes;
+  if (wr >= (SPLIT ? p.parts * p.tiles : p.tiles)) return;
+  const int part = SPLIT ? wr / p.tiles : 0;
+  const int tile0 = SPLIT ? wr - part * p.tiles : wr;
+  const int kt0 = SPLIT ? part * p.ks / p.parts : 0;
+  const int n_units = SPLIT ? (part + 1) * p.ks / p.parts - kt0 : (p.tiles - wr + p.G - 1) / p.G * p.ks;
 
   auto tile_mn = [&](int t, int& mt, int& nt) __attribute__((always_inline)) {
+    if constexpr (SPLIT) {
+      nt = t / p.m_tiles;
+      mt = t - nt * p.m_tiles;
+      return;
+    }
     const int per_group = p.gm * p.n_tiles;
     const int grp = t / per_group;
     const int first = grp * p.gm;
@@ -94,9 +116,9 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(g.W), 0, w_rows * row_bytes, kBufWord3);
   int va[NLA], vb[NLB];
   struct Cursor {
-    int tile, kt, slot;
+    int tile, kt, slot, left;
   };
-  Cursor ca{wr, 0, 0}, cb{wr, 0, 1};                    // next half stages to load
+  Cursor ca{tile0, kt0, 0, n_units}, cb{tile0, kt0, 1, n_units};   // next half stages to load
   auto setup_a = [&]() __attribute__((always_inline)) {
     int mt, nt;
     tile_mn(ca.tile, mt, nt);
@@ -126,14 +148,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   setup_a();
   setup_b();
   auto bump = [&](int slot) __attribute__((always_inline)) { return slot >= SLOTS - 2 ? slot + 2 - SLOTS : slot + 2; };
-  // to the next half stage; past the last tile, its last stage again.  True: another tile
+  // to the next half stage; past the last, that one again.  True: another tile
   auto advance = [&](Cursor& c) __attribute__((always_inline)) {
     c.slot = bump(c.slot);
+    if (--c.left <= 0) return false;
     if (++c.kt < p.ks) return false;
-    if (c.tile + p.G >= p.tiles) {
-      c.kt = p.ks - 1;
-      return false;
-    }
     c.tile += p.G;
     c.kt = 0;
     return true;
@@ -204,12 +223,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   for (int i = 0; i < I + J; ++i) read1(f0, lds[0], lds[1], 0, i);
 
   int sa = 0, sb = 1;
-  for (int tile = wr; tile < p.tiles; tile += p.G) {
+  const int n = SPLIT ? n_units : p.ks;                 // stages per tile
+  for (int tile = tile0, left = n_units; left > 0; tile += p.G, left -= n) {
 #pragma unroll
     for (int i = 0; i < I; ++i)
 #pragma unroll
       for (int j = 0; j < J; ++j) acc[i][j] = f32x16{};
-    for (int kt = 0; kt < p.ks; ++kt) {
+    for (int kt = 0; kt < n; ++kt) {
       const char *pa = lds[sa], *pb = lds[sb];
       slice(f0, f1, pa, pb, 1, std::integral_constant<int, 1>{});
       slice(f1, f0, pa, pb, 2, std::integral_constant<int, 2>{});
@@ -306,11 +326,13 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
       // blocks of one MFMA tile; for the residual add the old values of DEPTH blocks are
       // in flight (a load is not moved above an earlier store)
       constexpr int DEPTH = 4;
-      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(g.C, 0, g.M * g.N * 4, kBufWord3);
-      const int n = nt * kTN + wn * 128;
-      if (n < g.N) {                                    // N % 128 == 0: all of the wavefront's columns, or none
+      float* c = g.C;
+      if constexpr (SPLIT) c = g.partial + size_t(part) * g.M * g.N;
+      const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(c, 0, g.M * g.N * 4, kBufWord3);
+      const int nw = nt * kTN + wn * 128;
+      if (nw < g.N) {                                   // N % 128 == 0: all of the wavefront's columns, or none
         auto at = [&](int b) __attribute__((always_inline)) {
-          return hide(((m0 + b / J * 32) * g.N + n + col + b % J * 32) * 4);
+          return hide(((m0 + b / J * 32) * g.N + nw + col + b % J * 32) * 4);
         };
         float old[DEPTH][16];
         auto fetch = [&](int b) __attribute__((always_inline)) {
@@ -359,6 +381,41 @@ void launch_wide_tm(const GemmArgs& g, hipStream_t stream) {
 }
 
 }  // namespace
+
+// Equal parts of K per tile, a workgroup each, in one round; at least eight stages a part,
+// planes within the workspace.  Time: a stage takes about 1.5 us with 256 rows, 1.25 with
+// 192.  Up to 128 rows the tiles would mostly be padding.
+WideSplit wide_split(int M, int N, int K) {
+  WideSplit best{};
+  if (M <= 128) return best;
+  for (const int tm : {256, 192}) {
+    const int64_t tiles = int64_t(cdiv(M, tm)) * cdiv(N, kTN);
+    if (tiles > kMaxWorkers / 2) continue;
+    const int64_t fit = int64_t(gemm_partial_floats()) / (int64_t(M) * N);
+    const int parts = int(std::min({kMaxWorkers / tiles, int64_t(K / kBK / 8), fit}));
+    if (parts < 2) continue;
+    const double time = 14.0 + cdiv(K / kBK, parts) * (tm == 256 ? 1.5 : 1.25);
+    if (best.parts == 0 || time < best.time) best = WideSplit{tm, parts, time};
+  }
+  return best;
+}
+
+StreamSum launch_gemm_wide_split(const GemmArgs& g, hipStream_t stream) {
+  const WideSplit w = wide_split(g.M, g.N, g.K);
+  WidePlan p{};
+  p.m_tiles = cdiv(g.M, w.tm);
+  p.n_tiles = cdiv(g.N, kTN);
+  p.ks = g.K / kBK;
+  p.tiles = p.m_tiles * p.n_tiles;
+  p.parts = w.parts;
+  p.G = cdiv(p.tiles * p.parts, 8) * 8;
+  StreamSum s{};
+  s.partial = g.partial;
+  s.M = g.M, s.N = g.N, s.fixed = p.parts;
+  if (w.tm == 192) gemm_wide_kernel<kPlanes, 192><<<p.G, 256, 0, stream>>>(g, p);
+  else gemm_wide_kernel<kPlanes, 256><<<p.G, 256, 0, stream>>>(g, p);
+  return s;
+}
 
 void launch_gemm_wide(const GemmArgs& g, int epi, int tm, hipStream_t stream) {
   if (tm == 256) {

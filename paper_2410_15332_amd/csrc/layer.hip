@@ -40,21 +40,23 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return s;
 }
 
-// The residual stream's pass between a weight-streaming GEMM and the next norm:
-// h += the GEMM's partial sums, then y = RMSNorm(h) w, the row kept in registers
-// between the two.  One workgroup of 1024 threads per row: there are few rows, and a
-// row's planes are many independent loads, so what bounds it is load latency.
+// The residual stream's pass between a GEMM that left partial sums and the next norm:
+// h += the sums, then y = RMSNorm(h) w, the row kept in registers between the two.  One
+// workgroup of 1024 threads per row: there are few rows, and a row's planes are many
+// independent loads, so what bounds it is load latency.  The squares are added in
+// rmsnorm_kernel's order (through LDS), so that a layer run on its own, whose last sum
+// and next norm are separate launches, gives the same bits as inside a model call.
 constexpr int kSumThreads = 1024;
 constexpr int kSumKeep = 2;                             // float4 per thread: hidden <= 8192
 __global__ __launch_bounds__(kSumThreads) void rmsnorm_sum_kernel(StreamSum s, float* __restrict__ x,
                                                                   const uint16_t* __restrict__ w,
                                                                   uint16_t* __restrict__ out_bf16,
                                                                   float* __restrict__ out_f32, float eps) {
-  __shared__ float red[kSumThreads / 64];
+  __shared__ float red[kNormThreads / 64];
+  __shared__ float sq[kSumKeep * kSumThreads];
   const int row = blockIdx.x, hidden = s.N, n4 = hidden / 4;
   float4* xr = reinterpret_cast<float4*>(x + size_t(row) * hidden);
   float4 keep[kSumKeep];
-  float ss = 0.0f;
 #pragma unroll
   for (int k = 0; k < kSumKeep; ++k) {
     const int i = threadIdx.x + k * kSumThreads;
@@ -62,15 +64,20 @@ __global__ __launch_bounds__(kSumThreads) void rmsnorm_sum_kernel(StreamSum s, f
     const float4 o = xr[i], d = s.sum4(row, 4 * i);
     keep[k] = make_float4(o.x + d.x, o.y + d.y, o.z + d.z, o.w + d.w);
     xr[i] = keep[k];
-    ss += keep[k].x * keep[k].x + keep[k].y * keep[k].y + keep[k].z * keep[k].z + keep[k].w * keep[k].w;
+    sq[i] = keep[k].x * keep[k].x + keep[k].y * keep[k].y + keep[k].z * keep[k].z + keep[k].w * keep[k].w;
   }
+  __syncthreads();
+  if (threadIdx.x < kNormThreads) {
+    float ss = 0.0f;
+    for (int i = threadIdx.x; i < n4; i += kNormThreads) ss += sq[i];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  }
   __syncthreads();
   float total = 0.0f;
 #pragma unroll
-  for (int v = 0; v < kSumThreads / 64; ++v) total += red[v];
+  for (int v = 0; v < kNormThreads / 64; ++v) total += red[v];
   const float inv = 1.0f / sqrtf(total / float(hidden) + eps);
 #pragma unroll
   for (int k = 0; k < kSumKeep; ++k) {

@@ -144,10 +144,11 @@ void add_norm(StreamSum* pending, float* h, const uint16_t* w, uint16_t* x, floa
   pending->partial = nullptr;
 }
 
-// h += the product g; a streamed product stays pending until the next norm (add_norm).
+// h += the product g; partial sums stay pending until the next norm (add_norm).
 void residual_gemm(const GemmArgs& g, StreamSum* pending, hipStream_t stream) {
-  if (gemm_route(g, kResidual) == GemmRoute::kStream)
-    *pending = launch_gemm_stream(g, stream);
+  const GemmRoute r = gemm_route(g, kResidual);
+  if (is_partial(r))
+    *pending = launch_gemm_partial(g, r, stream);
   else
     launch_gemm(g, kResidual, stream);
 }
@@ -161,11 +162,12 @@ epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, cons
   const int n = s->n_s, H = c->hidden;
   const LayerGemms l = layer_gemms(c, w, n, h, ws);
   if (!normed) add_norm(pending, h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
-  // a streamed Q|K|V product is summed straight into the private blocks
-  const bool write = s->n_rerotated == 0 && gemm_route(l.qkv, kRope) == GemmRoute::kStream;
+  // partial sums of Q|K|V go straight into the private blocks
+  const GemmRoute qr = gemm_route(l.qkv, kRope);
+  const bool write = s->n_rerotated == 0 && is_partial(qr);
   if (write) {
     const StreamWrite sw{p->priv_block, p->priv_src, p->priv_rows, s->n_private, kc, vc};
-    launch_stream_rope_write(launch_gemm_stream(l.qkv, stream), l.qkv, sw, stream);
+    launch_stream_rope_write(launch_gemm_partial(l.qkv, qr, stream), l.qkv, sw, stream);
   } else {
     launch_gemm(l.qkv, kRope, stream);
   }

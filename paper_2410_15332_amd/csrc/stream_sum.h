@@ -15,6 +15,7 @@ struct StreamSum {
   int tm, tn, m_tiles, ks;   // rows and columns per tile, row tiles, K stages per tile (tile t = column tile * m_tiles + row tile)
   int kh;                // wavefronts of a workgroup that share an MFMA tile by k-slices: a plane each
   int units, G;          // K stages over all tiles, workers; units * G < 2^31
+  int fixed;             // planes of every tile, where that is one number (the fields above are then unused)
 
   // worker w runs units [begin(w), begin(w + 1)); owner(v): the worker of unit v
   __host__ __device__ int begin(int w) const { return int(int64_t(w) * units / G); }
@@ -26,7 +27,7 @@ struct StreamSum {
   // columns n .. n + 3 of row m (n % 4 == 0), the planes added in K order; four planes'
   // loads in flight at a time, the ones past the last repeating it and adding 0
   __device__ __forceinline__ float4 sum4(int m, int n) const {
-    const int np = planes(n / tn * m_tiles + m / tm);
+    const int np = fixed > 0 ? fixed : planes(n / tn * m_tiles + m / tm);
     const size_t plane = size_t(M) * N;
     const float* p = partial + size_t(m) * N + n;
     float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -49,6 +50,19 @@ struct StreamSum {
 
 // Enqueue the partial sums of g's product (g.partial: the GEMM workspace); returns how to sum them.
 StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream);
+// The same with 192- or 256-row tiles of 256 columns, each cut into equal parts of K
+// (gemm_wide.hip); parts = 0 where that gives fewer than two.  time: estimate in us.
+struct WideSplit {
+  int tm, parts;
+  double time;
+};
+WideSplit wide_split(int M, int N, int K);
+StreamSum launch_gemm_wide_split(const GemmArgs& g, hipStream_t stream);
+// The partial sums of a route that leaves them to the consumer.
+inline bool is_partial(GemmRoute r) { return r == GemmRoute::kStream || r == GemmRoute::kSplit; }
+inline StreamSum launch_gemm_partial(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
+  return r == GemmRoute::kSplit ? launch_gemm_wide_split(g, stream) : launch_gemm_stream(g, stream);
+}
 // Whether the partial sums of a product of these sizes fit the GEMM workspace.
 bool stream_fits(int M, int N, int K);
 // Enqueue the pass that sums the planes and runs g's epilogue.

@@ -225,3 +225,16 @@ def test_wide_tiles(m, n, k, epi):
     rng = np.random.default_rng(11)
     sample = sorted(set([0, 1, 127, 128, 191, 192, 255, 256, m - 2, m - 1] + rng.integers(0, m, 90).tolist()))
     _run(m, n, k, epi, tag=100 + WIDE.index((m, n, k, epi)), sample=sample)
+
+
+SPLIT = [  # 256-wide tiles in equal parts of K, each an fp32 plane (few tiles, long K, over 128 rows)
+    (600, 512, 4096, "residual"),       # 3 x 2 tiles of 256 rows in 8 parts of 8 stages
+    (550, 640, 4160, "store"),          # 65 stages: parts of 8 and 9; the last column tile half past the end
+    (700, 1280, 4096, "swiglu"),        # gate and up summed by the SwiGLU pass
+    (370, 256, 14336, "residual"),      # two row tiles of 192, 28 parts
+]
+
+
+@pytest.mark.parametrize("m,n,k,epi", SPLIT, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in SPLIT])
+def test_split_wide_tiles(m, n, k, epi):
+    _run(m, n, k, epi, tag=110 + SPLIT.index((m, n, k, epi)))

@@ -334,3 +334,25 @@ def test_decode_layer_writes_into_the_linked_cache(hq, hkv, d):
     before_v[blocks, :, :, slots] = vc[blocks, :, :, slots]
     assert torch.equal(kc.view(torch.int16), before_k.view(torch.int16))
     assert torch.equal(vc.view(torch.int16), before_v.view(torch.int16))
+
+
+@pytest.mark.parametrize("suffix", [30, 520])
+def test_layers_alone_are_the_model_call(suffix):
+    """epic_link_layer layer by layer and one epic_link_model call give the same residual
+    stream and the same caches bit for bit, also where a layer's last projection leaves
+    partial sums (streamed weights; split tiles past 512 rows) that the model call adds in
+    the next layer's norm."""
+    from paper_2410_15332_amd import epic_link as el
+    wl = _small("layers_alone", [40, 33], suffix, 4, hidden=512, ffn=4096, hq=8, hkv=2, d=64, layers=3)
+    st = _stage(wl, caches="synthetic")
+    st.run()
+    torch.cuda.synchronize()
+    caches = [_bits(t).copy() for t in st.k_caches + st.v_caches]
+    hidden = st.hidden.cpu().numpy().copy()
+    h = st.emb.clone()
+    for layer in range(wl.n_layers):
+        el.epic_link_layer(st.cfg, st.layers[layer], st.dplan, h, st.k_caches[layer], st.v_caches[layer], st.workspace)
+    torch.cuda.synchronize()
+    assert np.array_equal(h.cpu().numpy(), hidden)
+    for a, b in zip(caches, st.k_caches + st.v_caches):
+        assert np.array_equal(a, _bits(b))
