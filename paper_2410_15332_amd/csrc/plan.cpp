@@ -208,10 +208,14 @@ double estimate_makespan(const std::vector<Tile>& tiles, int split, int hkv, con
 }
 
 // Key blocks per split-KV work item: among splits max_nblk / n (n from 1 to 128
-// in about geometric steps, rounded up to whole 4-block tiles, never below 64
-// blocks, because every split writes and re-reads a tile of fp32 partial
-// results), the one with the shortest estimated launch, where a finer split
-// must be 3% shorter to win (fewer partials).  *time receives that estimate.
+// in about geometric steps, rounded up to whole 4-block tiles), the one with the
+// shortest estimated launch, where a finer split must be 3% shorter to win (fewer
+// partials).  Below 64 blocks only while every item has a CU to itself: there the
+// launch lasts as long as its longest item, whatever the others do (4 x 128 + 16
+// tokens, 8 heads of 64: 9 steps in one item 14.9 us, a step each 4.8 and 3.7 for
+// the combine); with more items the partials that every split writes and re-reads
+// cost more than they gain (10 x 512 tokens, 32 heads: 64 blocks 34 + 5 us, 32
+// blocks 33 + 7, 16 blocks 48 + 10).  *time receives that estimate.
 int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const TileShape& sh, double* time) {
   const int hkv = cfg->num_kv_heads;
   if (cfg->kv_split_blocks > 0) {
@@ -219,7 +223,8 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
     *time = estimate_makespan(tiles, split, hkv, sh);
     return split;
   }
-  constexpr int kMinSplit = 64;
+  constexpr int kMinSplit = 64;        // ... in general
+  constexpr int64_t kCus = 256;
   constexpr int64_t kMaxRounds = 16;   // past this many dispatch rounds, splitting cannot balance better
   int max_nblk = kKvTileBlocks;
   for (const Tile& t : tiles) max_nblk = std::max(max_nblk, t.nblk);
@@ -228,6 +233,9 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
     for (const Tile& t : tiles) n += std::max(1, cdiv(t.nblk, split));
     return n;
   };
+  // A first split adds the combine's launch, which a short decode item does not repay
+  // (in steps; 14 blocks unsplit 13.5 us, split 15.2; 125 blocks of 128 dims 23 -> 15).
+  const double first_split = sh.rows == kTileRowsTiny ? (cfg->head_dim == 64 ? 16.0 : 8.0) : 0.0;
   const int whole = cdiv(max_nblk, kKvTileBlocks) * kKvTileBlocks;
   int best = whole;
   double best_time = estimate_makespan(tiles, whole, hkv, sh);
@@ -235,16 +243,16 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
     int prev = whole;
     static constexpr int kParts[] = {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 96, 128};
     for (const int n : kParts) {
-      const int split = std::max(kMinSplit, cdiv(cdiv(max_nblk, n), kKvTileBlocks) * kKvTileBlocks);
+      int split = cdiv(cdiv(max_nblk, n), kKvTileBlocks) * kKvTileBlocks;
+      if (split < kMinSplit && n_items(split) * hkv > kCus) split = kMinSplit;
       if (split >= prev) continue;
       prev = split;
       if (n_items(split) * hkv > kMaxRounds * sh.slots) break;
-      const double t = estimate_makespan(tiles, split, hkv, sh);
+      const double t = estimate_makespan(tiles, split, hkv, sh) + first_split;
       if (t < best_time * 0.97) {               // finer splits must pay for their partials clearly
         best_time = t;
         best = split;
       }
-      if (split == kMinSplit) break;
     }
   }
   *time = best_time;
@@ -734,7 +742,11 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   for (const Group& g : groups) read += runs[g.run].n;
   for (const auto& o : own)
     for (const auto& x : o) read += x.second - x.first;
-  if (read * 4 > total * 3) return false;                 // fewer than a quarter of the block reads saved
+  // Not where fewer than a quarter of the block reads are saved, nor for requests of
+  // under 1024 tokens, whose items are too short to repay the combine.
+  int64_t n_rows = 0;
+  for (const DecodeReq& d : dr) n_rows += d.t > 0;
+  if (read * 4 > total * 3 || total < 64 * n_rows) return false;
   // Unshared blocks: ranges of at least kListBelow blocks as items of their own, the
   // rest of a request's listed together.
   constexpr int kListBelow = 48, kListMost = 96;

@@ -601,3 +601,27 @@ def test_shared_decode_rule():
     assert kinds(same, el.attn_cfg(32, 8, 128, 0.0, 16)) == {0}
     assert kinds(same[:1], cfg) == {0}
     assert kinds([el.Request([1024], [[64 * r + i for i in ids]], 20, 0) for r in range(4)], cfg) == {0}
+
+
+def test_small_launches_split_below_64_blocks():
+    """A split under 64 blocks only while every item has a CU (256) to itself; a short
+    decode item stays whole (its combine would cost more than it gains)."""
+    def shape(reqs, n_used, hq, hkv, d=64):
+        cfg = el.attn_cfg(hq, hkv, d)
+        need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
+        s, _, v = el.epic_plan_link(reqs, cfg, list(range(n_used, n_used + need)), n_used + need)
+        work = v["work"].reshape(-1, 8)
+        return s, int((work[:, 2] - work[:, 1]).max())
+
+    reqs, n = _long_request([128] * 4, 16, 4)
+    s, longest = shape(reqs, n, 8, 8)                      # 33 blocks x 8 heads
+    assert s.n_work > 1 and longest < 64 and s.n_work * 8 <= 256
+    reqs, n = _long_request([512] * 10, 64, 16)
+    s, longest = shape(reqs, n, 32, 8, 128)                # finer than 64 blocks would pass 256 items
+    assert longest == 64
+    reqs, n = _long_request([200], 2, 0)
+    s, _ = shape(reqs, n, 32, 8, 128)                      # 16-row tile over 14 blocks
+    assert s.tile_rows == 16 and s.n_work == 1 and s.n_partials == 0
+    reqs, n = _long_request([2000], 2, 0)
+    s, longest = shape(reqs, n, 32, 8, 128)                # ... over 126
+    assert s.tile_rows == 16 and s.n_work > 4 and s.n_work * 8 <= 256
