@@ -617,8 +617,11 @@ def test_small_launches_split_below_64_blocks():
     s, longest = shape(reqs, n, 8, 8)                      # 33 blocks x 8 heads
     assert s.n_work > 1 and longest < 64 and s.n_work * 8 <= 256
     reqs, n = _long_request([512] * 10, 64, 16)
-    s, longest = shape(reqs, n, 32, 8, 128)                # finer than 64 blocks would pass 256 items
-    assert longest == 64
+    s, longest = shape(reqs, n, 32, 8, 128)                # 32 items of at most 56 blocks: the CUs, no more
+    assert longest < 64 and s.n_work * 8 == 256
+    reqs, n = _long_request([512] * 20, 64, 16)
+    s, longest = shape(reqs, n, 32, 8, 128)                # finer than 64 blocks would pass them
+    assert longest >= 64
     reqs, n = _long_request([200], 2, 0)
     s, _ = shape(reqs, n, 32, 8, 128)                      # 16-row tile over 14 blocks
     assert s.tile_rows == 16 and s.n_work == 1 and s.n_partials == 0
