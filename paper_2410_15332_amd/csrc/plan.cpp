@@ -649,18 +649,24 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   const int G = cfg->num_q_heads / cfg->num_kv_heads, R = kTileRowsTiny / G;
   const int batch = static_cast<int>(dr.size());
   if (R < 2) return false;
-  int max_id = -1;
-  for (int i = 0; i < ps->n_linked_blocks; ++i) {
-    const int id = prev->linked_blocks[i];
-    if (id < 0 || id > (1 << 26)) return false;           // (validated later)
-    max_id = std::max(max_id, id);
-  }
+  // entry of every linked block by its physical id (open addressing; block ids may be sparse)
   struct Ref {
     uint64_t sig = 0;
-    int count = 0, last = -1, len = 0;
+    int id = -1, count = 0, last = -1, len = 0, run = -1;   // run: the one that starts with this block
     bool bad = false;
   };
-  std::vector<Ref> ref(static_cast<size_t>(max_id + 1));
+  size_t slots_n = 64;
+  while (slots_n < 2 * static_cast<size_t>(ps->n_linked_blocks)) slots_n *= 2;
+  std::vector<Ref> ref(slots_n);
+  std::vector<int> entry(static_cast<size_t>(ps->n_linked_blocks));
+  for (int i = 0; i < ps->n_linked_blocks; ++i) {
+    const int id = prev->linked_blocks[i];
+    if (id < 0) return false;                               // (rejected later)
+    size_t at = (static_cast<uint32_t>(id) * 2654435761u) & (slots_n - 1);
+    while (ref[at].id >= 0 && ref[at].id != id) at = (at + 1) & (slots_n - 1);
+    ref[at].id = id;
+    entry[i] = static_cast<int>(at);
+  }
   int64_t total = 0;
   auto frozen = [&](int b) { return dr[b].e - dr[b].a - (dr[b].room > 0 ? 1 : 0); };   // blocks that take no new row
   for (int b = 0; b < batch; ++b) {
@@ -668,7 +674,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     total += dr[b].e - dr[b].a + dr[b].extra;
     const uint64_t h = (uint64_t(b) + 1) * 0x9E3779B97F4A7C15ull;
     for (int i = 0; i < frozen(b); ++i) {
-      Ref& x = ref[prev->linked_blocks[dr[b].a + i]];
+      Ref& x = ref[entry[dr[b].a + i]];
       const int len = prev->block_len[dr[b].a + i];
       x.bad = x.bad || x.last == b || (x.count > 0 && x.len != len);
       x.sig += (h ^ (h >> 29)) * 0xBF58476D1CE4E5B9ull;
@@ -678,12 +684,11 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     }
   }
   auto sig_of = [&](int b, int i) {
-    const Ref& x = ref[prev->linked_blocks[dr[b].a + i]];
+    const Ref& x = ref[entry[dr[b].a + i]];
     return x.count > 1 && !x.bad ? x.sig : 0;
   };
   // runs of blocks with the same set of requests; a run of one request is its own
   std::vector<SharedRun> runs;
-  std::vector<int> run_at(static_cast<size_t>(max_id + 1), -1);   // by the run's first block
   std::vector<std::vector<std::pair<int, int>>> own(batch);       // [i0, i1) of each request, unshared
   auto add_own = [&](int b, int i, int n) {
     if (!own[b].empty() && own[b].back().second == i) own[b].back().second = i + n;
@@ -700,7 +705,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
         add_own(b, i, j - i);
       } else {
         const int32_t* ids = prev->linked_blocks + dr[b].a + i;
-        int& r = run_at[ids[0]];
+        int& r = ref[entry[dr[b].a + i]].run;
         if (r < 0) {
           r = static_cast<int>(runs.size());
           runs.push_back(SharedRun{b, i, j - i, {{b, i}}});
