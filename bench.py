@@ -604,8 +604,9 @@ def _decode_inputs(wl, ds, r, f):
 def bench_decode(args, wl):
     """Decode after the link step: one new token per request attends over its linked
     sequence (link step run once, untimed; the same decode step is then timed).  The
-    attention kernel reads each request's K/V once: roofline against HBM, algorithmic
-    bytes = sum over requests of (linked tokens + 1) x Hkv x D x 2 B x 2 (K and V)."""
+    attention cannot do without reading each linked block once, however many requests
+    link it: roofline against HBM, algorithmic bytes = tokens of the distinct linked
+    blocks x Hkv x D x 2 B x 2 (K and V)."""
     import numpy as np
     import torch
 
@@ -636,7 +637,8 @@ def bench_decode(args, wl):
     attn_ms = float(np.mean([e[1].elapsed_time(e[2]) for e in ev]))
     comb_ms = float(np.mean([e[2].elapsed_time(e[3]) for e in ev]))
     linked = ds.views["s_pos"].astype(np.int64) + 1
-    kv_bytes = float(linked.sum()) * wl.num_kv_heads * wl.head_dim * 2 * 2
+    _, first = np.unique(ds.views["linked_blocks"], return_index=True)
+    kv_bytes = float(ds.views["block_len"][first].sum()) * wl.num_kv_heads * wl.head_dim * 2 * 2
     gbs = kv_bytes / (attn_ms * 1e-3) / 1e9
     log(f"decode step {step_ms:.4f} ms: attention {attn_ms:.4f} ms ({gbs:.0f} GB/s of K/V), combine {comb_ms:.4f}")
     result = {
