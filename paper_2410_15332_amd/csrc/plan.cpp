@@ -649,20 +649,26 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   const int G = cfg->num_q_heads / cfg->num_kv_heads, R = kTileRowsTiny / G;
   const int batch = static_cast<int>(dr.size());
   if (R < 2) return false;
-  // entry of every linked block by its physical id (open addressing; block ids may be sparse)
+  // entry of every linked block by its physical id: the id itself where the ids are about
+  // as many as the blocks (a plan of 32 requests over 32000 linked blocks 1.0 ms, hashed
+  // 1.4), else open addressing
   struct Ref {
     uint64_t sig = 0;
     int id = -1, count = 0, last = -1, len = 0, run = -1;   // run: the one that starts with this block
     bool bad = false;
   };
+  int max_id = 0;
+  for (int i = 0; i < ps->n_linked_blocks; ++i) max_id = std::max(max_id, prev->linked_blocks[i]);
+  const bool dense = max_id < 2 * int64_t(ps->n_linked_blocks);
   size_t slots_n = 64;
-  while (slots_n < 2 * static_cast<size_t>(ps->n_linked_blocks)) slots_n *= 2;
+  while (!dense && slots_n < 2 * static_cast<size_t>(ps->n_linked_blocks)) slots_n *= 2;
+  if (dense) slots_n = static_cast<size_t>(max_id) + 1;
   std::vector<Ref> ref(slots_n);
   std::vector<int> entry(static_cast<size_t>(ps->n_linked_blocks));
   for (int i = 0; i < ps->n_linked_blocks; ++i) {
     const int id = prev->linked_blocks[i];
     if (id < 0) return false;                               // (rejected later)
-    size_t at = (static_cast<uint32_t>(id) * 2654435761u) & (slots_n - 1);
+    size_t at = dense ? static_cast<size_t>(id) : (static_cast<uint32_t>(id) * 2654435761u) & (slots_n - 1);
     while (ref[at].id >= 0 && ref[at].id != id) at = (at + 1) & (slots_n - 1);
     ref[at].id = id;
     entry[i] = static_cast<int>(at);

@@ -598,6 +598,7 @@ def test_shared_decode_rule():
 
     same = [el.Request([1024], [ids], 20, 0) for _ in range(4)]
     assert 1 in kinds(same, cfg)
+    assert 1 in kinds(same[:2], cfg)                       # block ids sparse: twice the blocks and more
     assert kinds(same, el.attn_cfg(32, 8, 128, 0.0, 16)) == {0}
     assert kinds(same[:1], cfg) == {0}
     assert kinds([el.Request([1024], [[64 * r + i for i in ids]], 20, 0) for r in range(4)], cfg) == {0}
