@@ -39,8 +39,9 @@ int gemm_counters();          // arrival counters at tile_count
 // How a GEMM runs: whole 256-wide tiles, one round of whole narrow tiles, narrow tiles
 // cut along K (the only route that uses the arrival counters), streamed weights
 // (gemm_stream.hip) or 256-wide tiles in equal parts of K (gemm_wide.hip); the last two
-// leave partial sums and a pass that adds them up.
-enum class GemmRoute { kWhole256, kWhole192, kWhole128, kWhole96, kCut, kStream, kSplit };
+// leave partial sums and a pass that adds them up.  kGlu: one round of whole streamed
+// gate|up tiles.
+enum class GemmRoute { kWhole256, kWhole192, kWhole128, kWhole96, kCut, kStream, kSplit, kGlu };
 GemmRoute gemm_route(const GemmArgs& g, int epi);
 // Zero the arrival counters (a kernel, so it can sit in a captured stream).
 void launch_gemm_clear(int* tile_count, hipStream_t stream);

@@ -667,6 +667,7 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
     const int64_t r192 = (int64_t(cdiv(g.M, 192)) * n256 + kMaxWorkers - 1) / kMaxWorkers;
     return r192 * 13 < r256 * 16 ? GemmRoute::kWhole192 : GemmRoute::kWhole256;
   }
+  if (swiglu && glu_fits(g.M, g.ffn, g.K)) return GemmRoute::kGlu;
   // Fewer: with a short K and one round of 96 x 128 or 128 x 128 tiles that fills at
   // least 3/4 of the CUs, those tiles whole (96 rows where they make such a round: more
   // CUs, fewer bytes each); else 256 x 128 tiles cut along K so that every CU gets a
@@ -738,6 +739,8 @@ void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream) {
   const GemmRoute r = gemm_route(g, epi);
   if (is_partial(r))
     launch_stream_finish(launch_gemm_partial(g, r, stream), g, epi, stream);
+  else if (r == GemmRoute::kGlu)
+    launch_gemm_glu(g, stream);
   else if (r == GemmRoute::kWhole256 || r == GemmRoute::kWhole192)
     launch_gemm_wide(g, epi, r == GemmRoute::kWhole256 ? 256 : 192, stream);
   else if (epi == kStoreF32)

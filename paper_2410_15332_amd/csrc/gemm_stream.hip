@@ -59,9 +59,19 @@ struct StreamArgs {
   float* partial;       // [planes][M][N]
   int M, N, K;
   StreamSum s;
+  uint16_t* act;        // whole gate|up tiles: their result
+  int ffn;
 };
 
-template <int TM, int TN, int NW, int CT, int NS, int OCC>
+__device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcpf(1.0f + fast_exp2(-x * kLog2e)); }
+
+// GLU: a tile's columns are TN / 2 gate columns and the same up columns; worker w has the
+// whole tile w and stores silu(gate) * up itself.  It starts at K stage w % ks and wraps:
+// rows of W a multiple of 4 KB apart put the same stage of every row on the same few
+// memory channels, so the workers have to be at different stages.  K = 4096, ffn 14336:
+// 32 rows 52.4 us in partial sums, 53.1 in whole tiles that start alike, 44.8 so (235 MB
+// at 5.2 TB/s); 128 rows 55.7, 55.7 and 51.4.
+template <int TM, int TN, int NW, int CT, int NS, int OCC, bool GLU = false>
 __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g) {
   constexpr int NG = (TM + TN) / 8;                    // 1 KB row groups per stage
   constexpr int NL = NG / NW;                           // ... per wavefront
@@ -69,6 +79,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
   constexpr int NT = (TM / 32) * (TN / 32 / CT);       // wavefront tiles of 32 rows x 32 CT columns
   constexpr int KH = NW / NT;                           // wavefronts that share one, by k-slices
   static_assert(KH * NT == NW && 4 % KH == 0, "wavefronts per tile");
+  static_assert(!GLU || (KH == 1 && CT == 2), "a wavefront holds the gate and up of its columns");
   constexpr int SB = (TM + TN) * 128;                  // bytes per stage
   __shared__ __attribute__((aligned(1024))) char lds[NS][SB];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -97,12 +108,14 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
       const int gi = wv * NL + i;
       const bool is_a = gi < TM / 8;
       const int row = (is_a ? gi : gi - TM / 8) * 8 + lrow;
-      const int gr = is_a ? min(mt * TM + row, g.M - 1) : nt * TN + row;
+      int gr = is_a ? min(mt * TM + row, g.M - 1) : nt * TN + row;
+      if (GLU && !is_a) gr = nt * (TN / 2) + row % (TN / 2) + (row >= TN / 2 ? g.ffn : 0);
       vo[i] = gr * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
     }
   };
   int du = u0, dtile = u0 / ks, dkt = u0 - dtile * ks;   // next unit to load
   setup(dtile);
+  if (GLU) dkt = wr % ks;
   auto dma_next = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) stream_dma16(rs[i], lds[buf] + (wv * NL + i) * 1024, vo[i], dkt * (kBK * 2));
@@ -110,7 +123,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
       ++du;
       if (++dkt == ks) {
         dkt = 0;
-        setup(++dtile);
+        if (!GLU) setup(++dtile);
       }
     }
   };
@@ -118,7 +131,8 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
   // ---- compute: wavefront -> tile (rt, ct) and its share of the stage's four k-slices
   const int mt_ = wv % NT, kh = wv / NT;
   constexpr int WC = TN / 32 / CT;                      // wavefront tiles along N
-  const int rt = mt_ / WC, ct = mt_ % WC * CT;
+  const int rt = mt_ / WC, ct = mt_ % WC * (GLU ? 1 : CT);
+  constexpr int CS = GLU ? WC : 1;                      // 32-column blocks between a wavefront's CT
   const int lbase = (lane & 31) * 128, lsw = (lane >> 1) & 7, half = lane >> 5;
   const int abase = rt * 4096 + lbase, bbase = (TM / 32 + ct) * 4096 + lbase;
 
@@ -144,7 +158,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
         const int c = ((2 * (kh * (4 / KH) + i) + half) ^ lsw) * 16;
         f.a[i] = *reinterpret_cast<const bf16x8*>(p + abase + c);
 #pragma unroll
-        for (int j = 0; j < CT; ++j) f.b[i][j] = *reinterpret_cast<const bf16x8*>(p + bbase + j * 4096 + c);
+        for (int j = 0; j < CT; ++j) f.b[i][j] = *reinterpret_cast<const bf16x8*>(p + bbase + j * CS * 4096 + c);
       }
       buf = buf + 1 == NS ? 0 : buf + 1;
       __builtin_amdgcn_sched_barrier(0);
@@ -173,10 +187,22 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
     }
     // this worker's part of the tile: plane (worker - first worker of the tile) * KH + kh
     const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
+    const int m0 = mt * TM + rt * 32 + half * 4;
+    if constexpr (GLU) {
+      const __amdgpu_buffer_rsrc_t ro =
+          __builtin_amdgcn_make_buffer_rsrc(g.act, 0, g.M * g.ffn * 2, kBufWord3);   // rows past M: dropped
+      const int n = nt * (TN / 2) + ct * 32 + (lane & 31);
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        __builtin_amdgcn_raw_buffer_store_b16(uint16_t(pack_bf16x2(silu(acc[0][r]) * acc[1][r], 0.0f)), ro,
+                                              ((m0 + (r >> 2) * 8 + (r & 3)) * g.ffn + n) * 2, 0, 0);
+      ++tile;
+      continue;
+    }
     const int plane = (wr - g.s.owner(tile * ks)) * KH + kh;
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
         g.partial + size_t(plane) * g.M * g.N, 0, g.M * g.N * 4, kBufWord3);   // rows past M: dropped
-    const int m0 = mt * TM + rt * 32 + half * 4, n = nt * TN + ct * 32 + (lane & 31);
+    const int n = nt * TN + ct * 32 + (lane & 31);
 #pragma unroll
     for (int r = 0; r < 16; ++r)
 #pragma unroll
@@ -201,7 +227,6 @@ __global__ __launch_bounds__(256) void stream_finish_kernel(StreamSum s, float* 
   float4 v = s.sum4(m, n);
   if constexpr (EPI == kSwiGLU) {
     const float4 up = s.sum4(m, ffn + n);
-    auto silu = [](float x) { return x * __builtin_amdgcn_rcpf(1.0f + fast_exp2(-x * kLog2e)); };
     *reinterpret_cast<uint2*>(act + size_t(m) * ffn + n) =
         make_uint2(pack_bf16x2(silu(v.x) * up.x, silu(v.y) * up.y), pack_bf16x2(silu(v.z) * up.z, silu(v.w) * up.w));
   } else {
@@ -359,6 +384,30 @@ StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream) {
   if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9, 1>(g, stream);
   if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4, 1>(g, stream);
   return launch_tm<128, 64, 8, 1, 6, 1>(g, stream);
+}
+
+// Gate|up of up to 128 rows where its 64 + 64-column tiles make one round that fills at
+// least 3/4 of the CUs, and W's rows are a multiple of 4 KB apart, so that the memory
+// channels are the bound (K = 5120, ffn 13824: 52.2 us in partial sums, 53.3 here).
+bool glu_fits(int M, int ffn, int K) {
+  return M <= 128 && ffn / 64 >= 192 && ffn / 64 <= 256 && K % 2048 == 0;
+}
+
+template <int TM, int NW, int NS>
+static void launch_glu(const GemmArgs& g, hipStream_t stream) {
+  StreamArgs a{};
+  a.A = g.A, a.W = g.W, a.M = g.M, a.N = g.N, a.K = g.K, a.act = g.act, a.ffn = g.ffn;
+  a.s.M = g.M, a.s.N = g.N, a.s.tm = TM, a.s.tn = 128, a.s.m_tiles = 1, a.s.kh = 1;
+  a.s.ks = g.K / kBK;
+  a.s.G = g.ffn / 64;
+  a.s.units = a.s.G * a.s.ks;
+  gemm_stream_kernel<TM, 128, NW, 2, NS, 1, true><<<a.s.G, NW * 64, 0, stream>>>(a);
+}
+
+void launch_gemm_glu(const GemmArgs& g, hipStream_t stream) {
+  if (g.M <= 32) launch_glu<32, 2, 7>(g, stream);
+  else if (g.M <= 64) launch_glu<64, 4, 6>(g, stream);
+  else launch_glu<128, 8, 4>(g, stream);
 }
 
 void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStream_t stream) {

@@ -65,6 +65,9 @@ inline StreamSum launch_gemm_partial(const GemmArgs& g, GemmRoute r, hipStream_t
 }
 // Whether the partial sums of a product of these sizes fit the GEMM workspace.
 bool stream_fits(int M, int N, int K);
+// Gate|up of a short row set in one round of whole tiles, with SwiGLU; whether it takes these sizes.
+bool glu_fits(int M, int ffn, int K);
+void launch_gemm_glu(const GemmArgs& g, hipStream_t stream);
 // Enqueue the pass that sums the planes and runs g's epilogue.
 void launch_stream_finish(const StreamSum& s, const GemmArgs& g, int epi, hipStream_t stream);
 // The link write of a streamed Q|K|V product: the plan's private blocks and the layer's caches.

@@ -238,3 +238,18 @@ SPLIT = [  # 256-wide tiles in equal parts of K, each an fp32 plane (few tiles, 
 @pytest.mark.parametrize("m,n,k,epi", SPLIT, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in SPLIT])
 def test_split_wide_tiles(m, n, k, epi):
     _run(m, n, k, epi, tag=110 + SPLIT.index((m, n, k, epi)))
+
+
+GLU = [  # up to 128 rows of gate|up in one round of whole 64 + 64-column tiles (192 to 256 of them)
+    (1, 2 * 12288, 2048),               # fewest tiles, one row; fewer K stages than tiles
+    (32, 2 * 16384, 2048),              # most tiles
+    (33, 2 * 12416, 2048),              # 194 tiles: no XCD order; 64-row tiles from here
+    (64, 2 * 14336, 4096),
+    (65, 2 * 12288, 6144),              # 128-row tiles
+    (128, 2 * 14336, 4096),
+]
+
+
+@pytest.mark.parametrize("m,n,k", GLU, ids=[f"{m}x{n}x{k}" for m, n, k in GLU])
+def test_whole_streamed_gate_up(m, n, k):
+    _run(m, n, k, "swiglu", tag=120 + GLU.index((m, n, k)))
