@@ -237,6 +237,14 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
   // (in steps; 14 blocks unsplit 13.5 us, split 15.2; 125 blocks of 128 dims 23 -> 15).
   const double first_split = sh.rows == kTileRowsTiny ? (cfg->head_dim == 64 ? 16.0 : 8.0) : 0.0;
   const int whole = cdiv(max_nblk, kKvTileBlocks) * kKvTileBlocks;
+  // Likewise link items of up to 8 steps of 64 dims: the combine is a third launch, and the
+  // host takes about 15 us to enqueue three, 13 for two (3 x 128 + 16 tokens, 7 steps: split
+  // 16.4 us, whole 13.6; 9 steps, split 15.0, whole 17.3).  Not 128 dims, whose steps take
+  // longer (5 steps: split 16.2, whole 18.0).
+  if (sh.rows != kTileRowsTiny && cfg->head_dim == 64 && whole <= 8 * kKvTileBlocks) {
+    *time = estimate_makespan(tiles, whole, hkv, sh);
+    return whole;
+  }
   int best = whole;
   double best_time = estimate_makespan(tiles, whole, hkv, sh);
   if (n_items(whole) * hkv < kMaxRounds * sh.slots) {
