@@ -617,6 +617,8 @@ def test_small_launches_split_below_64_blocks():
     reqs, n = _long_request([128] * 4, 16, 4)
     s, longest = shape(reqs, n, 8, 8)                      # 33 blocks x 8 heads
     assert s.n_work > 1 and longest < 64 and s.n_work * 8 <= 256
+    reqs, n = _long_request([128] * 3, 128, 4)
+    assert shape(reqs, n, 8, 8)[0].n_partials == 0         # 32 blocks of 64 dims: whole
     reqs, n = _long_request([512] * 10, 64, 16)
     s, longest = shape(reqs, n, 32, 8, 128)                # 32 items of at most 56 blocks: the CUs, no more
     assert longest < 64 and s.n_work * 8 == 256
