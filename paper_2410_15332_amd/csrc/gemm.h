@@ -43,6 +43,7 @@ int gemm_counters();          // arrival counters at tile_count
 // gate|up tiles.
 enum class GemmRoute { kWhole256, kWhole192, kWhole128, kWhole96, kCut, kStream, kSplit, kGlu };
 GemmRoute gemm_route(const GemmArgs& g, int epi);
+const char* gemm_route_name(GemmRoute r);
 // Zero the arrival counters (a kernel, so it can sit in a captured stream).
 void launch_gemm_clear(int* tile_count, hipStream_t stream);
 void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream);

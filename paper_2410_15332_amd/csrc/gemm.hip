@@ -719,6 +719,20 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
   return GemmRoute::kCut;
 }
 
+const char* gemm_route_name(GemmRoute r) {
+  switch (r) {
+    case GemmRoute::kWhole256: return "whole256";
+    case GemmRoute::kWhole192: return "whole192";
+    case GemmRoute::kWhole128: return "whole128";
+    case GemmRoute::kWhole96: return "whole96";
+    case GemmRoute::kCut: return "cut";
+    case GemmRoute::kStream: return "stream";
+    case GemmRoute::kSplit: return "split";   // epic_gemm_route_name adds the tile height
+    case GemmRoute::kGlu: return "glu";
+  }
+  return "";
+}
+
 size_t gemm_partial_floats() { return size_t(2 * kMaxWorkers) * kPartialFloats; }
 
 int gemm_counters() { return kCounters; }

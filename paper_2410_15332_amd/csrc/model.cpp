@@ -284,6 +284,18 @@ extern "C" epic_status epic_link_model(const epic_model_cfg* cfg, const epic_lay
   return hip_ok("final norm launch");
 }
 
+// The kernel family a product of these sizes runs (epilogue: GemmEpilogue, kRope too), or
+// "" for sizes that are refused.  Host only and not in the public header: it is for tests,
+// each of which is about one family.
+extern "C" const char* epic_gemm_route_name(int32_t epilogue, int32_t m, int32_t n, int32_t k) {
+  if (epilogue < kStoreF32 || epilogue > kRope || m <= 0 || n <= 0 || k <= 0 || n % 128 != 0 || k % 64 != 0) return "";
+  GemmArgs g{};
+  g.M = m, g.N = n, g.K = k, g.ffn = epilogue == kSwiGLU ? n / 2 : 0;
+  const GemmRoute r = gemm_route(g, epilogue);
+  if (r == GemmRoute::kSplit) return wide_split(m, n, k).tm == 192 ? "split192" : "split256";
+  return gemm_route_name(r);
+}
+
 extern "C" size_t epic_gemm_workspace_bytes(void) { return gemm_workspace_bytes(); }
 
 extern "C" epic_status epic_gemm(int32_t epilogue, const uint16_t* a, const uint16_t* w, int32_t m, int32_t n,

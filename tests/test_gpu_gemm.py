@@ -1,16 +1,19 @@
 """GPU parity of the projection GEMM (epic_gemm) against the oracle's plain
 definitions (oracle.projection, float64 on the bf16 operands).
 
-Cases: the four projections of the 32-layer link step (736 rows: whole 192 x 256 and
-96 x 128 tiles, 256 x 128 tiles cut along K across workgroups), whole 192-row tiles with row
-and column tails, whole 96- and 128-row tiles with row tails, the same projections at a
-compile-sized row count (whole-tile rounds plus cut tiles; checked on sampled
-rows), row and column tails, tiny shapes, tiles cut into up to 56 parts, the
-fallback finish of cut tiles (bit-identical to the polled one), and m = 0.  Bars: fp32 outputs
-max |err| <= 1e-4 * s, s = sqrt(K) * sigma_a * sigma_w (the spread of an output;
-fp32 accumulation of bf16 products leaves ~1e-6 s); SwiGLU (bf16 output)
-|err| <= 2^-8 |ref| + 1e-4 s.
+Each case names the kernel family that runs it (the host's choice by sizes, checked
+before the call and, for all cases, without a GPU in test_gemm_routes.py): whole tiles of
+256 or 192 rows x 256 columns, the same in equal parts of K (split), one round of whole
+128- or 96-row x 128-column tiles, 256 x 128 tiles cut along K with arrival counters
+(polled and fallback finish, bit-identical), streamed weights in partial sums, and whole
+streamed gate|up tiles (glu).  Among them are the four projections of the 32-layer link
+step at 736 rows, compile-sized row counts (checked on sampled rows), row and column tails,
+tiny shapes, and m = 0.  Bars: fp32 outputs max |err| <= 1e-4 * s, s = sqrt(K) * sigma_a *
+sigma_w (the spread of an output; fp32 accumulation of bf16 products leaves ~1e-6 s);
+SwiGLU (bf16 output) |err| <= 2^-8 |ref| + 1e-4 s.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -33,9 +36,18 @@ def _f64(bits):
     return synth.bf16_bits_to_f32(bits).astype(np.float64)
 
 
-def _run(m, n, k, epi, tag, sample=None):
+def kernel_of(m, n, k, epi):
+    """The kernel family that the host chooses for these sizes."""
     from paper_2410_15332_amd import epic_link as el
-    print(f"[gpu-test] gemm m={m} n={n} k={k} {epi}", flush=True)
+    f = el._lib.epic_gemm_route_name
+    f.restype = ctypes.c_char_p
+    return f({**EPI, "rope": 3}[epi], m, n, k).decode()
+
+
+def _run(m, n, k, epi, kernel, tag, sample=None):
+    from paper_2410_15332_amd import epic_link as el
+    print(f"[gpu-test] gemm m={m} n={n} k={k} {epi} {kernel}", flush=True)
+    assert kernel_of(m, n, k, epi) == kernel
     sa, sw = 1.0, 1.0 / np.sqrt(k)
     a = synth.matrix_bf16(SEED, 3 * tag, (m, k), sa)
     w = synth.matrix_bf16(SEED, 3 * tag + 1, (n, k), sw)
@@ -71,105 +83,122 @@ def _run(m, n, k, epi, tag, sample=None):
 
 
 LINK = [  # the projections of the Llama-3-8B-shaped link step, 736 S rows
-    (736, 6144, 4096, "store"),
-    (736, 4096, 4096, "residual"),
-    (736, 28672, 4096, "swiglu"),
-    (736, 4096, 14336, "residual"),
+    (736, 6144, 4096, "store", "cut"),
+    (736, 4096, 4096, "residual", "whole96"),
+    (736, 28672, 4096, "swiglu", "whole192"),
+    (736, 4096, 14336, "residual", "split256"),
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", LINK, ids=[f"{c[3]}_{c[1]}x{c[2]}" for c in LINK])
-def test_link_step_projections(m, n, k, epi):
-    _run(m, n, k, epi, tag=LINK.index((m, n, k, epi)))
+def _ids(cases):
+    return [f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in cases]
+
+
+@pytest.mark.parametrize("m,n,k,epi,kernel", LINK, ids=_ids(LINK))
+def test_link_step_projections(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=LINK.index((m, n, k, epi, kernel)))
 
 
 BIG = [  # whole-tile rounds (compile-sized row counts), sampled rows
-    (4096, 28672, 4096, "swiglu"),
-    (4100, 4224, 1024, "residual"),     # row tail and a column tail inside a 256-wide tile
-    (20480, 6144, 4096, "store"),
+    (4096, 28672, 4096, "swiglu", "whole256"),
+    (4100, 4224, 1024, "residual", "whole192"),   # row tail and a column tail inside a 256-wide tile
+    (20480, 6144, 4096, "store", "whole256"),
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", BIG, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in BIG])
-def test_large_row_counts_sampled(m, n, k, epi):
+@pytest.mark.parametrize("m,n,k,epi,kernel", BIG, ids=_ids(BIG))
+def test_large_row_counts_sampled(m, n, k, epi, kernel):
     rng = np.random.default_rng(7)
     sample = sorted(set([0, 1, 255, 256, 257, m - 257, m - 256, m - 1] + rng.integers(0, m, 56).tolist()))
-    _run(m, n, k, epi, tag=10 + BIG.index((m, n, k, epi)), sample=sample)
+    _run(m, n, k, epi, kernel, tag=10 + BIG.index((m, n, k, epi, kernel)), sample=sample)
 
 
 TALL = [  # whole tiles of 192 x 256 (fewer rounds x rows than 256 x 256): row and column tails
-    (550, 32768, 256, "store"),         # 3 x 128 tiles in 2 rounds of 192; last row tile 166 rows
-    (600, 24448, 512, "residual"),      # 4 x 96 tiles, last row tile 24 rows, last tile 128 columns
+    (550, 32768, 256, "store", "whole192"),       # 3 x 128 tiles in 2 rounds of 192; last row tile 166 rows
+    (600, 24448, 512, "residual", "whole192"),    # 4 x 96 tiles, last row tile 24 rows, last tile 128 columns
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", TALL, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in TALL])
-def test_192_row_tiles(m, n, k, epi):
-    _run(m, n, k, epi, tag=60 + TALL.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", TALL, ids=_ids(TALL))
+def test_192_row_tiles(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=60 + TALL.index((m, n, k, epi, kernel)))
 
 
 WHOLE_NARROW = [  # one round of whole 96 x 128 or 128 x 128 tiles (short K): row tails (n % 128 == 0)
-    (760, 4096, 2048, "store"),         # 8 x 32 tiles of 96 rows, last row tile 88 rows
-    (700, 4096, 1024, "swiglu"),        # ffn 2048: 8 x 32 tiles of 96 x 64 outputs, last row tile 28 rows
-    (800, 4096, 2048, "store"),         # 9 x 32 tiles of 96 rows would be 288: 7 x 32 of 128, last 32 rows
-    (200, 14336, 1024, "swiglu"),       # ffn 7168: 2 x 112 tiles of 128 x 64 outputs, last row tile 72 rows
+    (760, 4096, 2048, "store", "whole96"),        # 8 x 32 tiles of 96 rows, last row tile 88 rows
+    (700, 4096, 1024, "swiglu", "whole96"),       # ffn 2048: 8 x 32 tiles of 96 x 64 outputs, last row tile 28 rows
+    (800, 4096, 2048, "store", "whole128"),       # 9 x 32 tiles of 96 rows would be 288: 7 x 32 of 128, last 32 rows
+    (200, 14336, 1024, "swiglu", "whole128"),     # ffn 7168: 2 x 112 tiles of 128 x 64 outputs, last row tile 72 rows
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", WHOLE_NARROW, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in WHOLE_NARROW])
-def test_whole_narrow_tiles(m, n, k, epi):
-    _run(m, n, k, epi, tag=70 + WHOLE_NARROW.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", WHOLE_NARROW, ids=_ids(WHOLE_NARROW))
+def test_whole_narrow_tiles(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=70 + WHOLE_NARROW.index((m, n, k, epi, kernel)))
 
 
 SMALL = [
-    (1, 128, 64, "store"),
-    (28, 384, 256, "residual"),
-    (200, 768, 512, "store"),
-    (255, 384, 640, "swiglu"),          # ffn = 192: 64-column SwiGLU tiles
-    (257, 1024, 512, "swiglu"),
-    (513, 640, 1536, "residual"),
+    (1, 128, 64, "store", "whole192"),            # one tile, one row, one K stage
+    (28, 384, 256, "residual", "stream"),
+    (200, 768, 512, "store", "stream"),
+    (255, 384, 640, "swiglu", "stream"),          # ffn = 192
+    (257, 1024, 512, "swiglu", "stream"),
+    (513, 640, 1536, "residual", "split192"),
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", SMALL, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in SMALL])
-def test_small_and_ragged(m, n, k, epi):
-    _run(m, n, k, epi, tag=20 + SMALL.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", SMALL, ids=_ids(SMALL))
+def test_small_and_ragged(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=20 + SMALL.index((m, n, k, epi, kernel)))
 
 
-MANY = [  # few tiles, long K: a tile cut into 16-56 parts (the last-stage owner waits for all)
-    (64, 128, 14336, "residual"),       # 1 tile, 224 K stages over 56 workgroups
-    (16, 256, 8192, "store"),           # 2 tiles, 32 parts each
-    (1, 128, 4096, "swiglu"),           # one row, one 64-column SwiGLU tile in 16 parts
-    (200, 384, 1024, "swiglu"),         # 3 tiles of 4 parts
+MANY = [  # streamed weights, few tiles and a long K: a tile's K stages over many workers, a plane each
+    (64, 128, 14336, "residual", "stream"),       # 2 tiles of 64 columns, 56 planes each
+    (16, 256, 8192, "store", "stream"),           # 4 tiles of 32 planes
+    (1, 128, 4096, "swiglu", "stream"),           # one row, 2 tiles of 16 planes
+    (200, 384, 1024, "swiglu", "stream"),         # two row tiles, 12 tiles of 4 planes
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", MANY, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in MANY])
-def test_tiles_cut_into_many_parts(m, n, k, epi):
-    _run(m, n, k, epi, tag=50 + MANY.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", MANY, ids=_ids(MANY))
+def test_tiles_over_many_workers(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=50 + MANY.index((m, n, k, epi, kernel)))
 
 
-CUT = [(736, 6144, 4096, "store"), (736, 4096, 14336, "residual"), (300, 1024, 512, "store"),
-       (64, 128, 14336, "residual")]
+CUT = [  # 256 x 128 tiles cut along K: few tiles (many parts each), less than a round, row and column tails
+    (736, 6144, 4096, "store", "cut"),            # 3 x 48 tiles, up to 3 parts
+    (736, 6144, 4096, "residual", "cut"),
+    (1100, 4096, 4096, "residual", "cut"),        # 5 x 32 tiles, last row tile 76 rows
+    (200, 28672, 4096, "swiglu", "cut"),          # 224 tiles of 64 gate|up columns, one of 200 rows
+    (256, 28672, 4096, "swiglu", "cut"),
+    (3000, 384, 14336, "store", "cut"),           # 36 tiles of 224 stages over 256 workgroups: 8 or 9 parts
+    (513, 128, 960, "swiglu", "cut"),             # ffn 64: 3 tiles of 15 stages over 11 workgroups
+    (100, 131200, 128, "swiglu", "cut"),          # 3 rounds whole, 257 of two stages in 256 shares; 128 rows at most
+]
 
 
-@pytest.mark.parametrize("m,n,k,epi", CUT, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in CUT])
-def test_cut_tile_fallback_matches_fast_path(m, n, k, epi, monkeypatch):
+@pytest.mark.parametrize("m,n,k,epi,kernel", CUT, ids=_ids(CUT))
+def test_cut_tile_fallback_matches_fast_path(m, n, k, epi, kernel, monkeypatch):
     """A cut tile's last-stage owner finishes from its registers once the other parts
     have arrived; with no polls allowed (EPIC_GEMM_FINISH_POLLS=0) it always falls back
     to writing its partial and letting the last to arrive finish.  Both paths sum the
     same partials in the same K order: bit-identical outputs, each within the bar."""
-    fast = _run(m, n, k, epi, tag=40 + CUT.index((m, n, k, epi)))
+    sample = None if m * n < 10000000 else sorted({0, 1, 63, 64, m // 2, m - 2, m - 1})
+    fast = _run(m, n, k, epi, kernel, tag=40 + CUT.index((m, n, k, epi, kernel)), sample=sample)
     monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", "0")
-    slow = _run(m, n, k, epi, tag=40 + CUT.index((m, n, k, epi)))
+    slow = _run(m, n, k, epi, kernel, tag=40 + CUT.index((m, n, k, epi, kernel)), sample=sample)
     assert np.array_equal(fast, slow)
 
 
+REUSE = [(736, 6144, 4096, "residual", "cut"), (300, 1024, 512, "store", "stream")]
+
+
 def test_repeated_calls_reuse_workspace():
-    """Back-to-back calls on one workspace: the split-tile counters are reset."""
+    """Back-to-back calls with tiles cut along K and with streamed partial sums.  Each call
+    has a workspace of its own, full of stale bytes: the counters are cleared by the call."""
     for _ in range(2):
-        _run(736, 6144, 4096, "residual", tag=30)     # 256 x 128 tiles cut along K
-        _run(300, 1024, 512, "store", tag=31)
+        for case in REUSE:
+            _run(*case, tag=30 + REUSE.index(case))
 
 
 def test_empty_and_rejected_shapes():
@@ -195,49 +224,51 @@ def test_empty_and_rejected_shapes():
     assert e.value.status == 4
 
 
-STREAM = [  # weight streaming (up to 512 rows, fewer 256 x 128 tiles than CUs): edges of its row tiles
-    (32, 640, 1024, "store"),           # one full 32-row tile, 10 column tiles
-    (33, 640, 1024, "residual"),        # 64-row tiles from here
-    (64, 384, 4160, "swiglu"),          # 65 K stages, a 64-column split of 192
-    (65, 4096, 1088, "store"),          # 128-row tiles, 64 columns wide
-    (128, 2048, 14336, "residual"),     # ... 128 columns wide (at least 16 stages per worker)
-    (129, 4096, 8192, "store"),         # two row tiles, the second with one row
-    (512, 1024, 4096, "swiglu"),        # most rows
-    (5, 128, 64, "swiglu"),             # one stage per tile
-    (513, 128, 14336, "residual"),      # one row more: tiles cut along K, 37 parts
+STREAM = [  # weight streaming (up to 512 rows, less than a round of wide tiles): edges of its row tiles
+    (32, 640, 1024, "store", "stream"),           # one full 32-row tile, 10 column tiles
+    (33, 640, 1024, "residual", "stream"),        # 64-row tiles from here
+    (64, 384, 4160, "swiglu", "stream"),          # 65 K stages
+    (65, 4096, 1088, "store", "stream"),          # 128-row tiles, 64 columns wide
+    (128, 2048, 14336, "residual", "stream"),     # ... 128 columns wide (at least 16 stages per worker)
+    (129, 4096, 8192, "store", "stream"),         # two row tiles, the second with one row
+    (512, 1024, 4096, "swiglu", "stream"),        # most rows
+    (5, 128, 64, "swiglu", "stream"),             # one stage per tile
+    (513, 128, 14336, "residual", "split192"),    # one row more: 3 wide tiles in 28 parts of K
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", STREAM, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in STREAM])
-def test_weight_streaming(m, n, k, epi):
-    _run(m, n, k, epi, tag=80 + STREAM.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", STREAM, ids=_ids(STREAM))
+def test_weight_streaming(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=80 + STREAM.index((m, n, k, epi, kernel)))
 
 
 WIDE = [  # whole 256-column tiles: one K stage, an odd number, several tiles per workgroup, tails
-    (2100, 8192, 64, "store"),          # 9 x 32 tiles of one stage each
-    (2100, 8320, 192, "residual"),      # 3 stages; the last column tile is 128 wide
-    (3000, 11520, 448, "swiglu"),       # 7 stages, ffn 5760
+    (2100, 8192, 64, "store", "whole192"),        # 11 x 32 tiles of one stage each
+    (2048, 8192, 64, "residual", "whole256"),     # 8 x 32 tiles of one stage, a round of 256
+    (2100, 8320, 192, "residual", "whole192"),    # 3 stages; the last column tile is 128 wide
+    (3000, 11520, 448, "swiglu", "whole192"),     # 7 stages, ffn 5760
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", WIDE, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in WIDE])
-def test_wide_tiles(m, n, k, epi):
+@pytest.mark.parametrize("m,n,k,epi,kernel", WIDE, ids=_ids(WIDE))
+def test_wide_tiles(m, n, k, epi, kernel):
     rng = np.random.default_rng(11)
     sample = sorted(set([0, 1, 127, 128, 191, 192, 255, 256, m - 2, m - 1] + rng.integers(0, m, 90).tolist()))
-    _run(m, n, k, epi, tag=100 + WIDE.index((m, n, k, epi)), sample=sample)
+    _run(m, n, k, epi, kernel, tag=100 + WIDE.index((m, n, k, epi, kernel)), sample=sample)
 
 
 SPLIT = [  # 256-wide tiles in equal parts of K, each an fp32 plane (few tiles, long K, over 128 rows)
-    (600, 512, 4096, "residual"),       # 3 x 2 tiles of 256 rows in 8 parts of 8 stages
-    (550, 640, 4160, "store"),          # 65 stages: parts of 8 and 9; the last column tile half past the end
-    (700, 1280, 4096, "swiglu"),        # gate and up summed by the SwiGLU pass
-    (370, 256, 14336, "residual"),      # two row tiles of 192, 28 parts
+    (600, 512, 4096, "residual", "split192"),     # 4 x 2 tiles of 192 rows in 8 parts of 8 stages
+    (550, 640, 4160, "store", "split192"),        # 65 stages: parts of 8 and 9; the last column tile half past the end
+    (700, 1280, 4096, "swiglu", "split192"),      # gate and up summed by the SwiGLU pass
+    (363, 4096, 14336, "store", "split192"),      # two row tiles, 8 parts of 28 stages
+    (700, 2048, 14336, "residual", "split256"),   # 3 x 8 tiles of 256 rows, 10 parts of 22 or 23 stages
 ]
 
 
-@pytest.mark.parametrize("m,n,k,epi", SPLIT, ids=[f"{c[3]}_{c[0]}x{c[1]}x{c[2]}" for c in SPLIT])
-def test_split_wide_tiles(m, n, k, epi):
-    _run(m, n, k, epi, tag=110 + SPLIT.index((m, n, k, epi)))
+@pytest.mark.parametrize("m,n,k,epi,kernel", SPLIT, ids=_ids(SPLIT))
+def test_split_wide_tiles(m, n, k, epi, kernel):
+    _run(m, n, k, epi, kernel, tag=110 + SPLIT.index((m, n, k, epi, kernel)))
 
 
 GLU = [  # up to 128 rows of gate|up in one round of whole 64 + 64-column tiles (192 to 256 of them)
@@ -252,4 +283,4 @@ GLU = [  # up to 128 rows of gate|up in one round of whole 64 + 64-column tiles 
 
 @pytest.mark.parametrize("m,n,k", GLU, ids=[f"{m}x{n}x{k}" for m, n, k in GLU])
 def test_whole_streamed_gate_up(m, n, k):
-    _run(m, n, k, "swiglu", tag=120 + GLU.index((m, n, k)))
+    _run(m, n, k, "swiglu", "glu", tag=120 + GLU.index((m, n, k)))

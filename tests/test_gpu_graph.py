@@ -53,13 +53,20 @@ def test_attention_step_graph_replays_split_kv():
     _replays(st, lambda: [st.out, st.lse], lambda: (st.out.zero_(), st.lse.zero_()))
 
 
-def test_model_step_graph_replays():
-    """Model level: the 128-row projections cut tiles along K, so this also replays the
-    GEMM's partial sums and arrival counters (cleared by a kernel each call)."""
+# 1000 rows of a 4608 x 1024 Q|K|V projection: 256 x 128 tiles cut along K
+CUT_MODEL = ModelWorkload("graph_cut", 43, 2, 1024, 1024, 24, 24, 64, 16, 500000.0, 1e-5, [37, 100], 1000, 0)
+SMALL_MODEL = ModelWorkload("graph_small", 41, 2, 512, 1024, 8, 2, 64, 16, 500000.0, 1e-5, [37, 100, 51], 23, 5)
+
+
+@pytest.mark.parametrize("wl,caches", [(SMALL_MODEL, "compile"), (CUT_MODEL, "synthetic")],
+                         ids=["streamed_sums", "cut_tiles"])
+def test_model_step_graph_replays(wl, caches):
+    """Model level: a few rows' projections stream their weights into partial sums, a
+    thousand rows' Q|K|V cuts tiles along K, so this also replays the GEMM's partial sums
+    and its arrival counters (cleared by a kernel each call)."""
     from paper_2410_15332_amd import harness
-    print("[gpu-test] graph: small model link step", flush=True)
-    wl = ModelWorkload("graph_small", 41, 2, 512, 1024, 8, 2, 64, 16, 500000.0, 1e-5, [37, 100, 51], 23, 5)
-    st = harness.stage_model(wl, caches="compile")
+    print(f"[gpu-test] graph: model link step {wl.name}", flush=True)
+    st = harness.stage_model(wl, caches=caches)
     _replays(st, lambda: [st.out, st.k_caches[1]], lambda: st.out.zero_())
 
 

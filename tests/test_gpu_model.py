@@ -356,3 +356,29 @@ def test_layers_alone_are_the_model_call(suffix):
     assert np.array_equal(h.cpu().numpy(), hidden)
     for a, b in zip(caches, st.k_caches + st.v_caches):
         assert np.array_equal(a, _bits(b))
+
+
+CUT_ROPE = [  # 1000 question rows of a 4608 x 1024 Q|K|V projection: 256 x 128 tiles cut along K
+    _small("cut_rope_d64", [40, 33], 1000, 0, hidden=1024, ffn=256, hq=24, hkv=24, d=64, layers=1),
+    _small("cut_rope_d128", [40, 33], 1000, 0, hidden=1024, ffn=256, hq=12, hkv=12, d=128, layers=1),
+]
+
+
+@pytest.mark.parametrize("wl", CUT_ROPE, ids=[w.name for w in CUT_ROPE])
+def test_rotary_epilogue_of_cut_tiles(wl, monkeypatch):
+    """The rotary epilogue after a cut tile's parts are summed, both by the owner of the
+    last part and (no polls allowed) by the last to arrive: the same bits."""
+    from test_gpu_gemm import kernel_of
+    n = (wl.num_q_heads + 2 * wl.num_kv_heads) * wl.head_dim
+    assert kernel_of(wl.suffix_len, n, wl.hidden, "rope") == "cut"
+    st = _stage(wl, caches="synthetic")
+    caches = [tuple([_f64(synth.chunk_cache(wl.seed, j, m, wl.num_kv_heads, wl.head_dim, 0.5, layer=0)[i])
+                     for j, m in enumerate(wl.chunk_lens)] for i in (0, 1))]
+    st.run()
+    _check(st, 1, caches)
+    polled = [st.out.cpu().numpy().copy(), _bits(st.k_caches[0]).copy(), _bits(st.v_caches[0]).copy()]
+    monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", "0")
+    st.run()
+    torch.cuda.synchronize()
+    for a, b in zip(polled, [st.out.cpu().numpy(), _bits(st.k_caches[0]), _bits(st.v_caches[0])]):
+        assert np.array_equal(a, b)
