@@ -791,8 +791,10 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   // split: pieces of at most `split` blocks, by the estimated launch as in split_blocks
   const int slots = std::max(1, kShapeTiny.slots / cfg->num_kv_heads);
   auto pieces = [](const Item& it, int split) { return cdiv(it.i1 - it.i0, split); };
-  int longest = 1, best = 1;
+  // (whole where even whole items make more rounds than balancing needs)
+  int longest = 16;
   for (const Item& it : whole) longest = std::max(longest, it.i1 - it.i0);
+  int best = longest;
   double best_time = 0.0;
   for (const int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
     const int split = std::max(16, cdiv(longest, parts));

@@ -604,6 +604,38 @@ def test_shared_decode_rule():
     assert kinds([el.Request([1024], [[64 * r + i for i in ids]], 20, 0) for r in range(4)], cfg) == {0}
 
 
+def _many_requests(n_req, chunks, tokens, pool, hq, hkv, d, split=0, suffix=20):
+    """Link plan of requests of random chunks, and what a decode plan of one token each needs."""
+    cfg = el.attn_cfg(hq, hkv, d, 0.0, split)
+    rng = np.random.default_rng(3)
+    nb = -(-tokens // 16)
+    ids = [list(range(c * nb, (c + 1) * nb)) for c in range(pool)]
+    reqs = [el.Request([tokens] * chunks, [ids[c] for c in rng.permutation(pool)[:chunks]], suffix, 0)
+            for _ in range(n_req)]
+    need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
+    used = pool * nb
+    total = used + need + 2 * n_req
+    sizes, buf, _ = el.epic_plan_link(reqs, cfg, list(range(used, used + need)), total)
+    return sizes, buf, [1] * n_req, cfg, list(range(used + need, total)), total
+
+
+def _shared_items(d):
+    work = d["work"].reshape(-1, 8)
+    return work[(work[:, 0] >= 0) & (work[:, 7] == 1)]
+
+
+def test_shared_decode_of_more_items_than_rounds_stays_whole():
+    """370 requests of one common chunk and 32 heads: 24 shared items and 370 of the requests'
+    own blocks are more than the 16 rounds up to which splits are tried, and their partials
+    fit the fixed scratch array only unsplit.  The items stay whole."""
+    need = _many_requests(370, 1, 1024, 1, 32, 32, 64)
+    sizes, _, d = el.epic_plan_decode(*need)
+    shared = _shared_items(d)
+    assert len(shared) == 24 and set((shared[:, 2] - shared[:, 1]).tolist()) == {64}
+    assert sizes.n_partials == 2 * 370
+    assert el.epic_link_workspace_bytes(need[3], sizes) <= el.NOALLOC_SCRATCH_BYTES
+
+
 def test_small_launches_split_below_64_blocks():
     """A split under 64 blocks only while every item has a CU (256) to itself; a short
     decode item stays whole (its combine would cost more than it gains)."""
