@@ -788,7 +788,11 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     for (int i = 0; i < static_cast<int>(lists[b].size()); i += kListMost)
       whole.push_back(Item{kItemList, -1, b, i, std::min<int>(i + kListMost, static_cast<int>(lists[b].size())), 1});
   }
-  // split: pieces of at most `split` blocks, by the estimated launch as in split_blocks
+  // a caller with the fixed scratch array must not lose a plan that fitted it: most partials
+  const int64_t max_parts = (int64_t(EPIC_NOALLOC_SCRATCH_BYTES) / ((cfg->head_dim + 1) * 4) - 64) /
+                            (int64_t(cfg->num_kv_heads) * kTileRowsTiny);
+  // split: pieces of at most `split` blocks, by the estimated launch as in split_blocks, among
+  // those whose partials fit
   const int slots = std::max(1, kShapeTiny.slots / cfg->num_kv_heads);
   auto pieces = [](const Item& it, int split) { return cdiv(it.i1 - it.i0, split); };
   // (whole where even whole items make more rounds than balancing needs)
@@ -799,6 +803,10 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   for (const int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
     const int split = std::max(16, cdiv(longest, parts));
     std::vector<double> cost;
+    int64_t n_parts = 0;
+    for (const Item& it : whole) n_parts += int64_t(pieces(it, split)) * it.parts;
+    if (n_parts > max_parts && parts == 1) return false;
+    if (n_parts > max_parts) break;
     for (const Item& it : whole)
       for (int p = pieces(it, split), k = 0; k < p; ++k)
         cost.push_back(cdiv(cdiv(it.i1 - it.i0, p), kKvTileBlocks) + kShapeTiny.item_overhead +
@@ -881,9 +889,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     out->work.insert(out->work.end(), wk, wk + kWorkInts);
   }
   out->work.insert(out->work.end(), ext.begin(), ext.end());
-  // a caller with the fixed scratch array must not lose a plan that fitted it
-  const int64_t bytes = (int64_t(part) * cfg->num_kv_heads * kTileRowsTiny + 64) * (cfg->head_dim + 1) * 4;
-  return bytes <= int64_t(EPIC_NOALLOC_SCRATCH_BYTES);
+  return true;
 }
 
 epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const int32_t* new_tokens,

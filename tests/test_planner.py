@@ -636,6 +636,20 @@ def test_shared_decode_of_more_items_than_rounds_stays_whole():
     assert el.epic_link_workspace_bytes(need[3], sizes) <= el.NOALLOC_SCRATCH_BYTES
 
 
+def test_shared_decode_split_by_the_scratch_limit():
+    """36 requests of eight chunks each from 16, 32 heads of 128: 324 partials with whole items,
+    where the fixed scratch array holds 380 and any split passes it.  Whole items are taken;
+    43 requests pass the array unsplit, and nothing is shared."""
+    need = _many_requests(36, 8, 2000, 16, 32, 32, 128)
+    sizes, _, d = el.epic_plan_decode(*need)
+    shared = _shared_items(d)
+    assert len(shared) > 0 and set((shared[:, 2] - shared[:, 1]).tolist()) == {125}
+    assert sizes.n_partials == 36 * 9
+    assert el.epic_link_workspace_bytes(need[3], sizes) <= el.NOALLOC_SCRATCH_BYTES
+    _, _, d = el.epic_plan_decode(*_many_requests(43, 8, 2000, 16, 32, 32, 128))
+    assert len(_shared_items(d)) == 0
+
+
 def test_small_launches_split_below_64_blocks():
     """A split under 64 blocks only while every item has a CU (256) to itself; a short
     decode item stays whole (its combine would cost more than it gains)."""
