@@ -188,16 +188,19 @@ constexpr TileShape kShapeTiny{kTileRowsTiny, 768, 1.0, 2.0, 1.0};      // three
 // KV heads, head-minor as in the grid) are dealt in launch order to the
 // workgroup slots, each to the slot that frees up first -- as the hardware
 // dispatcher does -- and an item costs its steps plus a fixed prologue /
-// epilogue charge.
+// epilogue charge.  An item's heads cost the same, so where the heads divide the slots
+// evenly the slots stay in groups of equal finish times, one per head, and one slot of
+// each group stands for it: the same times from a heap of slots / heads entries.
 double estimate_makespan(const std::vector<Tile>& tiles, int split, int hkv, const TileShape& sh) {
-  std::vector<double> slots(sh.slots, 0.0);   // min-heap of slot finish times
+  const int same = sh.slots % hkv == 0 ? hkv : 1;       // slots per group
+  std::vector<double> slots(sh.slots / same, 0.0);   // min-heap of slot finish times
   double makespan = 0.0;
   for (const auto& [t, seg] : item_order(tiles, split)) {
     const int blocks = std::min(tiles[t].nblk, (seg + 1) * split) - seg * split;
     const bool partial = tiles[t].nblk > split;
     const double cost = cdiv(std::max(blocks, 1), kKvTileBlocks) * sh.step_cost + sh.item_overhead +
                         (partial ? sh.partial_cost : 0.0);
-    for (int g = 0; g < hkv; ++g) {
+    for (int g = 0; g < hkv; g += same) {
       std::pop_heap(slots.begin(), slots.end(), std::greater<double>());
       slots.back() += cost;
       makespan = std::max(makespan, slots.back());
@@ -652,54 +655,85 @@ double makespan(std::vector<double> cost, int slots) {
 // Work items over shared blocks for 16-row tiles; false where sharing does not pay.
 // A block is shared if several requests link it with the same valid length, none twice,
 // and all of it precedes their new rows (so it needs no causal mask).
+// A plan is built for every token, so each refusal comes as soon as its reason is known
+// (requests x chunks x tokens, both planner calls: 400 x 8 x 256 of 3000 chunks, nothing to
+// save, 1.7 ms against 5.5 with the work list built first; 300 x 64 x 20 of 200 chunks, over
+// the partials' limit, 1.0 against 12).
 bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::vector<DecodeReq>& dr,
                    const epic_attn_cfg* cfg, SharedWork* out) {
   const int G = cfg->num_q_heads / cfg->num_kv_heads, R = kTileRowsTiny / G;
   const int batch = static_cast<int>(dr.size());
   if (R < 2) return false;
+  // not for requests of under 1024 tokens, whose items are too short to repay the combine
+  int64_t total = 0, n_rows = 0;
+  for (const DecodeReq& d : dr) {
+    if (d.t == 0) continue;
+    total += d.e - d.a + d.extra;
+    ++n_rows;
+  }
+  if (total < 64 * n_rows) return false;
+  // a caller with the fixed scratch array must not lose a plan that fitted it: most partials
+  const int64_t max_parts = (int64_t(EPIC_NOALLOC_SCRATCH_BYTES) / ((cfg->head_dim + 1) * 4) - 64) /
+                            (int64_t(cfg->num_kv_heads) * kTileRowsTiny);
   // entry of every linked block by its physical id: the id itself where the ids are about
-  // as many as the blocks (a plan of 32 requests over 32000 linked blocks 1.0 ms, hashed
-  // 1.4), else open addressing
+  // as many as the blocks, else open addressing
   struct Ref {
     uint64_t sig = 0;
-    int id = -1, count = 0, last = -1, len = 0, run = -1;   // run: the one that starts with this block
+    int count = 0, last = -1, len = 0, run = -1;            // run: the one that starts with this block
     bool bad = false;
   };
-  int max_id = 0;
-  for (int i = 0; i < ps->n_linked_blocks; ++i) max_id = std::max(max_id, prev->linked_blocks[i]);
-  const bool dense = max_id < 2 * int64_t(ps->n_linked_blocks);
-  size_t slots_n = 64;
-  while (!dense && slots_n < 2 * static_cast<size_t>(ps->n_linked_blocks)) slots_n *= 2;
-  if (dense) slots_n = static_cast<size_t>(max_id) + 1;
-  std::vector<Ref> ref(slots_n);
-  std::vector<int> entry(static_cast<size_t>(ps->n_linked_blocks));
+  int max_id = 0, min_id = 0;
   for (int i = 0; i < ps->n_linked_blocks; ++i) {
-    const int id = prev->linked_blocks[i];
-    if (id < 0) return false;                               // (rejected later)
-    size_t at = dense ? static_cast<size_t>(id) : (static_cast<uint32_t>(id) * 2654435761u) & (slots_n - 1);
-    while (ref[at].id >= 0 && ref[at].id != id) at = (at + 1) & (slots_n - 1);
-    ref[at].id = id;
-    entry[i] = static_cast<int>(at);
+    max_id = std::max(max_id, prev->linked_blocks[i]);
+    min_id = std::min(min_id, prev->linked_blocks[i]);
   }
-  int64_t total = 0;
+  if (min_id < 0) return false;                             // (rejected later)
+  const bool dense = max_id < 2 * int64_t(ps->n_linked_blocks);
+  std::vector<int> hashed;                                  // !dense: entries of the blocks
+  size_t slots_n = static_cast<size_t>(max_id) + 1;
+  if (!dense) {
+    slots_n = 64;
+    while (slots_n < 2 * static_cast<size_t>(ps->n_linked_blocks)) slots_n *= 2;
+    std::vector<int> ids(slots_n, -1);
+    hashed.resize(static_cast<size_t>(ps->n_linked_blocks));
+    for (int i = 0; i < ps->n_linked_blocks; ++i) {
+      const int id = prev->linked_blocks[i];
+      size_t at = (static_cast<uint32_t>(id) * 2654435761u) & (slots_n - 1);
+      while (ids[at] >= 0 && ids[at] != id) at = (at + 1) & (slots_n - 1);
+      ids[at] = id;
+      hashed[i] = static_cast<int>(at);
+    }
+  }
+  const int32_t* entry = dense ? prev->linked_blocks : hashed.data();
   auto frozen = [&](int b) { return dr[b].e - dr[b].a - (dr[b].room > 0 ? 1 : 0); };   // blocks that take no new row
+  // Not where fewer than a quarter of the block reads are saved: counted exactly below, here
+  // at most (R rows share a read; R divides 256, so the counts may wrap).
+  std::vector<uint8_t> count(slots_n, 0);
+  int64_t saved = 0;
   for (int b = 0; b < batch; ++b) {
     if (dr[b].t == 0) continue;
-    total += dr[b].e - dr[b].a + dr[b].extra;
-    const uint64_t h = (uint64_t(b) + 1) * 0x9E3779B97F4A7C15ull;
-    for (int i = 0; i < frozen(b); ++i) {
-      Ref& x = ref[entry[dr[b].a + i]];
-      const int len = prev->block_len[dr[b].a + i];
-      x.bad = x.bad || x.last == b || (x.count > 0 && x.len != len);
-      x.sig += (h ^ (h >> 29)) * 0xBF58476D1CE4E5B9ull;
+    const int32_t* at = entry + dr[b].a;
+    for (int i = 0, n = frozen(b); i < n; ++i) saved += (count[at[i]]++ & (R - 1)) != 0;
+  }
+  if ((total - saved) * 4 > total * 3) return false;
+  std::vector<Ref> ref(slots_n);
+  for (int b = 0; b < batch; ++b) {
+    if (dr[b].t == 0) continue;
+    uint64_t h = (uint64_t(b) + 1) * 0x9E3779B97F4A7C15ull;
+    h = (h ^ (h >> 29)) * 0xBF58476D1CE4E5B9ull;
+    const int32_t *at = entry + dr[b].a, *lens = prev->block_len + dr[b].a;
+    for (int i = 0, n = frozen(b); i < n; ++i) {
+      Ref& x = ref[at[i]];
+      x.bad = x.bad || x.last == b || (x.count > 0 && x.len != lens[i]);
+      x.sig += h;
       x.last = b;
-      x.len = len;
+      x.len = lens[i];
       ++x.count;
     }
   }
   auto sig_of = [&](int b, int i) {
     const Ref& x = ref[entry[dr[b].a + i]];
-    return x.count > 1 && !x.bad ? x.sig : 0;
+    return x.count > 1 && !x.bad ? x.sig : uint64_t(0);
   };
   // runs of blocks with the same set of requests; a run of one request is its own
   std::vector<SharedRun> runs;
@@ -708,13 +742,15 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     if (!own[b].empty() && own[b].back().second == i) own[b].back().second = i + n;
     else own[b].emplace_back(i, i + n);
   };
+  int64_t parts_least = n_rows;             // a partial per member of a run, and one of a request's own blocks
   for (int b = 0; b < batch; ++b) {
     if (dr[b].t == 0) continue;
     const int fz = frozen(b), nb = dr[b].e - dr[b].a + dr[b].extra;
+    uint64_t sig = 0 < fz ? sig_of(b, 0) : 0;
     for (int i = 0; i < nb;) {
-      const uint64_t sig = i < fz ? sig_of(b, i) : 0;
+      uint64_t next = 0;
       int j = i + 1;
-      while (j < nb && (j < fz ? sig_of(b, j) : 0) == sig) ++j;
+      while (j < nb && (next = j < fz ? sig_of(b, j) : 0) == sig) ++j;
       if (sig == 0) {
         add_own(b, i, j - i);
       } else {
@@ -723,49 +759,47 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
         if (r < 0) {
           r = static_cast<int>(runs.size());
           runs.push_back(SharedRun{b, i, j - i, {{b, i}}});
+          ++parts_least;
         } else if (runs[r].n == j - i &&
                    std::equal(ids, ids + (j - i), prev->linked_blocks + dr[runs[r].b].a + runs[r].i)) {
           runs[r].members.emplace_back(b, i);
+          ++parts_least;
         } else {
           add_own(b, i, j - i);                           // the same blocks in another order
         }
       }
       i = j;
+      sig = next;
     }
+    if (parts_least > max_parts) return false;
   }
   // groups of at most R rows over a run, about equal
   struct Group {
-    int run;
-    std::vector<std::pair<int, int>> members;
+    int run, m0, m1;                                       // members [m0, m1) of the run
   };
   std::vector<Group> groups;
   int64_t read = 0;
   for (size_t r = 0; r < runs.size(); ++r) {
+    const auto& members = runs[r].members;
     int rows = 0;
-    for (const auto& m : runs[r].members) rows += dr[m.first].t;
+    for (const auto& m : members) rows += dr[m.first].t;
     const int parts = cdiv(rows, R), each = cdiv(rows, parts);
-    Group g{static_cast<int>(r), {}};
-    int fill = 0;
-    for (const auto& m : runs[r].members) {
-      const int t = dr[m.first].t;
+    int fill = 0, m0 = 0;
+    for (int k = 0; k < static_cast<int>(members.size()); ++k) {
+      const int t = dr[members[k].first].t;
       if (fill > 0 && (fill + t > R || fill >= each)) {
-        groups.push_back(g);
-        g.members.clear();
+        groups.push_back(Group{static_cast<int>(r), m0, k});
+        m0 = k;
         fill = 0;
       }
-      g.members.push_back(m);
       fill += t;
     }
-    groups.push_back(g);
+    groups.push_back(Group{static_cast<int>(r), m0, static_cast<int>(members.size())});
   }
   for (const Group& g : groups) read += runs[g.run].n;
   for (const auto& o : own)
     for (const auto& x : o) read += x.second - x.first;
-  // Not where fewer than a quarter of the block reads are saved, nor for requests of
-  // under 1024 tokens, whose items are too short to repay the combine.
-  int64_t n_rows = 0;
-  for (const DecodeReq& d : dr) n_rows += d.t > 0;
-  if (read * 4 > total * 3 || total < 64 * n_rows) return false;
+  if (read * 4 > total * 3) return false;
   // Unshared blocks: ranges of at least kListBelow blocks as items of their own, the
   // rest of a request's listed together.
   constexpr int kListBelow = 48, kListMost = 96;
@@ -777,7 +811,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   std::vector<Item> whole;
   for (size_t k = 0; k < groups.size(); ++k) {
     const SharedRun& r = runs[groups[k].run];
-    whole.push_back(Item{kItemShared, static_cast<int>(k), r.b, r.i, r.i + r.n, static_cast<int>(groups[k].members.size())});
+    whole.push_back(Item{kItemShared, static_cast<int>(k), r.b, r.i, r.i + r.n, groups[k].m1 - groups[k].m0});
   }
   for (int b = 0; b < batch; ++b) {
     for (const auto& x : own[b]) {
@@ -788,30 +822,31 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     for (int i = 0; i < static_cast<int>(lists[b].size()); i += kListMost)
       whole.push_back(Item{kItemList, -1, b, i, std::min<int>(i + kListMost, static_cast<int>(lists[b].size())), 1});
   }
-  // a caller with the fixed scratch array must not lose a plan that fitted it: most partials
-  const int64_t max_parts = (int64_t(EPIC_NOALLOC_SCRATCH_BYTES) / ((cfg->head_dim + 1) * 4) - 64) /
-                            (int64_t(cfg->num_kv_heads) * kTileRowsTiny);
   // split: pieces of at most `split` blocks, by the estimated launch as in split_blocks, among
-  // those whose partials fit
+  // those whose partials fit; whole where even whole items make more rounds than balancing needs
   const int slots = std::max(1, kShapeTiny.slots / cfg->num_kv_heads);
   auto pieces = [](const Item& it, int split) { return cdiv(it.i1 - it.i0, split); };
-  // (whole where even whole items make more rounds than balancing needs)
   int longest = 16;
-  for (const Item& it : whole) longest = std::max(longest, it.i1 - it.i0);
+  int64_t whole_parts = 0;
+  for (const Item& it : whole) {
+    longest = std::max(longest, it.i1 - it.i0);
+    whole_parts += it.parts;
+  }
+  if (whole_parts > max_parts) return false;
   int best = longest;
   double best_time = 0.0;
+  std::vector<double> cost;
   for (const int parts : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64}) {
     const int split = std::max(16, cdiv(longest, parts));
-    std::vector<double> cost;
     int64_t n_parts = 0;
-    for (const Item& it : whole) n_parts += int64_t(pieces(it, split)) * it.parts;
-    if (n_parts > max_parts && parts == 1) return false;
-    if (n_parts > max_parts) break;
-    for (const Item& it : whole)
-      for (int p = pieces(it, split), k = 0; k < p; ++k)
-        cost.push_back(cdiv(cdiv(it.i1 - it.i0, p), kKvTileBlocks) + kShapeTiny.item_overhead +
-                       kShapeTiny.partial_cost * (it.kind == kItemShared ? 1 + 0.25 * it.parts : 1));
-    if (cost.size() > 16u * static_cast<size_t>(slots)) break;
+    cost.clear();
+    for (const Item& it : whole) {
+      const int p = pieces(it, split);
+      n_parts += int64_t(p) * it.parts;
+      cost.insert(cost.end(), p, cdiv(cdiv(it.i1 - it.i0, p), kKvTileBlocks) + kShapeTiny.item_overhead +
+                                     kShapeTiny.partial_cost * (it.kind == kItemShared ? 1 + 0.25 * it.parts : 1));
+    }
+    if (n_parts > max_parts || cost.size() > 16u * static_cast<size_t>(slots)) break;
     const double t = makespan(cost, slots);
     if (parts == 1 || t < best_time * 0.97) best_time = t, best = split;
     if (split == 16) break;
@@ -837,7 +872,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
   std::stable_sort(items.begin(), items.end(), [](const Item& x, const Item& y) { return x.i1 - x.i0 > y.i1 - y.i0; });
   for (const Item& it : items) {
     if (it.kind == kItemShared)
-      for (const auto& m : groups[it.group].members) ++n_part[m.first];
+      for (int k = groups[it.group].m0; k < groups[it.group].m1; ++k) ++n_part[runs[groups[it.group].run].members[k].first];
     else
       ++n_part[it.b];
   }
@@ -868,7 +903,8 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     int32_t wk[kWorkInts] = {tile_of[it.b], base[it.b] + it.i0, base[it.b] + it.i1, -1, 0, 0, 0, it.kind};
     std::vector<int32_t> list;
     if (it.kind == kItemShared) {
-      for (const auto& m : groups[it.group].members) {
+      for (int k = groups[it.group].m0; k < groups[it.group].m1; ++k) {
+        const auto& m = runs[groups[it.group].run].members[k];
         const int p = take(m.first);
         for (int t = 0; t < dr[m.first].t; ++t) {
           list.push_back(row0[m.first] + t);
@@ -910,7 +946,6 @@ epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const
   std::sort(written.begin(), written.end());
   std::vector<DecodeReq>& dr = *dr_out;
   dr.assign(static_cast<size_t>(batch), DecodeReq{});
-  std::vector<ReqRows> rr(static_cast<size_t>(batch));
   int64_t n_s = 0, n_lb = 0, n_priv = 0, n_take = 0, max_pos = 0;
   for (int b = 0; b < batch; ++b) {
     DecodeReq& d = dr[b];
@@ -919,7 +954,6 @@ epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const
     EPIC_CHECK_ARG(0 <= d.a && d.a <= d.e && d.e <= ps->n_linked_blocks, "previous plan: bad blk_off at %d", b);
     d.t = new_tokens[b];
     EPIC_CHECK_ARG(d.t >= 0, "request %d: %d new tokens", b, d.t);
-    for (int i = d.a; i < d.e; ++i) rr[b].p0.push_back(prev->block_pos0[i]);
     if (d.e > d.a) {
       const int last = d.e - 1, len = prev->block_len[last];
       d.n = int64_t(prev->block_pos0[last]) + len;
@@ -928,8 +962,6 @@ epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const
     }
     d.extra = cdiv(d.t - d.room, kBlock);
     EPIC_CHECK_ARG(d.n + d.t < (int64_t(1) << 30), "request %d: too many tokens", b);
-    for (int i = 0; i < d.extra; ++i) rr[b].p0.push_back(static_cast<int32_t>(d.n + d.room + int64_t(i) * kBlock));
-    for (int i = 0; i < d.t; ++i) rr[b].pos.push_back(static_cast<int32_t>(d.n + i));
     n_s += d.t;
     n_lb += (d.e - d.a) + d.extra;
     n_priv += (d.room > 0 ? 1 : 0) + d.extra;
@@ -955,7 +987,14 @@ epic_status decode_shape(const epic_plan_sizes* ps, const epic_plan* prev, const
     s.n_work = static_cast<int32_t>(shared->work.size()) / kWorkInts;
     s.n_partials = shared->n_partials;
   } else {
-    shared->work.clear();
+    std::vector<ReqRows> rr(static_cast<size_t>(batch));
+    for (int b = 0; b < batch; ++b) {
+      const DecodeReq& d = dr[b];
+      rr[b].p0.reserve(static_cast<size_t>(d.e - d.a) + d.extra);
+      rr[b].p0.assign(prev->block_pos0 + d.a, prev->block_pos0 + d.e);
+      for (int i = 0; i < d.extra; ++i) rr[b].p0.push_back(static_cast<int32_t>(d.n + d.room + int64_t(i) * kBlock));
+      for (int i = 0; i < d.t; ++i) rr[b].pos.push_back(static_cast<int32_t>(d.n + i));
+    }
     choose_tiles(rr, cfg, &s, tiles_out, split_out);
   }
   s.n_s = static_cast<int32_t>(n_s);
