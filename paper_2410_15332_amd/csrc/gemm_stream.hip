@@ -35,6 +35,7 @@ namespace epic {
 namespace {
 
 constexpr int kBK = 64;
+constexpr int kWorkers = 256;                           // one workgroup per CU
 constexpr int kMinUnits = 4;                            // K stages per worker, at least
 constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
 
@@ -71,15 +72,13 @@ __device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcp
 // memory channels, so the workers have to be at different stages.  K = 4096, ffn 14336:
 // 32 rows 52.4 us in partial sums, 53.1 in whole tiles that start alike, 44.8 so (235 MB
 // at 5.2 TB/s); 128 rows 55.7, 55.7 and 51.4.
-template <int TM, int TN, int NW, int CT, int NS, int OCC, bool GLU = false>
-__global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g) {
+template <int TM, int TN, int NW, int CT, int NS, bool GLU = false>
+__global__ __launch_bounds__(NW * 64, 1) void gemm_stream_kernel(StreamArgs g) {
   constexpr int NG = (TM + TN) / 8;                    // 1 KB row groups per stage
   constexpr int NL = NG / NW;                           // ... per wavefront
   static_assert(NG % NW == 0, "row groups per wavefront");
-  constexpr int NT = (TM / 32) * (TN / 32 / CT);       // wavefront tiles of 32 rows x 32 CT columns
-  constexpr int KH = NW / NT;                           // wavefronts that share one, by k-slices
-  static_assert(KH * NT == NW && 4 % KH == 0, "wavefronts per tile");
-  static_assert(!GLU || (KH == 1 && CT == 2), "a wavefront holds the gate and up of its columns");
+  static_assert((TM / 32) * (TN / 32 / CT) == NW, "a wavefront per 32 rows x 32 CT columns");
+  static_assert(!GLU || CT == 2, "a wavefront holds the gate and up of its columns");
   constexpr int SB = (TM + TN) * 128;                  // bytes per stage
   __shared__ __attribute__((aligned(1024))) char lds[NS][SB];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -128,10 +127,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
     }
   };
 
-  // ---- compute: wavefront -> tile (rt, ct) and its share of the stage's four k-slices
-  const int mt_ = wv % NT, kh = wv / NT;
-  constexpr int WC = TN / 32 / CT;                      // wavefront tiles along N
-  const int rt = mt_ / WC, ct = mt_ % WC * (GLU ? 1 : CT);
+  // ---- compute: wavefront -> row block rt, first column block ct
+  constexpr int WC = TN / 32 / CT;                      // wavefronts along N
+  const int rt = wv / WC, ct = wv % WC * (GLU ? 1 : CT);
   constexpr int CS = GLU ? WC : 1;                      // 32-column blocks between a wavefront's CT
   const int lbase = (lane & 31) * 128, lsw = (lane >> 1) & 7, half = lane >> 5;
   const int abase = rt * 4096 + lbase, bbase = (TM / 32 + ct) * 4096 + lbase;
@@ -146,7 +144,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
     for (int j = 0; j < CT; ++j) acc[j] = f32x16{};
     // the k-slices of unit u are read while unit u - 1 is on the matrix cores
     struct Frags {
-      bf16x8 a[4 / KH], b[4 / KH][CT];
+      bf16x8 a[4], b[4][CT];
     } f0, f1;
     auto fetch = [&](Frags& f) __attribute__((always_inline)) {
       stream_wait<(NS - 2) * NL>();                     // this wavefront's loads of unit u
@@ -154,8 +152,8 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
       dma_next(buf == 0 ? NS - 1 : buf - 1);            // unit u + NS - 1, where u - 1 was
       const char* p = lds[buf];
 #pragma unroll
-      for (int i = 0; i < 4 / KH; ++i) {
-        const int c = ((2 * (kh * (4 / KH) + i) + half) ^ lsw) * 16;
+      for (int i = 0; i < 4; ++i) {
+        const int c = ((2 * i + half) ^ lsw) * 16;
         f.a[i] = *reinterpret_cast<const bf16x8*>(p + abase + c);
 #pragma unroll
         for (int j = 0; j < CT; ++j) f.b[i][j] = *reinterpret_cast<const bf16x8*>(p + bbase + j * CS * 4096 + c);
@@ -165,7 +163,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
     };
     auto mma = [&](const Frags& f) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < 4 / KH; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < CT; ++j) acc[j] = mfma_32x32x16(f.a[i], f.b[i][j], acc[j]);
       __builtin_amdgcn_sched_barrier(0);
@@ -185,7 +183,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
     } else {
       mma(f0);
     }
-    // this worker's part of the tile: plane (worker - first worker of the tile) * KH + kh
+    // this worker's part of the tile: plane (worker - first worker of the tile)
     const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
     const int m0 = mt * TM + rt * 32 + half * 4;
     if constexpr (GLU) {
@@ -199,7 +197,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void gemm_stream_kernel(StreamArgs g)
       ++tile;
       continue;
     }
-    const int plane = (wr - g.s.owner(tile * ks)) * KH + kh;
+    const int plane = wr - g.s.owner(tile * ks);
     const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
         g.partial + size_t(plane) * g.M * g.N, 0, g.M * g.N * 4, kBufWord3);   // rows past M: dropped
     const int n = nt * TN + ct * 32 + (lane & 31);
@@ -333,16 +331,15 @@ __global__ __launch_bounds__(2 * D) void stream_rope_write_kernel(StreamSum s, G
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-StreamSum make_sum(int M, int N, int K, int TM, int TN, int workers, int kh, const float* partial) {
+StreamSum make_sum(int M, int N, int K, int TM, int TN, const float* partial) {
   StreamSum s{};
   s.partial = partial;
   s.M = M, s.N = N;
   s.tm = TM, s.tn = TN;
   s.m_tiles = cdiv(M, TM);
   s.ks = K / kBK;
-  s.kh = kh;
   s.units = s.m_tiles * (N / TN) * s.ks;
-  s.G = s.units < workers * kMinUnits ? cdiv(s.units, kMinUnits) : workers;
+  s.G = s.units < kWorkers * kMinUnits ? cdiv(s.units, kMinUnits) : kWorkers;
   return s;
 }
 
@@ -352,38 +349,39 @@ StreamSum make_sum(int M, int N, int K, int TM, int TN, int workers, int kh, con
 // 8 stages per worker: 18.1 -> 19.9).
 constexpr int kWideUnits = 16;
 bool wide_tiles(int M, int N, int K) {
-  return int64_t(cdiv(M, 128)) * (N / 128) * (K / kBK) >= int64_t(kWideUnits) * 256;
+  return int64_t(cdiv(M, 128)) * (N / 128) * (K / kBK) >= int64_t(kWideUnits) * kWorkers;
 }
 
-template <int TM, int TN, int NW, int CT, int NS, int OCC>
+template <int TM, int TN, int NW, int CT, int NS>
 StreamSum launch_tm(const GemmArgs& g, hipStream_t stream) {
   StreamArgs a{};
   a.A = g.A, a.W = g.W, a.partial = g.partial, a.M = g.M, a.N = g.N, a.K = g.K;
-  a.s = make_sum(g.M, g.N, g.K, TM, TN, 256 * OCC, NW / (TM / 32 * (TN / 32) / CT), g.partial);
-  gemm_stream_kernel<TM, TN, NW, CT, NS, OCC><<<a.s.G, NW * 64, 0, stream>>>(a);
+  a.s = make_sum(g.M, g.N, g.K, TM, TN, g.partial);
+  gemm_stream_kernel<TM, TN, NW, CT, NS><<<a.s.G, NW * 64, 0, stream>>>(a);
   return a.s;
 }
 
 }  // namespace
 
-// planes of a tile: at most ceil(ks / stages per worker) + 1 workers, two wavefronts each
+// Planes of a tile: at most ceil(ks / stages per worker) + 1 workers.  They have half of the
+// workspace: products whose planes need more were not measured here.
 bool stream_fits(int M, int N, int K) {
   const int tm = M <= 32 ? 32 : M <= 64 ? 64 : 128;
   const int64_t units = int64_t(cdiv(M, tm)) * (N / 64) * (K / kBK);
   if (units >= (1 << 23)) return false;                 // 32-bit arithmetic of StreamSum::owner
-  const int64_t per = std::max<int64_t>(units / 2 / 256, 1);   // of either tile width
+  const int64_t per = std::max<int64_t>(units / 2 / kWorkers, 1);   // of either tile width
   const int64_t planes = (K / kBK + per - 1) / per + 1;
   return 2 * planes * M * N <= int64_t(gemm_partial_floats());
 }
 
 StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream) {
-  // Wavefronts: as few as cover the tile, so a 32- or 64-row stage costs few barriers and
-  // LDS reads (W_down of 32 rows: 2 wavefronts 29.2 us, 4 sharing k-slices 32.7; of 64
-  // rows: 4 wavefronts 31.8, 8 33.0).
-  if (g.M <= 32) return launch_tm<32, 64, 2, 1, 12, 1>(g, stream);
-  if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9, 1>(g, stream);
-  if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4, 1>(g, stream);
-  return launch_tm<128, 64, 8, 1, 6, 1>(g, stream);
+  // One wavefront per 32 rows x 32 or 64 columns, so a 32- or 64-row stage costs few barriers
+  // and LDS reads (W_down of 32 rows: 2 wavefronts 29.2 us, 4 that share the k-slices of a
+  // stage 32.7; of 64 rows: 4 wavefronts 31.8, 8 33.0).
+  if (g.M <= 32) return launch_tm<32, 64, 2, 1, 12>(g, stream);
+  if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9>(g, stream);
+  if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4>(g, stream);
+  return launch_tm<128, 64, 8, 1, 6>(g, stream);
 }
 
 // Gate|up of up to 128 rows where its 64 + 64-column tiles make one round that fills at
@@ -397,11 +395,11 @@ template <int TM, int NW, int NS>
 static void launch_glu(const GemmArgs& g, hipStream_t stream) {
   StreamArgs a{};
   a.A = g.A, a.W = g.W, a.M = g.M, a.N = g.N, a.K = g.K, a.act = g.act, a.ffn = g.ffn;
-  a.s.M = g.M, a.s.N = g.N, a.s.tm = TM, a.s.tn = 128, a.s.m_tiles = 1, a.s.kh = 1;
+  a.s.M = g.M, a.s.N = g.N, a.s.tm = TM, a.s.tn = 128, a.s.m_tiles = 1;
   a.s.ks = g.K / kBK;
   a.s.G = g.ffn / 64;
   a.s.units = a.s.G * a.s.ks;
-  gemm_stream_kernel<TM, 128, NW, 2, NS, 1, true><<<a.s.G, NW * 64, 0, stream>>>(a);
+  gemm_stream_kernel<TM, 128, NW, 2, NS, true><<<a.s.G, NW * 64, 0, stream>>>(a);
 }
 
 void launch_gemm_glu(const GemmArgs& g, hipStream_t stream) {

@@ -1,6 +1,6 @@
 // The result of a weight-streaming GEMM before its consumer: fp32 partial sums of C in
-// planes [M][N], dealt as gemm_stream.hip describes.  A tile (TM rows x 64 columns) has
-// (last worker - first worker + 1) * kh planes, worker-major, i.e. in K order.
+// planes [M][N], dealt as gemm_stream.hip describes.  A tile (tm rows x tn columns) has
+// last worker - first worker + 1 planes, in K order.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -13,7 +13,6 @@ struct StreamSum {
   const float* partial;
   int M, N;
   int tm, tn, m_tiles, ks;   // rows and columns per tile, row tiles, K stages per tile (tile t = column tile * m_tiles + row tile)
-  int kh;                // wavefronts of a workgroup that share an MFMA tile by k-slices: a plane each
   int units, G;          // K stages over all tiles, workers; units * G < 2^31
   int fixed;             // planes of every tile, where that is one number (the fields above are then unused)
 
@@ -22,7 +21,7 @@ struct StreamSum {
   __host__ __device__ int owner(int v) const {
     return int((uint32_t(v + 1) * uint32_t(G) + uint32_t(units) - 1) / uint32_t(units)) - 1;
   }
-  __host__ __device__ int planes(int tile) const { return (owner((tile + 1) * ks - 1) - owner(tile * ks) + 1) * kh; }
+  __host__ __device__ int planes(int tile) const { return owner((tile + 1) * ks - 1) - owner(tile * ks) + 1; }
 
   // columns n .. n + 3 of row m (n % 4 == 0), the planes added in K order; four planes'
   // loads in flight at a time, the ones past the last repeating it and adding 0
