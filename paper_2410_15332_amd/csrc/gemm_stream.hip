@@ -10,6 +10,13 @@
 //     planes in K order (stream_sum.h): no counters, no waiting on another workgroup,
 //     and the sum is fused into the pass that reads C anyway (residual + RMSNorm,
 //     SwiGLU, rotary embedding);
+//   - a stage's four k-slices add to accumulators of their own (two of them where the 64
+//     columns of a wavefront leave no registers for four), added up at the end of a part:
+//     a chain of additions then has a quarter of the length, and its error grows with the
+//     square root of that.  Relative error against float64 with one chain -> now (256-row
+//     tiles cut along K, which these kernels replaced): 500 rows, N 3072, K 2048 2.0e-7 ->
+//     1.05e-7 (1.14e-7); 64 rows, 16384, 2048 2.7e-7 -> 1.3e-7 (1.9e-7); 256 rows, 4096, 14336
+//     3.7e-7 -> 2.6e-7 (2.6e-7).  It costs 0.2 to 0.5 us of 10 to 20;
 //   - LDS is a ring of NS stages, loads issued NS - 1 stages ahead of their use (144 KB
 //     in flight per CU), and a wavefront reads a stage's fragments while the previous
 //     stage is on the matrix cores.
@@ -72,8 +79,10 @@ __device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcp
 // memory channels, so the workers have to be at different stages.  K = 4096, ffn 14336:
 // 32 rows 52.4 us in partial sums, 53.1 in whole tiles that start alike, 44.8 so (235 MB
 // at 5.2 TB/s); 128 rows 55.7, 55.7 and 51.4.
-template <int TM, int TN, int NW, int CT, int NS, bool GLU = false>
-__global__ __launch_bounds__(NW * 64, 1) void gemm_stream_kernel(StreamArgs g) {
+// All bounds say 512 threads: for fewer, the compiler has more than 256 registers, puts the
+// accumulators into AGPRs and moves them there and back for every part (0.4 us more).
+template <int TM, int TN, int NW, int CT, int NS, int NA, bool GLU = false>
+__global__ __launch_bounds__(512, 1) void gemm_stream_kernel(StreamArgs g) {
   constexpr int NG = (TM + TN) / 8;                    // 1 KB row groups per stage
   constexpr int NL = NG / NW;                           // ... per wavefront
   static_assert(NG % NW == 0, "row groups per wavefront");
@@ -139,9 +148,11 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_stream_kernel(StreamArgs g) {
   int buf = 0, u = u0, tile = u0 / ks;
   while (u < u1) {
     const int ue = min(u1, (tile + 1) * ks);
-    f32x16 acc[CT];
+    f32x16 sums[NA][CT];                                // k-slice i of a stage adds to sums[i % NA]
 #pragma unroll
-    for (int j = 0; j < CT; ++j) acc[j] = f32x16{};
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < CT; ++j) sums[i][j] = f32x16{};
     // the k-slices of unit u are read while unit u - 1 is on the matrix cores
     struct Frags {
       bf16x8 a[4], b[4][CT];
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_stream_kernel(StreamArgs g) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < CT; ++j) acc[j] = mfma_32x32x16(f.a[i], f.b[i][j], acc[j]);
+        for (int j = 0; j < CT; ++j) sums[i % NA][j] = mfma_32x32x16(f.a[i], f.b[i][j], sums[i % NA][j]);
       __builtin_amdgcn_sched_barrier(0);
     };
     fetch(f0);
@@ -182,6 +193,13 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_stream_kernel(StreamArgs g) {
       mma(f1);
     } else {
       mma(f0);
+    }
+    f32x16 acc[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) {
+      acc[j] = sums[0][j];
+      if constexpr (NA == 2) acc[j] += sums[1][j];
+      if constexpr (NA == 4) acc[j] = (acc[j] + sums[1][j]) + (sums[2][j] + sums[3][j]);
     }
     // this worker's part of the tile: plane (worker - first worker of the tile)
     const int nt = tile / m_tiles, mt = tile - nt * m_tiles;
@@ -352,12 +370,12 @@ bool wide_tiles(int M, int N, int K) {
   return int64_t(cdiv(M, 128)) * (N / 128) * (K / kBK) >= int64_t(kWideUnits) * kWorkers;
 }
 
-template <int TM, int TN, int NW, int CT, int NS>
+template <int TM, int TN, int NW, int CT, int NS, int NA>
 StreamSum launch_tm(const GemmArgs& g, hipStream_t stream) {
   StreamArgs a{};
   a.A = g.A, a.W = g.W, a.partial = g.partial, a.M = g.M, a.N = g.N, a.K = g.K;
   a.s = make_sum(g.M, g.N, g.K, TM, TN, g.partial);
-  gemm_stream_kernel<TM, TN, NW, CT, NS><<<a.s.G, NW * 64, 0, stream>>>(a);
+  gemm_stream_kernel<TM, TN, NW, CT, NS, NA><<<a.s.G, NW * 64, 0, stream>>>(a);
   return a.s;
 }
 
@@ -378,10 +396,10 @@ StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream) {
   // One wavefront per 32 rows x 32 or 64 columns, so a 32- or 64-row stage costs few barriers
   // and LDS reads (W_down of 32 rows: 2 wavefronts 29.2 us, 4 that share the k-slices of a
   // stage 32.7; of 64 rows: 4 wavefronts 31.8, 8 33.0).
-  if (g.M <= 32) return launch_tm<32, 64, 2, 1, 12>(g, stream);
-  if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9>(g, stream);
-  if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4>(g, stream);
-  return launch_tm<128, 64, 8, 1, 6>(g, stream);
+  if (g.M <= 32) return launch_tm<32, 64, 2, 1, 12, 4>(g, stream);
+  if (g.M <= 64) return launch_tm<64, 64, 4, 1, 9, 4>(g, stream);
+  if (wide_tiles(g.M, g.N, g.K)) return launch_tm<128, 128, 8, 2, 4, 2>(g, stream);
+  return launch_tm<128, 64, 8, 1, 6, 4>(g, stream);
 }
 
 // Gate|up of up to 128 rows where its 64 + 64-column tiles make one round that fills at
@@ -399,7 +417,7 @@ static void launch_glu(const GemmArgs& g, hipStream_t stream) {
   a.s.ks = g.K / kBK;
   a.s.G = g.ffn / 64;
   a.s.units = a.s.G * a.s.ks;
-  gemm_stream_kernel<TM, 128, NW, 2, NS, true><<<a.s.G, NW * 64, 0, stream>>>(a);
+  gemm_stream_kernel<TM, 128, NW, 2, NS, 1, true><<<a.s.G, NW * 64, 0, stream>>>(a);
 }
 
 void launch_gemm_glu(const GemmArgs& g, hipStream_t stream) {

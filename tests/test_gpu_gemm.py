@@ -242,6 +242,37 @@ def test_weight_streaming(m, n, k, epi, kernel):
     _run(m, n, k, epi, kernel, tag=80 + STREAM.index((m, n, k, epi, kernel)))
 
 
+CHAINS = [  # streamed products and the longest chain of matrix instructions of a part (planes per tile)
+    (500, 3072, 2048, 24, 3),           # 6144 stages over 256 workers, a chain for each of a stage's four k-slices
+    (64, 16384, 2048, 32, 1),           # 8192 stages: a tile each
+    (64, 4096, 14336, 56, 5),           # 14336 stages
+    (256, 4096, 14336, 112, 5),         # 128-column tiles: two chains
+]
+
+
+@pytest.mark.parametrize("m,n,k,chain,planes", CHAINS, ids=[f"{c[0]}x{c[1]}x{c[2]}" for c in CHAINS])
+def test_streamed_sums_keep_their_precision(m, n, k, chain, planes):
+    """Relative 2-norm error of fp32 sums against float64.  Rounding a sum to nearest costs
+    r = 2^-23 / sqrt(12) sqrt(0.541) of it (rms, mantissas log-uniform), and a matrix
+    instruction rounds its running sum twice; of independent terms the sum after j of L
+    instructions has j / L of the final variance.  So chains of at most c instructions
+    leave r^2 c, the addition of a part's chains at most r^2, and p planes r^2 p / 2."""
+    from paper_2410_15332_amd import epic_link as el
+    assert kernel_of(m, n, k, "store") == "stream"
+    gen = torch.Generator(device="cuda").manual_seed(n + m)
+    a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    c = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    el.epic_gemm(el.GEMM_STORE, a, w, c=c,
+                 workspace=torch.empty(el.epic_gemm_workspace_bytes(), dtype=torch.uint8, device="cuda"))
+    ref = a.double() @ w.double().t().contiguous()
+    err = float((c.double() - ref).norm() / ref.norm())
+    r = 2.0 ** -23 / np.sqrt(12) * np.sqrt(0.541)
+    bound = r * np.sqrt(chain + 1 + planes / 2)
+    print(f"[gpu-test] {m}x{n}x{k}: error {err:.3e}, bound {bound:.3e}", flush=True)
+    assert err <= bound
+
+
 WIDE = [  # whole 256-column tiles: one K stage, an odd number, several tiles per workgroup, tails
     (2100, 8192, 64, "store", "whole192"),        # 11 x 32 tiles of one stage each
     (2048, 8192, 64, "residual", "whole256"),     # 8 x 32 tiles of one stage, a round of 256
