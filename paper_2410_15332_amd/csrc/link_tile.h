@@ -11,7 +11,7 @@ namespace epic {
 template <int D>
 struct VTile {
   static constexpr int LD = 18;
-  uint16_t e[D * LD];
+  alignas(4) uint16_t e[D * LD];               // read and written four bytes at a time too
 
   // thread tid (of 2 D) moves dim tid / 2, slots 8 (tid % 2) .. + 7
   __device__ __forceinline__ void load(const uint16_t* slab, int tid) {
