@@ -42,11 +42,13 @@ int gemm_counters();          // arrival counters at tile_count
 // leave partial sums and a pass that adds them up.  kGlu: one round of whole streamed
 // gate|up tiles.
 enum class GemmRoute { kWhole256, kWhole192, kWhole128, kWhole96, kCut, kStream, kSplit, kGlu };
-GemmRoute gemm_route(const GemmArgs& g, int epi);
+// in_layer: the pass that sums partials also does what another launch would (a norm, the
+// link write).
+GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer);
 const char* gemm_route_name(GemmRoute r);
 // Zero the arrival counters (a kernel, so it can sit in a captured stream).
 void launch_gemm_clear(int* tile_count, hipStream_t stream);
-void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream);
+void launch_gemm(const GemmArgs& g, int epi, GemmRoute r, hipStream_t stream);
 void launch_gemm_wide(const GemmArgs& g, int epi, int tm, hipStream_t stream);
 
 }  // namespace epic

@@ -650,7 +650,7 @@ void launch_epi(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
 
 }  // namespace
 
-GemmRoute gemm_route(const GemmArgs& g, int epi) {
+GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer) {
   // At least a round of 256 x 256 tiles: whole tiles only (measured: cutting tiles
   // along K costs about one tile time in partial traffic, more than a short last
   // round).  The tiles are 256 or 192 rows high, whichever takes less time: a round
@@ -683,34 +683,43 @@ GemmRoute gemm_route(const GemmArgs& g, int epi) {
     if (one_round(t96)) return GemmRoute::kWhole96;
     if (one_round(t128)) return GemmRoute::kWhole128;
   }
-  // Else the least estimated time (us), each line fitted to epic_gemm on one box; w: MB
-  // of weights, u: K stages per workgroup.  Measured examples (K x N, rows: us):
-  //   streamed weights  4096 x 4096, 128: 15.6, 448: 29.7; 14336 x 4096, 128: 34, 384: 75, 512: 86
-  //   whole wide tiles  4096 x 28672, 300: 87.6 (cut 115), 512: 103 (139); 4096 x 6144, 1500: 70 (88);
-  //                     8192 x 4096, 2600: 155 (246); 8192 x 57344, 100: 192 (217)
-  //   split wide tiles  14336 x 4096, 363: 57 (streamed 75), 736: 97 (cut 120), 2000: 206 (249);
-  //                     8192 x 2048, 600: 42 (53); 4096 x 28672, 192: 74 (99)
-  //   cut tiles         4096 x 4096, 1472: 61-66 (split 66-69), 2000: 73-80 (split 80-83)
+  // Else the least estimated time (us).  The estimates are fitted to every route at 1486
+  // sizes (N 1024-32768, K 512-14336, 1-7000 rows; relative deviation 4-8%), of which they
+  // take routes 0.5% (geometric mean) behind the best one, and 27% ahead of cutting always.
+  // w: MB of weights, u: K stages per workgroup.  Measured examples (K x N, rows: us):
+  //   streamed weights  4096 x 4096, 128: 15.6, 384: 29; 14336 x 4096, 128: 31, 384: 53
+  //   whole wide tiles  4096 x 28672, 300: 87 (cut 115), 512: 115 (150); 4096 x 6144, 1500: 68 (84)
+  //   split wide tiles  14336 x 4096, 363: 57 (streamed 75), 736: 92 (cut 110), 2000: 206 (249);
+  //                     8192 x 2048, 600: 42 (53)
+  //   cut tiles         4096 x 4096, 1472: 61-66 (split 66-69); 14336 x 16384, 64: 90 (streamed 114)
+  //   ... a whole number of rounds of them, none cut: 2048 x 16384, 300: 37 (whole wide tiles 40),
+  //                     4096 x 8192, 769: 64 (split 71), 2048 x 32768, 129: 40 (53)
   // In a layer the pass that sums partials replaces a norm or a link write (bonus).
   constexpr double kNever = 1e30;
-  const double bonus = epi == kResidual ? 5.0 : epi == kRope ? 10.0 : 0.0;
+  const double bonus = !in_layer ? 0.0 : epi == kResidual ? 5.0 : epi == kRope ? 10.0 : 0.0;
   const double w = double(g.K) * g.N * 2e-6, plane = double(g.M) * g.N * 4e-6;
   const int64_t ks = g.K / kBK;
-  const int t128r = cdiv(g.M, 128);
+  const double per_mb = g.M <= 32 ? 0.12 : g.M <= 64 ? 0.14 : g.M <= 128 ? 0.155 : g.M <= 256 ? 0.27 : g.M <= 384 ? 0.52 : 0.66;
   const double stream = g.M <= kStreamRows && stream_fits(g.M, g.N, g.K)
-                            ? 12.0 + w * (t128r <= 1 ? 0.2 : t128r == 2 ? 0.32 : t128r == 3 ? 0.5 : 0.6) +
-                                  std::max(plane - 8.0, 0.0) * 0.4 - bonus
+                            ? 9.0 + w * per_mb + 0.08 * std::max(w - 100.0, 0.0) + 0.38 * plane - bonus
                             : kNever;
   const WideSplit sp = wide_split(g.M, g.N, g.K);
-  const double split = sp.parts >= 2 ? sp.time + 4.0 + sp.parts * plane / 5.0 - bonus : kNever;
+  const double split = sp.parts >= 2 ? wide_split_time(sp, g.M, g.N, g.K) + 0.24 * sp.parts * plane - bonus : kNever;
   auto whole = [&](int tm) {                            // one round; a stage takes longer the more CUs run
     const int64_t tiles = int64_t(cdiv(g.M, tm)) * n256;
     if (n256 == 0 || tiles > kMaxWorkers) return kNever;
-    return 10.0 + ks * (tm == 256 ? 0.85 + 0.65 * tiles / kMaxWorkers : 0.7 + 0.55 * tiles / kMaxWorkers);
+    const double t = double(tiles) / kMaxWorkers;
+    return 5.8 + ks * (tm == 256 ? 0.90 + 0.44 * t : 0.69 + 0.37 * t) + 0.05 * w + 0.067 * plane;
   };
   const double whole256 = whole(256), whole192 = whole(192);
+  // A stage of a 256 x 128 tile: less where wavefronts have no rows (64 each) if that holds
+  // for a whole round; a stage of one row tile's waits for weights that no other tile shares.
   const int64_t cut_tiles = int64_t(m_tiles) * n128;
-  const double cut = 10.0 + 1.06 * double(cut_tiles * ks) / kMaxWorkers + 2.5 * kMaxWorkers / double(cut_tiles);
+  const double live = double(cdiv(g.M, 64) * 64) / (m_tiles * kTM);
+  const bool rounds = cut_tiles % kMaxWorkers == 0;     // whole rounds: nothing is cut
+  const double stage = m_tiles == 1 ? (0.61 + 0.45 * live) * (rounds || kMaxWorkers % cut_tiles == 0 ? 1.0 : 1.12)
+                                    : rounds ? 0.46 + 0.54 * live : 1.11;
+  const double cut = 10.2 + stage * double(cut_tiles * ks) / kMaxWorkers + (rounds ? 0.0 : 2.5 * kMaxWorkers / double(cut_tiles));
   const double best = std::min({stream, split, whole256, whole192, cut});
   if (best == stream) return GemmRoute::kStream;
   if (best == split) return GemmRoute::kSplit;
@@ -748,9 +757,8 @@ void launch_gemm_clear(int* tile_count, hipStream_t stream) {
   gemm_clear_kernel<<<1, 256, 0, stream>>>(tile_count);
 }
 
-void launch_gemm(const GemmArgs& g, int epi, hipStream_t stream) {
+void launch_gemm(const GemmArgs& g, int epi, GemmRoute r, hipStream_t stream) {
   if (g.M == 0) return;
-  const GemmRoute r = gemm_route(g, epi);
   if (is_partial(r))
     launch_stream_finish(launch_gemm_partial(g, r, stream), g, epi, stream);
   else if (r == GemmRoute::kGlu)

@@ -382,11 +382,20 @@ void launch_wide_tm(const GemmArgs& g, hipStream_t stream) {
 
 }  // namespace
 
+// A stage takes longer with 256 rows than with 192, and the more CUs run; and what of the
+// weights does not come from the L2 in time.
+double wide_split_time(const WideSplit& s, int M, int N, int K) {
+  const double w = double(K) * N * 2e-6, t = double(cdiv(M, s.tm)) * cdiv(N, kTN) * s.parts / kMaxWorkers;
+  return 9.4 + cdiv(K / kBK, s.parts) * ((s.tm == 256 ? 1.14 : 0.78) + 0.36 * t) + 0.02 * w +
+         0.045 * std::max(w - 120.0, 0.0);
+}
+
 // Equal parts of K per tile, a workgroup each, in one round; at least eight stages a part,
-// planes within the workspace.  Time: a stage takes about 1.5 us with 256 rows, 1.25 with
-// 192.  Up to 128 rows the tiles would mostly be padding.
+// planes within the workspace.  The height by the time of the stages alone, 1.5 us with 256
+// rows and 1.25 with 192.  Up to 128 rows the tiles would mostly be padding.
 WideSplit wide_split(int M, int N, int K) {
   WideSplit best{};
+  double best_time = 0.0;
   if (M <= 128) return best;
   for (const int tm : {256, 192}) {
     const int64_t tiles = int64_t(cdiv(M, tm)) * cdiv(N, kTN);
@@ -394,8 +403,8 @@ WideSplit wide_split(int M, int N, int K) {
     const int64_t fit = int64_t(gemm_partial_floats()) / (int64_t(M) * N);
     const int parts = int(std::min({kMaxWorkers / tiles, int64_t(K / kBK / 8), fit}));
     if (parts < 2) continue;
-    const double time = 14.0 + cdiv(K / kBK, parts) * (tm == 256 ? 1.5 : 1.25);
-    if (best.parts == 0 || time < best.time) best = WideSplit{tm, parts, time};
+    const double time = cdiv(K / kBK, parts) * (tm == 256 ? 1.5 : 1.25);
+    if (best.parts == 0 || time < best_time) best = WideSplit{tm, parts}, best_time = time;
   }
   return best;
 }

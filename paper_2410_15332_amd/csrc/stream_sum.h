@@ -50,12 +50,12 @@ struct StreamSum {
 // Enqueue the partial sums of g's product (g.partial: the GEMM workspace); returns how to sum them.
 StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream);
 // The same with 192- or 256-row tiles of 256 columns, each cut into equal parts of K
-// (gemm_wide.hip); parts = 0 where that gives fewer than two.  time: estimate in us.
+// (gemm_wide.hip); parts = 0 where that gives fewer than two.
 struct WideSplit {
   int tm, parts;
-  double time;
 };
 WideSplit wide_split(int M, int N, int K);
+double wide_split_time(const WideSplit& s, int M, int N, int K);   // estimate in us, without the planes
 StreamSum launch_gemm_wide_split(const GemmArgs& g, hipStream_t stream);
 // The partial sums of a route that leaves them to the consumer.
 inline bool is_partial(GemmRoute r) { return r == GemmRoute::kStream || r == GemmRoute::kSplit; }

@@ -24,9 +24,24 @@ def test_whole_gate_up_cases():
 def test_layer_cases_with_cut_tiles():
     import test_gpu_graph as graph
     import test_gpu_model as model
-    for wl in model.CUT_ROPE + [graph.CUT_MODEL]:
-        n = (wl.num_q_heads + 2 * wl.num_kv_heads) * wl.head_dim
-        assert gemm.kernel_of(wl.suffix_len, n, wl.hidden, "rope") == "cut"
+    for hq, hkv, d in model.CUT_ROPE:
+        assert gemm.kernel_of(64, (hq + 2 * hkv) * d, 14336, "rope", True) == "cut"
+    wl = graph.CUT_MODEL
+    assert gemm.kernel_of(wl.suffix_len, 2 * wl.ffn, wl.hidden, "swiglu", True) == "cut"
+
+
+# (m, n, k, epilogue), how much longer the route before took than cut tiles: where they make
+# whole rounds, so that nothing is cut, and where few rows meet heavy weights
+FASTER_CUT = [
+    (257, 16384, 2048, "swiglu", 1.13), (320, 16384, 2048, "store", 1.09), (448, 16384, 4096, "swiglu", 1.13),
+    (769, 8192, 4096, "residual", 1.13),
+    (256, 32768, 4096, "store", 1.21), (64, 16384, 14336, "store", 1.26),
+]
+
+
+@pytest.mark.parametrize("m,n,k,epi,_", FASTER_CUT)
+def test_cut_tiles_where_they_were_measured_faster(m, n, k, epi, _):
+    assert gemm.kernel_of(m, n, k, epi) == "cut"
 
 
 def test_refused_sizes_have_no_kernel():

@@ -36,12 +36,12 @@ def _f64(bits):
     return synth.bf16_bits_to_f32(bits).astype(np.float64)
 
 
-def kernel_of(m, n, k, epi):
-    """The kernel family that the host chooses for these sizes."""
+def kernel_of(m, n, k, epi, in_layer=False):
+    """The kernel family that the host chooses for these sizes, alone or in a decoder layer."""
     from paper_2410_15332_amd import epic_link as el
     f = el._lib.epic_gemm_route_name
     f.restype = ctypes.c_char_p
-    return f({**EPI, "rope": 3}[epi], m, n, k).decode()
+    return f({**EPI, "rope": 3}[epi], m, n, k, in_layer).decode()
 
 
 def _run(m, n, k, epi, kernel, tag, sample=None):
@@ -139,7 +139,7 @@ def test_whole_narrow_tiles(m, n, k, epi, kernel):
 
 SMALL = [
     (1, 128, 64, "store", "whole192"),            # one tile, one row, one K stage
-    (28, 384, 256, "residual", "stream"),
+    (28, 384, 256, "residual", "whole192"),       # two tiles, the second half past the end
     (200, 768, 512, "store", "stream"),
     (255, 384, 640, "swiglu", "stream"),          # ffn = 192
     (257, 1024, 512, "swiglu", "stream"),
@@ -165,15 +165,16 @@ def test_tiles_over_many_workers(m, n, k, epi, kernel):
     _run(m, n, k, epi, kernel, tag=50 + MANY.index((m, n, k, epi, kernel)))
 
 
-CUT = [  # 256 x 128 tiles cut along K: few tiles (many parts each), less than a round, row and column tails
+CUT = [  # 256 x 128 tiles cut along K: less than a round, few tiles, row tails; and whole rounds, none cut
     (736, 6144, 4096, "store", "cut"),            # 3 x 48 tiles, up to 3 parts
     (736, 6144, 4096, "residual", "cut"),
-    (1100, 4096, 4096, "residual", "cut"),        # 5 x 32 tiles, last row tile 76 rows
-    (200, 28672, 4096, "swiglu", "cut"),          # 224 tiles of 64 gate|up columns, one of 200 rows
+    (1700, 1280, 4096, "residual", "cut"),        # 7 x 10 tiles, last row tile 164 rows, up to 5 parts
+    (200, 20480, 1536, "swiglu", "cut"),          # 160 tiles of 64 gate|up columns, one of 200 rows
     (256, 28672, 4096, "swiglu", "cut"),
-    (3000, 384, 14336, "store", "cut"),           # 36 tiles of 224 stages over 256 workgroups: 8 or 9 parts
+    (6000, 384, 3072, "store", "cut"),            # 24 x 3 tiles, 4 or 5 parts
     (513, 128, 960, "swiglu", "cut"),             # ffn 64: 3 tiles of 15 stages over 11 workgroups
     (100, 131200, 128, "swiglu", "cut"),          # 3 rounds whole, 257 of two stages in 256 shares; 128 rows at most
+    (300, 16384, 2048, "store", "cut"),           # 2 x 128 tiles: one round, nothing cut
 ]
 
 
@@ -188,6 +189,28 @@ def test_cut_tile_fallback_matches_fast_path(m, n, k, epi, kernel, monkeypatch):
     monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", "0")
     slow = _run(m, n, k, epi, kernel, tag=40 + CUT.index((m, n, k, epi, kernel)), sample=sample)
     assert np.array_equal(fast, slow)
+
+
+def test_tiles_cut_into_many_parts(monkeypatch):
+    """36 tiles of 224 K stages over 256 workgroups: 8 or 9 parts a tile, polled and by the
+    last to arrive.  Same bar as the other cases, against float64 on the device."""
+    from paper_2410_15332_amd import epic_link as el
+    m, n, k = 9000, 128, 14336
+    print(f"[gpu-test] gemm m={m} n={n} k={k} store cut", flush=True)
+    assert kernel_of(m, n, k, "store") == "cut"
+    gen = torch.Generator(device="cuda").manual_seed(SEED)
+    a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(0.0, k ** -0.5, generator=gen)
+    ws = torch.full((el.epic_gemm_workspace_bytes(),), 0xAB, dtype=torch.uint8, device="cuda")
+    out = []
+    for polls in (None, "0"):
+        if polls is not None:
+            monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", polls)
+        out.append(torch.full((m, n), float("nan"), device="cuda"))
+        el.epic_gemm(el.GEMM_STORE, a, w, c=out[-1], workspace=ws)
+    err = (out[0].double() - a.double() @ w.double().t().contiguous()).abs().max()
+    assert float(err) <= 1e-4
+    assert torch.equal(out[0], out[1])
 
 
 REUSE = [(736, 6144, 4096, "residual", "cut"), (300, 1024, 512, "store", "stream")]

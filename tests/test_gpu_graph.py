@@ -53,8 +53,8 @@ def test_attention_step_graph_replays_split_kv():
     _replays(st, lambda: [st.out, st.lse], lambda: (st.out.zero_(), st.lse.zero_()))
 
 
-# 1000 rows of a 4608 x 1024 Q|K|V projection: 256 x 128 tiles cut along K
-CUT_MODEL = ModelWorkload("graph_cut", 43, 2, 1024, 1024, 24, 24, 64, 16, 500000.0, 1e-5, [37, 100], 1000, 0)
+# 200 rows of a 20480 x 1536 gate|up: 160 tiles of 256 rows x 64 + 64 columns, cut along K
+CUT_MODEL = ModelWorkload("graph_cut", 43, 2, 1536, 10240, 8, 4, 64, 16, 500000.0, 1e-5, [37, 100], 200, 0)
 SMALL_MODEL = ModelWorkload("graph_small", 41, 2, 512, 1024, 8, 2, 64, 16, 500000.0, 1e-5, [37, 100, 51], 23, 5)
 
 
@@ -62,7 +62,7 @@ SMALL_MODEL = ModelWorkload("graph_small", 41, 2, 512, 1024, 8, 2, 64, 16, 50000
                          ids=["streamed_sums", "cut_tiles"])
 def test_model_step_graph_replays(wl, caches):
     """Model level: a few rows' projections stream their weights into partial sums, a
-    thousand rows' Q|K|V cuts tiles along K, so this also replays the GEMM's partial sums
+    couple of hundred rows' gate|up cuts tiles along K, so this also replays the GEMM's partial sums
     and its arrival counters (cleared by a kernel each call)."""
     from paper_2410_15332_amd import harness
     print(f"[gpu-test] graph: model link step {wl.name}", flush=True)

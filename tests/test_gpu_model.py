@@ -358,27 +358,57 @@ def test_layers_alone_are_the_model_call(suffix):
         assert np.array_equal(a, _bits(b))
 
 
-CUT_ROPE = [  # 1000 question rows of a 4608 x 1024 Q|K|V projection: 256 x 128 tiles cut along K
-    _small("cut_rope_d64", [40, 33], 1000, 0, hidden=1024, ffn=256, hq=24, hkv=24, d=64, layers=1),
-    _small("cut_rope_d128", [40, 33], 1000, 0, hidden=1024, ffn=256, hq=12, hkv=12, d=128, layers=1),
-]
+# 64 rows of a 28672 x 14336 Q|K|V: the sizes at which a layer cuts the tiles of that projection
+CUT_ROPE = [(112, 56, 128), (224, 112, 64)]
 
 
-@pytest.mark.parametrize("wl", CUT_ROPE, ids=[w.name for w in CUT_ROPE])
-def test_rotary_epilogue_of_cut_tiles(wl, monkeypatch):
+@pytest.mark.parametrize("hq,hkv,d", CUT_ROPE)
+def test_rotary_epilogue_of_cut_tiles(hq, hkv, d, monkeypatch):
     """The rotary epilogue after a cut tile's parts are summed, both by the owner of the
-    last part and (no polls allowed) by the last to arrive: the same bits."""
+    last part and (no polls allowed) by the last to arrive: the same bits in the caches and
+    in the residual stream, and k and v against float64 as in
+    test_decode_layer_writes_into_the_linked_cache (14336 terms a sum)."""
+    from paper_2410_15332_amd import epic_link as el
     from test_gpu_gemm import kernel_of
-    n = (wl.num_q_heads + 2 * wl.num_kv_heads) * wl.head_dim
-    assert kernel_of(wl.suffix_len, n, wl.hidden, "rope") == "cut"
-    st = _stage(wl, caches="synthetic")
-    caches = [tuple([_f64(synth.chunk_cache(wl.seed, j, m, wl.num_kv_heads, wl.head_dim, 0.5, layer=0)[i])
-                     for j, m in enumerate(wl.chunk_lens)] for i in (0, 1))]
-    st.run()
-    _check(st, 1, caches)
-    polled = [st.out.cpu().numpy().copy(), _bits(st.k_caches[0]).copy(), _bits(st.v_caches[0]).copy()]
-    monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", "0")
-    st.run()
-    torch.cuda.synchronize()
-    for a, b in zip(polled, [st.out.cpu().numpy(), _bits(st.k_caches[0]), _bits(st.v_caches[0])]):
-        assert np.array_equal(a, b)
+    rows, hidden, ffn, theta, eps = 64, 14336, 128, 500000.0, 1e-5
+    n = (hq + 2 * hkv) * d
+    print(f"[gpu-test] rotary epilogue of cut tiles, {hq}/{hkv} heads of {d}", flush=True)
+    assert kernel_of(rows, n, hidden, "rope", True) == "cut"
+    cfg = el.attn_cfg(hq, hkv, d, rope_theta=theta)
+    sizes, host, v = el.epic_plan_link([el.Request([], [], rows, 0)], cfg, [0, 1, 2, 3], 4)
+    mcfg = el.epic_model_cfg(cfg, hidden, ffn, 1, theta, eps)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+
+    def lin(out, inp):
+        return torch.empty((out, inp), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.5 * inp ** -0.5, generator=gen)
+
+    norm = torch.ones(hidden, dtype=torch.bfloat16, device="cuda")
+    w = [norm, lin(n, hidden), lin(hidden, hq * d), norm, lin(2 * ffn, hidden), lin(hidden, ffn)]
+    layer = el.epic_layer_weights(*(t.data_ptr() for t in w))
+    emb = torch.randn(rows, hidden, generator=torch.Generator().manual_seed(5)).cuda()
+    ws = torch.empty(el.epic_model_workspace_bytes(mcfg, sizes), dtype=torch.uint8, device="cuda")
+    plan, got = el.DevicePlan(sizes, host), []
+    for polls in (None, "0"):
+        if polls is not None:
+            monkeypatch.setenv("EPIC_GEMM_FINISH_POLLS", polls)
+        kc = torch.zeros((4, hkv, 16, d), dtype=torch.bfloat16, device="cuda")
+        vc = torch.zeros((4, hkv, d, 16), dtype=torch.bfloat16, device="cuda")
+        h = emb.clone()
+        el.epic_link_layer(mcfg, layer, plan, h, kc, vc, ws)
+        torch.cuda.synchronize()
+        got.append((h, kc, vc))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    x = emb.double()
+    x = x * torch.rsqrt(x.square().mean(-1, keepdim=True) + eps)
+    kv = (x @ w[1][hq * d:].double().t().contiguous()).view(rows, 2 * hkv, d)
+    k, vv = kv[:, :hkv], kv[:, hkv:]
+    pos = torch.arange(rows, dtype=torch.float64, device="cuda")
+    ang = pos[:, None] * theta ** (-torch.arange(d // 2, dtype=torch.float64, device="cuda") / (d // 2))
+    c, s = ang.cos()[:, None], ang.sin()[:, None]
+    a, b = k[..., :d // 2], k[..., d // 2:]
+    k = torch.cat((a * c - b * s, b * c + a * s), -1)
+    blocks, slots = v["s_slot"] // 16, v["s_slot"] % 16
+    for out, ref in ((got[0][1][blocks, :, slots], k), (got[0][2][blocks, :, :, slots], vv)):
+        err = (out.double() - ref).abs()
+        assert bool((err <= 2.0 ** -8 * ref.abs() + 2.0 ** -7 * ref.pow(2).mean().sqrt()).all()), err.max()
