@@ -55,6 +55,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "gemm_device.h"
 #include "stream_sum.h"
 
 namespace epic {
@@ -63,7 +64,6 @@ namespace {
 
 constexpr int kTM = 256, kBK = 64;
 constexpr int kThreads = 512;
-constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
 constexpr int kMaxWorkers = 256;                        // one workgroup per CU
 constexpr int kPartialFloats = kTM * 256;               // per partial slot (twice a 256 x 128 tile)
 constexpr int kMaxSplitTiles = 2 * kMaxWorkers;
@@ -104,28 +104,6 @@ struct GemmLds {
   char a[Shape<TM>::NS][Shape<TM>::A_STAGE];
   char b[Shape<TM>::NS][Shape<TM>::B_STAGE];
 };
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-// One 16-byte-per-lane buffer->LDS load (1 KB per wavefront: lane l's 16 bytes land
-// at dst + 16 l).  A plain function, so the call is never a template-dependent
-// expression (the host pass cannot check this builtin inside a template).
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rs, char* dst, int voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, soff, 0, 0);
-}
-
-// Workgroup barrier ordering LDS accesses only (waits for this wavefront's LDS
-// reads, not for its buffer->LDS loads still in flight).
-__device__ __forceinline__ void barrier_lds() {
-  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-// At most N of this wavefront's vector memory operations outstanding (they
-// complete in issue order); gfx9 encoding: vmcnt bits [3:0] and [15:14].
-template <int N>
-__device__ __forceinline__ void wait_vmem() {
-  static_assert(N >= 0 && N < 64, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
-}
 
 // Position in a workgroup's sequence of K stages: tile, stage, and the stage range
 // [kbeg, kend) of the current segment (the part of the tile this workgroup owns).

@@ -34,6 +34,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "gemm_device.h"
 #include "link_tile.h"
 #include "stream_sum.h"
 
@@ -44,22 +45,6 @@ namespace {
 constexpr int kBK = 64;
 constexpr int kWorkers = 256;                           // one workgroup per CU
 constexpr int kMinUnits = 4;                            // K stages per worker, at least
-constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-__device__ __forceinline__ void stream_dma16(__amdgpu_buffer_rsrc_t rs, char* dst, int voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, soff, 0, 0);
-}
-// workgroup barrier ordering LDS accesses only (buffer->LDS loads stay in flight)
-__device__ __forceinline__ void stream_barrier() {
-  __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-template <int N>
-__device__ __forceinline__ void stream_wait() {
-  static_assert(N >= 0 && N < 64, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
-}
 
 struct StreamArgs {
   const uint16_t* A;
@@ -126,7 +111,7 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(StreamArgs g) {
   if (GLU) dkt = wr % ks;
   auto dma_next = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) stream_dma16(rs[i], lds[buf] + (wv * NL + i) * 1024, vo[i], dkt * (kBK * 2));
+    for (int i = 0; i < NL; ++i) dma16(rs[i], lds[buf] + (wv * NL + i) * 1024, vo[i], dkt * (kBK * 2));
     if (du + 1 < u1) {                                  // past the last unit: that one again
       ++du;
       if (++dkt == ks) {
@@ -158,8 +143,8 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(StreamArgs g) {
       bf16x8 a[4], b[4][CT];
     } f0, f1;
     auto fetch = [&](Frags& f) __attribute__((always_inline)) {
-      stream_wait<(NS - 2) * NL>();                     // this wavefront's loads of unit u
-      stream_barrier();                                 // everyone's; and unit u - 1 is read
+      wait_vmem<(NS - 2) * NL>();                     // this wavefront's loads of unit u
+      barrier_lds();                                 // everyone's; and unit u - 1 is read
       dma_next(buf == 0 ? NS - 1 : buf - 1);            // unit u + NS - 1, where u - 1 was
       const char* p = lds[buf];
 #pragma unroll
@@ -229,7 +214,7 @@ __global__ __launch_bounds__(512, 1) void gemm_stream_kernel(StreamArgs g) {
       }
     ++tile;
   }
-  stream_wait<0>();                                     // no load may land in LDS after the workgroup ends
+  wait_vmem<0>();                                     // no load may land in LDS after the workgroup ends
 }
 
 // C = sum of the planes, stored (kStoreF32) or added (kResidual): four columns per thread.

@@ -39,6 +39,7 @@
 
 #include "device_common.h"
 #include "gemm.h"
+#include "gemm_device.h"
 #include "stream_sum.h"
 
 namespace epic {
@@ -46,21 +47,7 @@ namespace epic {
 namespace {
 
 constexpr int kBK = 64, kTN = 256;
-constexpr int kBufWord3 = 0x00020000;                   // gfx9 raw buffer descriptor word 3
 constexpr int kMaxWorkers = 256;
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-__device__ __forceinline__ void wide_dma16(__amdgpu_buffer_rsrc_t rs, char* dst, int voff, int soff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)dst, 16, voff, soff, 0, 0);
-}
-
-// at most N of this wavefront's vector memory operations outstanding
-template <int N>
-__device__ __forceinline__ void wide_wait() {
-  static_assert(N >= 0 && N < 64, "vmcnt field");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
-}
 
 struct WidePlan {
   int m_tiles, n_tiles, tiles;
@@ -158,11 +145,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
     return true;
   };
   auto dma_a = [&](int i) __attribute__((always_inline)) {
-    wide_dma16(rsa, lds[ca.slot] + (NLA * wv + i) * 1024, va[i], ca.kt * 128);
+    dma16(rsa, lds[ca.slot] + (NLA * wv + i) * 1024, va[i], ca.kt * 128);
     if (i == NLA - 1 && advance(ca)) setup_a();
   };
   auto dma_b = [&](int i) __attribute__((always_inline)) {
-    wide_dma16(rsb, lds[cb.slot] + (NLB * wv + i) * 1024, vb[i], cb.kt * 128);
+    dma16(rsb, lds[cb.slot] + (NLB * wv + i) * 1024, vb[i], cb.kt * 128);
     if (i == NLB - 1 && advance(cb)) setup_b();
   };
 
@@ -205,8 +192,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   // the next stage's loads landed, everyone's (the A loads past it stay in flight), and
   // this stage is read
   auto sync = [&]() __attribute__((always_inline)) {
-    wide_wait<NLA>();
-    __asm__ volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    wait_vmem<NLA>();
+    barrier_lds();
   };
 
 #pragma unroll
@@ -217,7 +204,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   for (int i = 0; i < NLA; ++i) dma_a(i);
 #pragma unroll
   for (int i = 0; i < NLB / 2; ++i) dma_b(i);
-  wide_wait<NLA + NLB / 2>();                           // stage 0
+  wait_vmem<NLA + NLB / 2>();                           // stage 0
   __asm__ volatile("s_barrier" ::: "memory");
 #pragma unroll
   for (int i = 0; i < I + J; ++i) read1(f0, lds[0], lds[1], 0, i);
@@ -363,7 +350,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
       }
     }
   }
-  wide_wait<0>();                                       // no load may land in LDS after the workgroup ends
+  wait_vmem<0>();                                       // no load may land in LDS after the workgroup ends
 }
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }
