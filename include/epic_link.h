@@ -110,7 +110,7 @@ typedef struct {
   int32_t n_linked_blocks;  /* entries of the linked block tables */
   int32_t n_private;        /* private blocks taken from the free list */
   int32_t n_tiles;          /* attention query tiles (per KV head) */
-  int32_t n_work;           /* attention work items (per KV head) */
+  int32_t n_work;           /* attention work items (per KV head), list entries among them */
   int32_t n_partials;       /* split-KV partial results (per KV head) */
   int32_t tile_rows;        /* query rows (S row x head) per tile: 16, 128 or 256 */
   int32_t max_pos;          /* 1 + largest linked position in the batch */
@@ -192,7 +192,11 @@ epic_status epic_plan_link(const epic_link_request* reqs, int32_t batch,
  * order from free_blocks (distinct, not linked by prev).  The new plan links
  * everything prev linked plus the new blocks; it lists as private only the blocks
  * that receive a new token, so epic_link_attention with it (q_s / k_s / v_s of the
- * new tokens) writes nothing else.  Host only, integer, synchronous. */
+ * new tokens) writes nothing else.  Requests that link the same blocks may share work
+ * items (see epic_plan), so the parts that a row's softmax is merged from, and with them
+ * the last bits of its result, depend on the batch; with kv_split_blocks set, or where the
+ * partials of whole shared items would pass EPIC_NOALLOC_SCRATCH_BYTES, each request has
+ * items of its own.  Host only, integer, synchronous. */
 epic_status epic_plan_decode_sizes(const epic_plan_sizes* prev_sizes, const epic_plan* prev,
                                    const int32_t* new_tokens, const epic_attn_cfg* cfg, int32_t n_free,
                                    epic_plan_sizes* out);
@@ -280,7 +284,8 @@ epic_status epic_link_attention_noalloc(const epic_attn_cfg* cfg, const epic_pla
  * stream, events[0] before the link write, events[1] before the attention
  * kernel, events[2] after it and events[3] after the split-KV combine (per
  * layer for the model entry points; each record overwrites the previous one;
- * with few rows their Q|K|V projection writes the private blocks itself, so
+ * where their Q|K|V projection leaves partial sums and nothing is re-rotated, the
+ * pass that adds them up writes the private blocks itself, before events[0], so
  * nothing runs between events[0] and events[1]).
  * Never fails. */
 epic_status epic_set_profile_events(void* const* events);
@@ -353,14 +358,20 @@ epic_status epic_link_model(const epic_model_cfg* cfg, const epic_layer_weights*
  * of 256 every operand and output below 2^31 bytes; else EPIC_ERR_UNSUPPORTED.
  * Device pointers, 16-byte aligned.  workspace: at least epic_gemm_workspace_bytes()
  * bytes of device memory, 256-byte aligned, owned by the caller; it holds the
- * partial sums of output tiles cut along k and their arrival counters (cleared by
- * this call), so calls in flight at the same time need separate workspaces.
- * A tile cut along k is summed in a fixed order (the part that holds the tile's last
- * k stage, then the others in k order), so results do not depend on timing.  The
- * environment variable EPIC_GEMM_FINISH_POLLS (read at each launch, default 4096)
- * bounds how long that last part's workgroup polls for the others before falling
- * back to the last-to-arrive protocol; 0 forces the fallback (a test hook; the sums
- * are the same either way).
+ * partial sums of products that are divided along k and the arrival counters of tiles
+ * cut along k (cleared by this call), so calls in flight at the same time need separate
+ * workspaces.
+ * How a product is divided depends on its sizes alone, and its parts are added in a fixed
+ * order, so results do not depend on timing:
+ *   - whole tiles: one chain of additions in k order (gate and up of few rows: from a k
+ *     stage of the tile's own, wrapping);
+ *   - parts of k in separate planes (few rows, or few tiles and a long k): each part in one
+ *     to four chains over its k slices, the parts in k order;
+ *   - tiles cut along k: the part that holds the tile's last k stage first, then the others
+ *     in k order.  The environment variable EPIC_GEMM_FINISH_POLLS (read at each launch,
+ *     default 4096) bounds how long that last part's workgroup polls for the others before
+ *     falling back to the last-to-arrive protocol; 0 forces the fallback (a test hook; the
+ *     sums are the same either way).
  * Enqueued on `stream` (NULL: the default stream); returns after the enqueue. */
 typedef enum { EPIC_GEMM_STORE = 0, EPIC_GEMM_RESIDUAL = 1, EPIC_GEMM_SWIGLU = 2 } epic_gemm_epilogue;
 size_t epic_gemm_workspace_bytes(void);

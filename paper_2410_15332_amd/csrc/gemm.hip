@@ -10,9 +10,10 @@
 //               position (rotary pairs (i, i + D/2)), v heads as they are; bf16 q, k, v
 //
 // Three families of kernels, chosen by gemm_route below:
-//   - many rows: whole 256- or 192-row tiles of 256 columns (gemm_wide.hip);
-//   - short row sets: small tiles, K dealt in equal shares, sums in the consumer
-//     (gemm_stream.hip);
+//   - many rows: whole 256- or 192-row tiles of 256 columns, or equal parts of K of
+//     them (gemm_wide.hip);
+//   - short row sets: small tiles, K dealt in equal shares, sums in the consumer; gate|up
+//     of up to 128 rows in whole tiles (gemm_stream.hip);
 //   - in between (this file): 128-column tiles, whole where one round of them fills the
 //     chip, else cut along K.
 //

@@ -61,9 +61,10 @@ __device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcp
 // GLU: a tile's columns are TN / 2 gate columns and the same up columns; worker w has the
 // whole tile w and stores silu(gate) * up itself.  It starts at K stage w % ks and wraps:
 // rows of W a multiple of 4 KB apart put the same stage of every row on the same few
-// memory channels, so the workers have to be at different stages.  K = 4096, ffn 14336:
-// 32 rows 52.4 us in partial sums, 53.1 in whole tiles that start alike, 44.8 so (235 MB
-// at 5.2 TB/s); 128 rows 55.7, 55.7 and 51.4.
+// memory channels, so the workers have to be at different stages.  K = 4096, ffn 14336 (235
+// MB): 32 rows 44.6 us (5.3 TB/s), all starting at stage 0 53.1; before, one round of 96 x 128
+// tiles 47.4, and partial sums would take 51.8; 128 rows 51.0, 128 x 128 tiles 52.2, partial
+// sums 63.1.
 // All bounds say 512 threads: for fewer, the compiler has more than 256 registers, puts the
 // accumulators into AGPRs and moves them there and back for every part (0.4 us more).
 template <int TM, int TN, int NW, int CT, int NS, int NA, bool GLU = false>
@@ -389,7 +390,11 @@ StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream) {
 
 // Gate|up of up to 128 rows where its 64 + 64-column tiles make one round that fills at
 // least 3/4 of the CUs, and W's rows are a multiple of 4 KB apart, so that the memory
-// channels are the bound (K = 5120, ffn 13824: 52.2 us in partial sums, 53.3 here).
+// channels are the bound.  Against what else would run (us, 1 / 32 / 64 / 128 rows):
+//   K = 2048, ffn 12416: 23.4 / 23.4 / 24.1 / 26.8, one round of narrow tiles 25.9 / 26.2 / 26.5 / 28.8
+//   K = 6144, ffn 14336: 61 / 64 / 68 / 79, narrow tiles 73 / 75 / 78 / 87
+//   K = 8192, ffn 16384: 90 / 90 / 90 / 99, partial sums 117 / 115 / 117 / 140
+// Not K = 5120, ffn 13824: 50.6 / 52.6 / 56.6 / 65.4, narrow tiles 49.3 / 51.8 / 55.4 / 65.2.
 bool glu_fits(int M, int ffn, int K) {
   return M <= 128 && ffn / 64 >= 192 && ffn / 64 <= 256 && K % 2048 == 0;
 }

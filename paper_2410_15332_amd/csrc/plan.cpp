@@ -237,13 +237,15 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
     return n;
   };
   // A first split adds the combine's launch, which a short decode item does not repay
-  // (in steps; 14 blocks unsplit 13.5 us, split 15.2; 125 blocks of 128 dims 23 -> 15).
+  // (in steps; called one by one, 14 blocks unsplit 13.5 us, split 15.2; 125 blocks of 128
+  // dims 23 -> 15).
   const double first_split = sh.rows == kTileRowsTiny ? (cfg->head_dim == 64 ? 16.0 : 8.0) : 0.0;
   const int whole = cdiv(max_nblk, kKvTileBlocks) * kKvTileBlocks;
-  // Likewise link items of up to 8 steps of 64 dims: the combine is a third launch, and the
-  // host takes about 15 us to enqueue three, 13 for two (3 x 128 + 16 tokens, 7 steps: split
-  // 16.4 us, whole 13.6; 9 steps, split 15.0, whole 17.3).  Not 128 dims, whose steps take
-  // longer (5 steps: split 16.2, whole 18.0).
+  // Likewise link items of up to 8 steps of 64 dims.  Calls made one by one go at the host's
+  // pace, two launches whole (7 / 8 / 9 steps 13.6 / 15.9 / 16.5 us), three split (17.3 / 17.5 /
+  // 17.0); replayed from a HIP graph whole takes 21.0 / 23.2 / 23.7, split 19-21 / 19-21 / 20, so
+  // there the line would lie at 6.  Not 128 dims, whose steps take longer (5 steps: whole 15.3,
+  // split 17.2, in a graph 22.8 and 19.3; 6 steps: 19.5 and 16.9, 27.2 and 20.7).
   if (sh.rows != kTileRowsTiny && cfg->head_dim == 64 && whole <= 8 * kKvTileBlocks) {
     *time = estimate_makespan(tiles, whole, hkv, sh);
     return whole;
