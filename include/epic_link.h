@@ -364,7 +364,8 @@ epic_status epic_link_model(const epic_model_cfg* cfg, const epic_layer_weights*
  * How a product is divided depends on its sizes alone, and its parts are added in a fixed
  * order, so results do not depend on timing:
  *   - whole tiles: one chain of additions in k order (gate and up of few rows: from a k
- *     stage of the tile's own, wrapping);
+ *     stage of the tile's own, wrapping); with an fp32 result and less than a round of tiles, a
+ *     chain for each of up to a few equal parts of k, added to c one after the other;
  *   - parts of k in separate planes (few rows, or few tiles and a long k): each part in one
  *     to four chains over its k slices, the parts in k order;
  *   - tiles cut along k: the part that holds the tile's last k stage first, then the others

@@ -25,6 +25,8 @@ struct GemmArgs {
   int hq, hkv, head_dim;
   float* partial;      // split-tile partial sums, gemm_workspace_bytes() with tile_count
   int* tile_count;     // arrival counters of split tiles (per wavefront); zero before the first launch
+  bool in_layer;       // of a decoder layer: the pass that sums partials also does what another launch would (a
+                       // norm, the link write), and the sum's rounding is far below that of its bf16 operands
 };
 // Requirements: K % 64 == 0; N % 128 == 0 (kStoreF32 / kResidual / kRope); ffn % 128 == 0
 // (kSwiGLU); head_dim 64 or 128 (kRope); M * K and N * K below 2^30 (byte offsets of the
@@ -42,13 +44,12 @@ int gemm_counters();          // arrival counters at tile_count
 // leave partial sums and a pass that adds them up.  kGlu: one round of whole streamed
 // gate|up tiles.
 enum class GemmRoute { kWhole256, kWhole192, kWhole128, kWhole96, kCut, kStream, kSplit, kGlu };
-// in_layer: the pass that sums partials also does what another launch would (a norm, the
-// link write).
-GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer);
+GemmRoute gemm_route(const GemmArgs& g, int epi);
 const char* gemm_route_name(GemmRoute r);
 // Zero the arrival counters (a kernel, so it can sit in a captured stream).
 void launch_gemm_clear(int* tile_count, hipStream_t stream);
 void launch_gemm(const GemmArgs& g, int epi, GemmRoute r, hipStream_t stream);
 void launch_gemm_wide(const GemmArgs& g, int epi, int tm, hipStream_t stream);
+int gemm_chains(const GemmArgs& g, int epi);   // chains of additions that a 256-column tile needs
 
 }  // namespace epic

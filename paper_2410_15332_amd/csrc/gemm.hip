@@ -629,7 +629,7 @@ void launch_epi(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
 
 }  // namespace
 
-GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer) {
+GemmRoute gemm_route(const GemmArgs& g, int epi) {
   // At least a round of 256 x 256 tiles: whole tiles only (measured: cutting tiles
   // along K costs about one tile time in partial traffic, more than a short last
   // round).  The tiles are 256 or 192 rows high, whichever takes less time: a round
@@ -667,7 +667,7 @@ GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer) {
   // take routes 0.5% (geometric mean) behind the best one, and 27% ahead of cutting always.
   // w: MB of weights, u: K stages per workgroup.  Measured examples (K x N, rows: us):
   //   streamed weights  4096 x 4096, 128: 15.6, 384: 29; 14336 x 4096, 128: 31, 384: 53
-  //   whole wide tiles  4096 x 28672, 300: 87 (cut 115), 512: 115 (150); 4096 x 6144, 1500: 68 (84)
+  //   whole wide tiles  4096 x 28672, 300: 87 (cut 115), 512: 115 (150); 4096 x 6144, 1500: 68 (84; 77 in two chains)
   //   split wide tiles  14336 x 4096, 363: 57 (streamed 75), 736: 92 (cut 110), 2000: 206 (249);
   //                     8192 x 2048, 600: 42 (53)
   //   cut tiles         4096 x 4096, 1472: 61-66 (split 66-69); 14336 x 16384, 64: 90 (streamed 114)
@@ -675,20 +675,22 @@ GemmRoute gemm_route(const GemmArgs& g, int epi, bool in_layer) {
   //                     4096 x 8192, 769: 64 (split 71), 2048 x 32768, 129: 40 (53)
   // In a layer the pass that sums partials replaces a norm or a link write (bonus).
   constexpr double kNever = 1e30;
-  const double bonus = !in_layer ? 0.0 : epi == kResidual ? 5.0 : epi == kRope ? 10.0 : 0.0;
+  const double bonus = !g.in_layer ? 0.0 : epi == kResidual ? 5.0 : epi == kRope ? 10.0 : 0.0;
   const double w = double(g.K) * g.N * 2e-6, plane = double(g.M) * g.N * 4e-6;
   const int64_t ks = g.K / kBK;
   const double per_mb = g.M <= 32 ? 0.12 : g.M <= 64 ? 0.14 : g.M <= 128 ? 0.155 : g.M <= 256 ? 0.27 : g.M <= 384 ? 0.52 : 0.66;
   const double stream = g.M <= kStreamRows && stream_fits(g.M, g.N, g.K)
                             ? 9.0 + w * per_mb + 0.08 * std::max(w - 100.0, 0.0) + 0.38 * plane - bonus
                             : kNever;
-  const WideSplit sp = wide_split(g.M, g.N, g.K);
+  const WideSplit sp = wide_split(g, epi);
   const double split = sp.parts >= 2 ? wide_split_time(sp, g.M, g.N, g.K) + 0.24 * sp.parts * plane - bonus : kNever;
-  auto whole = [&](int tm) {                            // one round; a stage takes longer the more CUs run
+  const int chains = std::min<int64_t>(gemm_chains(g, epi), ks);
+  auto whole = [&](int tm) {     // one round; a stage takes longer the more CUs run; a further chain is a tile written and read
     const int64_t tiles = int64_t(cdiv(g.M, tm)) * n256;
     if (n256 == 0 || tiles > kMaxWorkers) return kNever;
     const double t = double(tiles) / kMaxWorkers;
-    return 5.8 + ks * (tm == 256 ? 0.90 + 0.44 * t : 0.69 + 0.37 * t) + 0.05 * w + 0.067 * plane;
+    return 5.8 + ks * (tm == 256 ? 0.90 + 0.44 * t : 0.69 + 0.37 * t) + 0.05 * w + 0.067 * plane +
+           (chains - 1) * (tm == 256 ? 8.0 + 0.15 * plane : 8.0 + 0.12 * plane);
   };
   const double whole256 = whole(256), whole192 = whole(192);
   // A stage of a 256 x 128 tile: less where wavefronts have no rows (64 each) if that holds
@@ -739,7 +741,7 @@ void launch_gemm_clear(int* tile_count, hipStream_t stream) {
 void launch_gemm(const GemmArgs& g, int epi, GemmRoute r, hipStream_t stream) {
   if (g.M == 0) return;
   if (is_partial(r))
-    launch_stream_finish(launch_gemm_partial(g, r, stream), g, epi, stream);
+    launch_stream_finish(launch_gemm_partial(g, epi, r, stream), g, epi, stream);
   else if (r == GemmRoute::kGlu)
     launch_gemm_glu(g, stream);
   else if (r == GemmRoute::kWhole256 || r == GemmRoute::kWhole192)

@@ -36,6 +36,7 @@
 // wavefront hold gate and up, or the two halves of rotary pairs (D = 64 needs no order).
 // Rows past M and columns past N are read clamped and never stored.
 #include <algorithm>
+#include <cmath>
 
 #include "device_common.h"
 #include "gemm.h"
@@ -55,6 +56,8 @@ struct WidePlan {
   int gm;                      // row tiles per ordering group
   int G;                       // workgroups, a multiple of 8
   int parts;                   // kPlanes: equal parts of K per tile, a workgroup each
+  int chains;                  // kResidual: parts of K added to the output one after the other
+  int fresh;                   // kResidual: the output holds nothing yet
 };
 constexpr int kPlanes = 4;     // epilogue: fp32 partial sums into planes (stream_sum.h)
 
@@ -210,8 +213,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
   for (int i = 0; i < I + J; ++i) read1(f0, lds[0], lds[1], 0, i);
 
   int sa = 0, sb = 1;
-  const int n = SPLIT ? n_units : p.ks;                 // stages per tile
-  for (int tile = tile0, left = n_units; left > 0; tile += p.G, left -= n) {
+  constexpr bool CHAINS = EPI == kResidual;
+  int chain = 0;
+  for (int tile = tile0, left = n_units; left > 0;) {
+    // stages until the sums go to the output: the tile's, or its next chain's
+    const int n = SPLIT ? n_units : CHAINS ? (chain + 1) * p.ks / p.chains - chain * p.ks / p.chains : p.ks;
 #pragma unroll
     for (int i = 0; i < I; ++i)
 #pragma unroll
@@ -316,6 +322,9 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
       float* c = g.C;
       if constexpr (SPLIT) c = g.partial + size_t(part) * g.M * g.N;
       const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(c, 0, g.M * g.N * 4, kBufWord3);
+      // what to add to: nothing (an empty range reads as 0) for the first chain of a plain product
+      const __amdgpu_buffer_rsrc_t ri =
+          __builtin_amdgcn_make_buffer_rsrc(c, 0, chain == 0 && p.fresh ? 0 : g.M * g.N * 4, kBufWord3);
       const int nw = nt * kTN + wn * 128;
       if (nw < g.N) {                                   // N % 128 == 0: all of the wavefront's columns, or none
         auto at = [&](int b) __attribute__((always_inline)) {
@@ -328,7 +337,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
 #pragma unroll
             for (int r = 0; r < 16; ++r)
               old[b % DEPTH][r] = __builtin_bit_cast(
-                  float, __builtin_amdgcn_raw_buffer_load_b32(ro, o + ((r >> 2) * 8 + (r & 3)) * g.N * 4, 0, 0));
+                  float, __builtin_amdgcn_raw_buffer_load_b32(ri, o + ((r >> 2) * 8 + (r & 3)) * g.N * 4, 0, 0));
             __builtin_amdgcn_sched_barrier(0);
           }
         };
@@ -349,6 +358,11 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(GemmArgs g, WidePlan 
         }
       }
     }
+    left -= n;
+    if (!CHAINS || ++chain == p.chains) {
+      chain = 0;
+      tile += p.G;
+    }
   }
   wait_vmem<0>();                                       // no load may land in LDS after the workgroup ends
 }
@@ -364,10 +378,42 @@ void launch_wide_tm(const GemmArgs& g, hipStream_t stream) {
   p.gm = std::min(p.m_tiles, 8);
   p.tiles = p.m_tiles * p.n_tiles;
   p.G = cdiv(cdiv(p.tiles, cdiv(p.tiles, kMaxWorkers)), 8) * 8;
+  if constexpr (EPI == kStoreF32 || EPI == kResidual) {
+    p.chains = std::min(gemm_chains(g, EPI), p.ks);
+    p.fresh = EPI == kStoreF32;
+    if (EPI == kResidual || p.chains > 1) {
+      gemm_wide_kernel<kResidual, TM><<<p.G, 256, 0, stream>>>(g, p);
+      return;
+    }
+  }
   gemm_wide_kernel<EPI, TM><<<p.G, 256, 0, stream>>>(g, p);
 }
 
 }  // namespace
+
+// Chains of additions that a tile's sums have to be made of, so that fp32 results are as exact as
+// by what ran these sizes before.  A chain of L matrix instructions leaves a rounding error
+// of sqrt(L).  Products of less than a round of 256-row tiles used to be 256 x 128 tiles cut along
+// K into shares of x tiles; a tile's parts c_i (of L) left sqrt(L sum c_i^2), with a sum of x
+// where the shares are parts of tiles, else on average x - x^2 / 3 up to a tile and
+// 1 - 1 / (3 x) past it.  As many equal chains as the reciprocal of that leave no more.
+// Relative error and us, cut -> one chain -> the chains needed:
+//   whole tiles  3000 rows, N 4096, K 4096   3.59e-7 -> 3.95e-7 -> 2.72e-7, 109 -> 82 -> 94
+//                3000, 4096, 14336           6.95e-7 -> 7.64e-7 -> 5.33e-7, 356 -> 259 -> 274
+//                296, 28672, 4096            3.56e-7 -> 3.95e-7 -> 2.73e-7, 116 -> 83 -> 95
+//   split tiles  912, 2176, 1024             0.94e-7 -> 1.28e-7 -> 0.88e-7, 33 -> 18 -> 26
+// Two sets of accumulators instead, for which 192 rows leave the registers, are spilled.
+int gemm_chains(const GemmArgs& g, int epi) {
+  if ((epi != kStoreF32 && epi != kResidual) || g.in_layer) return 1;
+  const int m_tiles = cdiv(g.M, 256);
+  if (int64_t(m_tiles) * cdiv(g.N, kTN) >= kMaxWorkers) return 1;
+  const int tiles = m_tiles * cdiv(g.N, 128);
+  const int shares = int(std::min<int64_t>(kMaxWorkers, std::max<int64_t>(1, int64_t(tiles) * (g.K / kBK) / 4)));
+  if (tiles % shares == 0) return 1;
+  const double x = double(tiles) / shares;
+  const double sum = shares % tiles == 0 ? x : x <= 1.0 ? x - x * x / 3 : 1.0 - 1.0 / (3 * x);
+  return int(std::ceil(1.0 / sum - 1e-9));
+}
 
 // A stage takes longer with 256 rows than with 192, and the more CUs run; and what of the
 // weights does not come from the L2 in time.
@@ -377,10 +423,12 @@ double wide_split_time(const WideSplit& s, int M, int N, int K) {
          0.045 * std::max(w - 120.0, 0.0);
 }
 
-// Equal parts of K per tile, a workgroup each, in one round; at least eight stages a part,
-// planes within the workspace.  The height by the time of the stages alone, 1.5 us with 256
-// rows and 1.25 with 192.  Up to 128 rows the tiles would mostly be padding.
-WideSplit wide_split(int M, int N, int K) {
+// Equal parts of K per tile, a workgroup each, in one round; at least eight stages a part
+// (fewer only where the sums need more chains), planes within the workspace.  The height by
+// the time of the stages alone, 1.5 us with 256 rows and 1.25 with 192.  Up to 128 rows the
+// tiles would mostly be padding.
+WideSplit wide_split(const GemmArgs& g, int epi) {
+  const int M = g.M, N = g.N, K = g.K, chains = gemm_chains(g, epi);
   WideSplit best{};
   double best_time = 0.0;
   if (M <= 128) return best;
@@ -388,16 +436,17 @@ WideSplit wide_split(int M, int N, int K) {
     const int64_t tiles = int64_t(cdiv(M, tm)) * cdiv(N, kTN);
     if (tiles > kMaxWorkers / 2) continue;
     const int64_t fit = int64_t(gemm_partial_floats()) / (int64_t(M) * N);
-    const int parts = int(std::min({kMaxWorkers / tiles, int64_t(K / kBK / 8), fit}));
-    if (parts < 2) continue;
+    const int64_t most = std::min({kMaxWorkers / tiles, int64_t(K / kBK), fit});
+    const int parts = int(std::min(most, std::max<int64_t>(K / kBK / 8, chains)));
+    if (parts < 2 || parts < chains) continue;
     const double time = cdiv(K / kBK, parts) * (tm == 256 ? 1.5 : 1.25);
     if (best.parts == 0 || time < best_time) best = WideSplit{tm, parts}, best_time = time;
   }
   return best;
 }
 
-StreamSum launch_gemm_wide_split(const GemmArgs& g, hipStream_t stream) {
-  const WideSplit w = wide_split(g.M, g.N, g.K);
+StreamSum launch_gemm_wide_split(const GemmArgs& g, int epi, hipStream_t stream) {
+  const WideSplit w = wide_split(g, epi);
   WidePlan p{};
   p.m_tiles = cdiv(g.M, w.tm);
   p.n_tiles = cdiv(g.N, kTN);

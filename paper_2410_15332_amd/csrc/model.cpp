@@ -108,7 +108,7 @@ LayerGemms layer_gemms(const epic_model_cfg* c, const epic_layer_weights* w, int
   LayerGemms l{};
   auto set = [&](GemmArgs& g, const uint16_t* a, const uint16_t* wt, int N, int K) {
     g.A = a, g.W = wt, g.M = n, g.N = N, g.K = K;
-    g.partial = ws.gemm_partial, g.tile_count = ws.gemm_count;
+    g.partial = ws.gemm_partial, g.tile_count = ws.gemm_count, g.in_layer = true;
   };
   set(l.qkv, ws.x, w->wqkv, (hq + 2 * hkv) * D, H);
   l.qkv.q = ws.q, l.qkv.k = ws.k, l.qkv.v = ws.v, l.qkv.cs = ws.cs;
@@ -127,10 +127,9 @@ LayerGemms layer_gemms(const epic_model_cfg* c, const epic_layer_weights* w, int
 void start_layers(const epic_model_cfg* c, const epic_layer_weights* w, const epic_plan_sizes* s, const epic_plan* p,
                   const float* h, const LayerWs& ws, hipStream_t stream) {
   const LayerGemms l = layer_gemms(c, w, s->n_s, nullptr, ws);
-  const bool cut = gemm_route(l.qkv, kRope, true) == GemmRoute::kCut ||
-                   gemm_route(l.wo, kResidual, true) == GemmRoute::kCut ||
-                   gemm_route(l.gate_up, kSwiGLU, true) == GemmRoute::kCut ||
-                   gemm_route(l.down, kResidual, true) == GemmRoute::kCut;
+  const bool cut = gemm_route(l.qkv, kRope) == GemmRoute::kCut || gemm_route(l.wo, kResidual) == GemmRoute::kCut ||
+                   gemm_route(l.gate_up, kSwiGLU) == GemmRoute::kCut ||
+                   gemm_route(l.down, kResidual) == GemmRoute::kCut;
   launch_rmsnorm_start(h, w->attn_norm, ws.x, s->n_s, c->hidden, c->rms_eps, p->s_pos, ws.cs, c->attn.head_dim,
                        c->rope_theta, ws.gemm_count, cut ? gemm_counters() : 0, stream);
 }
@@ -147,9 +146,9 @@ void add_norm(StreamSum* pending, float* h, const uint16_t* w, uint16_t* x, floa
 
 // h += the product g; partial sums stay pending until the next norm (add_norm).
 void residual_gemm(const GemmArgs& g, StreamSum* pending, hipStream_t stream) {
-  const GemmRoute r = gemm_route(g, kResidual, true);
+  const GemmRoute r = gemm_route(g, kResidual);
   if (is_partial(r))
-    *pending = launch_gemm_partial(g, r, stream);
+    *pending = launch_gemm_partial(g, kResidual, r, stream);
   else
     launch_gemm(g, kResidual, r, stream);
 }
@@ -164,11 +163,11 @@ epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, cons
   const LayerGemms l = layer_gemms(c, w, n, h, ws);
   if (!normed) add_norm(pending, h, w->attn_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
   // partial sums of Q|K|V go straight into the private blocks
-  const GemmRoute qr = gemm_route(l.qkv, kRope, true);
+  const GemmRoute qr = gemm_route(l.qkv, kRope);
   const bool write = s->n_rerotated == 0 && is_partial(qr);
   if (write) {
     const StreamWrite sw{p->priv_block, p->priv_src, p->priv_rows, s->n_private, kc, vc};
-    launch_stream_rope_write(launch_gemm_partial(l.qkv, qr, stream), l.qkv, sw, stream);
+    launch_stream_rope_write(launch_gemm_partial(l.qkv, kRope, qr, stream), l.qkv, sw, stream);
   } else {
     launch_gemm(l.qkv, kRope, qr, stream);
   }
@@ -179,7 +178,7 @@ epic_status run_layer(const epic_model_cfg* c, const epic_layer_weights* w, cons
   if (st != EPIC_OK) return st;
   residual_gemm(l.wo, pending, stream);
   add_norm(pending, h, w->mlp_norm, ws.x, nullptr, n, H, c->rms_eps, stream);
-  launch_gemm(l.gate_up, kSwiGLU, gemm_route(l.gate_up, kSwiGLU, true), stream);
+  launch_gemm(l.gate_up, kSwiGLU, gemm_route(l.gate_up, kSwiGLU), stream);
   residual_gemm(l.down, pending, stream);
   return hip_ok("decoder layer launch");
 }
@@ -291,9 +290,9 @@ extern "C" epic_status epic_link_model(const epic_model_cfg* cfg, const epic_lay
 extern "C" const char* epic_gemm_route_name(int32_t epilogue, int32_t m, int32_t n, int32_t k, int32_t in_layer) {
   if (epilogue < kStoreF32 || epilogue > kRope || m <= 0 || n <= 0 || k <= 0 || n % 128 != 0 || k % 64 != 0) return "";
   GemmArgs g{};
-  g.M = m, g.N = n, g.K = k, g.ffn = epilogue == kSwiGLU ? n / 2 : 0;
-  const GemmRoute r = gemm_route(g, epilogue, in_layer != 0);
-  if (r == GemmRoute::kSplit) return wide_split(m, n, k).tm == 192 ? "split192" : "split256";
+  g.M = m, g.N = n, g.K = k, g.ffn = epilogue == kSwiGLU ? n / 2 : 0, g.in_layer = in_layer != 0;
+  const GemmRoute r = gemm_route(g, epilogue);
+  if (r == GemmRoute::kSplit) return wide_split(g, epilogue).tm == 192 ? "split192" : "split256";
   return gemm_route_name(r);
 }
 
@@ -336,7 +335,7 @@ extern "C" epic_status epic_gemm(int32_t epilogue, const uint16_t* a, const uint
   }
   gemm_workspace(workspace, &g.partial, &g.tile_count);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const GemmRoute r = gemm_route(g, epilogue, false);
+  const GemmRoute r = gemm_route(g, epilogue);
   if (r == GemmRoute::kCut) launch_gemm_clear(g.tile_count, s);
   launch_gemm(g, epilogue, r, s);
   return hip_ok("projection GEMM launch");

@@ -54,13 +54,13 @@ StreamSum launch_gemm_stream(const GemmArgs& g, hipStream_t stream);
 struct WideSplit {
   int tm, parts;
 };
-WideSplit wide_split(int M, int N, int K);
+WideSplit wide_split(const GemmArgs& g, int epi);
 double wide_split_time(const WideSplit& s, int M, int N, int K);   // estimate in us, without the planes
-StreamSum launch_gemm_wide_split(const GemmArgs& g, hipStream_t stream);
+StreamSum launch_gemm_wide_split(const GemmArgs& g, int epi, hipStream_t stream);
 // The partial sums of a route that leaves them to the consumer.
 inline bool is_partial(GemmRoute r) { return r == GemmRoute::kStream || r == GemmRoute::kSplit; }
-inline StreamSum launch_gemm_partial(const GemmArgs& g, GemmRoute r, hipStream_t stream) {
-  return r == GemmRoute::kSplit ? launch_gemm_wide_split(g, stream) : launch_gemm_stream(g, stream);
+inline StreamSum launch_gemm_partial(const GemmArgs& g, int epi, GemmRoute r, hipStream_t stream) {
+  return r == GemmRoute::kSplit ? launch_gemm_wide_split(g, epi, stream) : launch_gemm_stream(g, stream);
 }
 // Whether the partial sums of a product of these sizes fit the GEMM workspace.
 bool stream_fits(int M, int N, int K);

@@ -16,6 +16,13 @@ def test_cases_take_the_kernel_they_name(name):
         assert gemm.kernel_of(m, n, k, epi) == kernel, (m, n, k, epi)
 
 
+def test_precision_cases_take_the_kernel_they_name():
+    for m, n, k, kernel, _, _ in gemm.WIDE_CHAINS:
+        assert gemm.kernel_of(m, n, k, "store") == kernel
+    for m, n, k, _, _ in gemm.CHAINS:
+        assert gemm.kernel_of(m, n, k, "store") == "stream"
+
+
 def test_whole_gate_up_cases():
     for m, n, k in gemm.GLU:
         assert gemm.kernel_of(m, n, k, "swiglu") == "glu"

@@ -280,8 +280,12 @@ def test_streamed_sums_keep_their_precision(m, n, k, chain, planes):
     instruction rounds its running sum twice; of independent terms the sum after j of L
     instructions has j / L of the final variance.  So chains of at most c instructions
     leave r^2 c, the addition of a part's chains at most r^2, and p planes r^2 p / 2."""
-    from paper_2410_15332_amd import epic_link as el
     assert kernel_of(m, n, k, "store") == "stream"
+    _check_error(m, n, k, chain, planes)
+
+
+def _check_error(m, n, k, chain, planes):
+    from paper_2410_15332_amd import epic_link as el
     gen = torch.Generator(device="cuda").manual_seed(n + m)
     a = torch.empty((m, k), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
     w = torch.empty((n, k), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
@@ -296,11 +300,31 @@ def test_streamed_sums_keep_their_precision(m, n, k, chain, planes):
     assert err <= bound
 
 
+WIDE_CHAINS = [  # less than a round of 256-column tiles: matrix instructions per chain, chains (or planes)
+    (912, 2176, 1024, "split192", 16, 5),     # 16 K stages: parts of 3 and 4
+    (629, 2048, 2048, "split192", 24, 6),
+    (3000, 4096, 4096, "whole192", 128, 2),
+    (3000, 5120, 8192, "whole256", 256, 2),
+]
+
+
+@pytest.mark.parametrize("m,n,k,kernel,chain,chains", WIDE_CHAINS, ids=[f"{c[0]}x{c[1]}x{c[2]}" for c in WIDE_CHAINS])
+def test_wide_tiles_keep_their_precision(m, n, k, kernel, chain, chains):
+    """As above: a whole tile's chains are added one after the other to the output, which
+    rounds like planes.  One chain over all of K would pass the bound (3000 x 4096 x 4096: 3.95e-7
+    against 2.9e-7)."""
+    assert kernel_of(m, n, k, "store") == kernel
+    _check_error(m, n, k, chain, chains)
+
+
 WIDE = [  # whole 256-column tiles: one K stage, an odd number, several tiles per workgroup, tails
     (2100, 8192, 64, "store", "whole192"),        # 11 x 32 tiles of one stage each
     (2048, 8192, 64, "residual", "whole256"),     # 8 x 32 tiles of one stage, a round of 256
     (2100, 8320, 192, "residual", "whole192"),    # 3 stages; the last column tile is 128 wide
     (3000, 11520, 448, "swiglu", "whole192"),     # 7 stages, ffn 5760
+    (4700, 2176, 1984, "store", "whole192"),      # two chains of 15 and 16 stages; the last column tile is 128 wide
+    (5000, 2048, 2112, "residual", "whole192"),   # two chains of 16 and 17 stages
+    (6000, 2176, 2112, "store", "whole256"),      # two chains of 16 and 17 stages
 ]
 
 
@@ -316,6 +340,8 @@ SPLIT = [  # 256-wide tiles in equal parts of K, each an fp32 plane (few tiles, 
     (550, 640, 4160, "store", "split192"),        # 65 stages: parts of 8 and 9; the last column tile half past the end
     (700, 1280, 4096, "swiglu", "split192"),      # gate and up summed by the SwiGLU pass
     (363, 4096, 14336, "store", "split192"),      # two row tiles, 8 parts of 28 stages
+    (736, 1024, 192, "store", "split192"),        # 3 stages in two parts
+    (1250, 1024, 448, "residual", "split192"),    # 7 stages in three parts, last row tile 98 rows
     (700, 2048, 14336, "residual", "split256"),   # 3 x 8 tiles of 256 rows, 10 parts of 22 or 23 stages
 ]
 
