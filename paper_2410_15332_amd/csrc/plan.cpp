@@ -654,6 +654,27 @@ double makespan(std::vector<double> cost, int slots) {
   return end;
 }
 
+// Estimated us of a decode step, over shared items and with every request reading its own
+// blocks, fitted to 220 random batches of which a quarter of the block reads or more could be
+// shared (2-32 requests of 1-64 chunks of 33-2048 tokens; deviation 10% rms).  The reads are what
+// sharing saves.  It costs launch slots for more and shorter items and their list entries, and
+// partials: a row of 30 chunks of 100 tokens has one per chunk where its own blocks need two or three.
+// Sharing whenever a quarter of the reads were saved made 58 of the 220 slower: 25 requests of 34 x
+// 59 tokens from 102 chunks, 32/4 heads of 128, 22.8 -> 43.6 us (us on the GPU); 10 of 30 x 137 from 120,
+// 16/8 heads, 31.3 -> 34.2; 4 of 14 x 396 from 14, 14.8 -> 18.2.  Shared where that is 10% shorter by these
+// estimates: 119 of the 220, none slower, all together 1.303 times as fast as plain (sharing every
+// one 1.276, the faster of the two 1.327); at 5% shorter 131, one slower by 4%, 1.309.
+struct ShareCost {
+  double blk_mb, row_mb;                                    // a block's K and V, a partial row, of all heads
+  int hkv, dim;
+  double plain(int64_t blocks) const { return 11.05 + 0.118 * double(blocks) * blk_mb; }
+  double shared(int64_t blocks, double makespan, int64_t entries, int64_t part_rows) const {
+    return 9.84 + 0.297 * makespan * dim / 128 + 0.107 * double(blocks) * blk_mb +
+           0.818 * double(entries) * hkv / kShapeTiny.slots + 1.01 * double(part_rows) * row_mb;
+  }
+  bool pays(double shared_us, int64_t total) const { return shared_us <= 0.9 * plain(total); }
+};
+
 // Work items over shared blocks for 16-row tiles; false where sharing does not pay.
 // A block is shared if several requests link it with the same valid length, none twice,
 // and all of it precedes their new rows (so it needs no causal mask).
@@ -717,7 +738,9 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     const int32_t* at = entry + dr[b].a;
     for (int i = 0, n = frozen(b); i < n; ++i) saved += (count[at[i]]++ & (R - 1)) != 0;
   }
-  if ((total - saved) * 4 > total * 3) return false;
+  const ShareCost us{cfg->num_kv_heads * 16.0 * cfg->head_dim * 4e-6, double(cfg->num_q_heads) * cfg->head_dim * 4e-6,
+                     cfg->num_kv_heads, cfg->head_dim};
+  if ((total - saved) * 4 > total * 3 || !us.pays(us.shared(total - saved, 0.0, 0, 0), total)) return false;
   std::vector<Ref> ref(slots_n);
   for (int b = 0; b < batch; ++b) {
     if (dr[b].t == 0) continue;
@@ -775,6 +798,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     }
     if (parts_least > max_parts) return false;
   }
+  if (!us.pays(us.shared(total - saved, 0.0, parts_least / R, parts_least), total)) return false;
   // groups of at most R rows over a run, about equal
   struct Group {
     int run, m0, m1;                                       // members [m0, m1) of the run
@@ -853,6 +877,19 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     if (parts == 1 || t < best_time * 0.97) best_time = t, best = split;
     if (split == 16) break;
   }
+  int64_t entries = 0, part_rows = 0;
+  for (const Item& it : whole) {
+    const int p = pieces(it, best);
+    int rows = dr[it.b].t, listed = it.kind == kItemList ? cdiv(it.i1 - it.i0, p) : 0;
+    if (it.kind == kItemShared) {
+      rows = 0;
+      for (int k = groups[it.group].m0; k < groups[it.group].m1; ++k) rows += dr[runs[groups[it.group].run].members[k].first].t;
+      listed = 2 * rows;
+    }
+    entries += int64_t(p) * (1 + cdiv(listed, kExtInts));
+    part_rows += int64_t(p) * rows;
+  }
+  if (!us.pays(us.shared(read, best_time, entries, part_rows), total)) return false;
   // tiles: one per request with rows; partials of a tile are consecutive
   std::vector<int> tile_of(batch, -1), n_part(batch, 0), row0(batch, 0), base(batch, 0);
   int n_tiles = 0, rows = 0, lb = 0;

@@ -29,7 +29,7 @@ def _f64(bits):
     return synth.bf16_bits_to_f32(bits).astype(np.float64)
 
 
-def _run_decode(wl, steps, spare_blocks=64, tile_rows=0):
+def _run_decode(wl, steps, spare_blocks=64, tile_rows=0, kinds=None):
     from paper_2410_15332_amd import epic_link as el, harness
     print(f"[gpu-test] decode after {wl.name} k={wl.k}: steps {[sum(s) for s in steps]} tokens, "
           f"tile rows {tile_rows or 'auto'}", flush=True)
@@ -55,6 +55,9 @@ def _run_decode(wl, steps, spare_blocks=64, tile_rows=0):
             assert ds.sizes.tile_rows == tile_rows
         elif max(new) <= 16 // (wl.num_q_heads // wl.num_kv_heads) and sum(new) > 0:
             assert ds.sizes.tile_rows == 16, "decode-shaped plan without 16-row tiles"
+        work = ds.views["work"].reshape(-1, 8)
+        if kinds and min(new) > 0:
+            assert kinds <= set(work[work[:, 0] >= 0, 7].tolist()), "item kinds of the plan"
         ds.run(st.k_cache, st.v_cache)
         torch.cuda.synchronize()
         out, lse = ds.out.float().cpu().numpy(), ds.lse.cpu().numpy()
@@ -129,3 +132,14 @@ def test_decode_over_shared_chunks(hq, hkv, d):
     wl = AttnWorkload(f"shared_{hq}_{hkv}_{d}", 77, hq, hkv, d, 16, reqs, [533, 800, 47, 1200],
                       [5, 16, 31, 1, 9, 20, 64], 16)
     _run_decode(wl, [[1] * 7, [min(rows, x) for x in (2, 0, 1, 3, 1, 2, 1)], [1] * 7], spare_blocks=64)
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(8, 8, 64), (32, 8, 128), (64, 8, 64)])
+def test_decode_over_chunks_shared_by_many(hq, hkv, d):
+    """The same with requests enough that sharing pays, so that the plans have shared items and
+    block lists: 16, 4 and 2 S rows per 16-row tile."""
+    some = [[0, 1, 2], [1, 0, 2], [2, 2, 3], [0, 3], [3, 1, 0], [1, 4], [0, 1, 4], [4, 0, 3]]
+    n = 40
+    wl = AttnWorkload(f"many_{hq}_{hkv}_{d}", 78, hq, hkv, d, 16, [some[i % 8] for i in range(n)],
+                      [1533, 1800, 47, 1200, 1000], [5 + 3 * i % 41 for i in range(n)], 16)
+    _run_decode(wl, [[1] * n, [i % 3 % (16 * hkv // hq) for i in range(n)], [1] * n], spare_blocks=160, kinds={1, 2})

@@ -536,8 +536,9 @@ def _items_of_rows(sizes, d):
 
 
 @pytest.mark.parametrize("seed", range(8))
-@pytest.mark.parametrize("hq,hkv", [(8, 8), (32, 8), (16, 2), (16, 1)])
-def test_shared_decode_items_cover_each_row_once(seed, hq, hkv):
+@pytest.mark.parametrize("many", [False, True])       # few small requests, which mostly share nothing, or enough to share
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (32, 8), (64, 8), (16, 2), (16, 1)])
+def test_shared_decode_items_cover_each_row_once(seed, hq, hkv, many):
     """Decode plans over shared chunk caches, against the definition: each new row's items
     cover exactly the blocks of its own request, each once (a shared item by the same
     physical block and length, all of it before the row), and write each of its tile's
@@ -546,23 +547,29 @@ def test_shared_decode_items_cover_each_row_once(seed, hq, hkv):
     rng = np.random.default_rng(900 + seed)
     cfg = el.attn_cfg(hq, hkv, 64)
     R = 16 // (hq // hkv)
-    pool = [int(x) for x in rng.integers(1, 900, 8)]
+    n_pool = 24 if many else 8
+    pool = [int(x) for x in rng.integers(1, 2500 if many else 900, n_pool)]
     blocks, nxt = [], 0
     for n in pool:
         blocks.append(list(range(nxt, nxt + -(-n // 16))))
         nxt += -(-n // 16)
     reqs = []
-    for _ in range(int(rng.integers(2, 14))):
+    for _ in range(int(rng.integers(40, 60) if many else rng.integers(2, 14))):
         ids = [int(x) for x in rng.integers(0, 8, int(rng.integers(1, 7)))]
-        lens = [pool[c] - (1 if rng.random() < 0.1 and pool[c] % 16 > 1 else 0) for c in ids]
+        if many:                                           # most chunks stand in a request once, and at full length
+            ids = [int(x) for x in rng.permutation(n_pool)[:int(rng.integers(1, 7))]]
+            ids += [c for c in ids if c < 3]
+        lens = [pool[c] - (1 if rng.random() < (0.01 if many else 0.1) and pool[c] % 16 > 1 else 0) for c in ids]
         reqs.append(el.Request(lens, [blocks[c] for c in ids], int(rng.integers(1, 40)), int(rng.choice([0, 4, 32]))))
     need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
-    total = nxt + need + 64
+    total = nxt + need + 2 * len(reqs) + 64
     sizes, buf, v = el.epic_plan_link(reqs, cfg, list(range(nxt, nxt + need)), total)
-    new = [int(rng.integers(0, R + 1)) for _ in reqs]
+    new = [int(rng.integers(0, (max(1, R // 4) if many else R) + 1)) for _ in reqs]
     new[0] = 1
     ds, _, d = el.epic_plan_decode(sizes, buf, new, cfg, list(range(nxt + need, total)), total)
     assert ds.tile_rows == 16
+    if many:
+        assert hkv < 8 or R == 2 or len(_shared_items(d)) > 0     # (where it is sure to pay)
     cover, parts = _items_of_rows(ds, d)
     key = lambda b: (int(d["linked_blocks"][b]), int(d["block_len"][b]))  # noqa: E731
     for r in range(ds.n_s):
@@ -587,23 +594,39 @@ def test_shared_decode_items_cover_each_row_once(seed, hq, hkv):
 
 
 def test_shared_decode_rule():
-    """Sharing is taken where it saves a quarter of the block reads, and not with a forced
-    split, for one request, or when nothing is common."""
+    """Sharing is taken where requests enough have blocks in common, whatever the block ids
+    are, and not with a forced split, for one request, or when nothing is common."""
     cfg = el.attn_cfg(32, 8, 128)
-    ids = list(range(64))
 
     def kinds(reqs, cfg):
         need = el.epic_plan_sizes_get(reqs, cfg, 1 << 30).n_private
-        sizes, buf, _ = el.epic_plan_link(reqs, cfg, list(range(500, 500 + need)), 900)
-        _, _, d = el.epic_plan_decode(sizes, buf, [1] * len(reqs), cfg, list(range(700, 740)), 900)
+        sizes, buf, _ = el.epic_plan_link(reqs, cfg, list(range(5000, 5000 + need)), 6000)
+        _, _, d = el.epic_plan_decode(sizes, buf, [1] * len(reqs), cfg, list(range(5500, 5540)), 6000)
         return set(d["work"].reshape(-1, 8)[:, 7].tolist())
 
-    same = [el.Request([1024], [ids], 20, 0) for _ in range(4)]
-    assert 1 in kinds(same, cfg)
-    assert 1 in kinds(same[:2], cfg)                       # block ids sparse: twice the blocks and more
-    assert kinds(same, el.attn_cfg(32, 8, 128, 0.0, 16)) == {0}
-    assert kinds(same[:1], cfg) == {0}
-    assert kinds([el.Request([1024], [[64 * r + i for i in ids]], 20, 0) for r in range(4)], cfg) == {0}
+    def same(first):
+        return [el.Request([1024], [list(range(first, first + 64))], 20, 0) for _ in range(16)]
+
+    assert 1 in kinds(same(0), cfg)
+    assert 1 in kinds(same(4900), cfg)                     # block ids sparse: twice the blocks and more
+    assert kinds(same(0), el.attn_cfg(32, 8, 128, 0.0, 16)) == {0}
+    assert kinds(same(0)[:1], cfg) == {0}
+    assert kinds([el.Request([1024], [list(range(64 * r, 64 * r + 64))], 20, 0) for r in range(16)], cfg) == {0}
+
+
+# (requests, chunks each, tokens, pool, query heads, KV heads, dim): us on the GPU plain and shared
+SHARING = [
+    ((25, 34, 59, 102, 32, 4, 128), 22.8, 43.6), ((20, 32, 53, 128, 32, 4, 128), 19.9, 37.9),
+    ((29, 45, 57, 90, 32, 8, 128), 42.1, 61.1), ((4, 14, 396, 14, 32, 4, 128), 14.8, 18.2),
+    ((2, 4, 827, 4, 32, 4, 128), 12.4, 14.6),
+    ((32, 8, 2000, 64, 32, 8, 128), 263.0, 121.6),
+]
+
+
+@pytest.mark.parametrize("shape,plain,shared", SHARING, ids=["x".join(map(str, x[0])) for x in SHARING])
+def test_shared_decode_where_it_is_faster(shape, plain, shared):
+    _, _, d = el.epic_plan_decode(*_many_requests(*shape))
+    assert (len(_shared_items(d)) > 0) == (shared < plain)
 
 
 def _many_requests(n_req, chunks, tokens, pool, hq, hkv, d, split=0, suffix=20):
