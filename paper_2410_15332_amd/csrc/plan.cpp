@@ -238,15 +238,16 @@ int split_blocks(const epic_attn_cfg* cfg, const std::vector<Tile>& tiles, const
   };
   // A first split adds the combine's launch, which a short decode item does not repay
   // (in steps; called one by one, 14 blocks unsplit 13.5 us, split 15.2; 125 blocks of 128
-  // dims 23 -> 15).
-  const double first_split = sh.rows == kTileRowsTiny ? (cfg->head_dim == 64 ? 16.0 : 8.0) : 0.0;
+  // dims 23 -> 15; on the GPU, 120 items of 110 blocks of 64 dims in two parts 22.6 -> 19.2).
+  const double first_split = sh.rows == kTileRowsTiny ? 8.0 : 0.0;
   const int whole = cdiv(max_nblk, kKvTileBlocks) * kKvTileBlocks;
   // Likewise link items of up to 8 steps of 64 dims.  Calls made one by one go at the host's
   // pace, two launches whole (7 / 8 / 9 steps 13.6 / 15.9 / 16.5 us), three split (17.3 / 17.5 /
   // 17.0); replayed from a HIP graph whole takes 21.0 / 23.2 / 23.7, split 19-21 / 19-21 / 20, so
   // there the line would lie at 6.  Not 128 dims, whose steps take longer (5 steps: whole 15.3,
-  // split 17.2, in a graph 22.8 and 19.3; 6 steps: 19.5 and 16.9, 27.2 and 20.7).
-  if (sh.rows != kTileRowsTiny && cfg->head_dim == 64 && whole <= 8 * kKvTileBlocks) {
+  // split 17.2, in a graph 22.8 and 19.3; 6 steps: 19.5 and 16.9, 27.2 and 20.7).  And decode items
+  // of up to 16 steps of 64 dims: two launches, 15 us on the GPU, are through when three are enqueued.
+  if (cfg->head_dim == 64 && whole <= (sh.rows == kTileRowsTiny ? 16 : 8) * kKvTileBlocks) {
     *time = estimate_makespan(tiles, whole, hkv, sh);
     return whole;
   }

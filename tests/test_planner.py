@@ -720,3 +720,18 @@ def test_small_launches_split_below_64_blocks():
     reqs, n = _long_request([2000], 2, 0)
     s, longest = shape(reqs, n, 32, 8, 128)                # ... over 126
     assert s.tile_rows == 16 and s.n_work > 4 and s.n_work * 8 <= 256
+
+
+@pytest.mark.parametrize("requests,blocks,split", [(2, 64, False), (2, 68, True), (15, 64, False), (15, 110, True)])
+def test_decode_items_of_64_dims_split_past_16_steps(requests, blocks, split):
+    """Decode of 64 dims: items of up to 16 steps (64 blocks) stay whole; past them a split is
+    taken where its parts are shorter by more than the combine (8 x 64 heads, us on the GPU, whole ->
+    split: 2 requests of 68 blocks 15.3 -> 11.2, 15 of 110 blocks 22.6 -> 19.1)."""
+    cfg = el.attn_cfg(8, 8, 64)
+    reqs = [el.Request([16 * (blocks - 1)], [list(range(r * blocks, r * blocks + blocks - 1))], 1, 0) for r in range(requests)]
+    free = list(range(requests * blocks, requests * blocks + 4 * requests))
+    total = requests * blocks + 4 * requests
+    need = el.epic_plan_sizes_get(reqs, cfg, len(free)).n_private
+    sizes, buf, _ = el.epic_plan_link(reqs, cfg, free[:need], total)
+    sizes, _, _ = el.epic_plan_decode(sizes, buf, [1] * requests, cfg, free[need:], total)
+    assert (sizes.n_partials > 0) == split
