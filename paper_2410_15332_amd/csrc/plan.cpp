@@ -674,6 +674,10 @@ struct ShareCost {
            0.818 * double(entries) * hkv / kShapeTiny.slots + 1.01 * double(part_rows) * row_mb;
   }
   bool pays(double shared_us, int64_t total) const { return shared_us <= 0.9 * plain(total); }
+  // partial rows past which sharing cannot pay, at least `blocks` read
+  int64_t most_parts(int64_t blocks, int64_t total) const {
+    return static_cast<int64_t>(std::max(0.0, (0.9 * plain(total) - shared(blocks, 0.0, 0, 0)) / (1.01 * row_mb)));
+  }
 };
 
 // Work items over shared blocks for 16-row tiles; false where sharing does not pay.
@@ -769,6 +773,7 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
     else own[b].emplace_back(i, i + n);
   };
   int64_t parts_least = n_rows;             // a partial per member of a run, and one of a request's own blocks
+  const int64_t parts_limit = std::min(max_parts, us.most_parts(total - saved, total));
   for (int b = 0; b < batch; ++b) {
     if (dr[b].t == 0) continue;
     const int fz = frozen(b), nb = dr[b].e - dr[b].a + dr[b].extra;
@@ -797,9 +802,8 @@ bool shared_decode(const epic_plan_sizes* ps, const epic_plan* prev, const std::
       i = j;
       sig = next;
     }
-    if (parts_least > max_parts) return false;
+    if (parts_least > parts_limit) return false;
   }
-  if (!us.pays(us.shared(total - saved, 0.0, parts_least / R, parts_least), total)) return false;
   // groups of at most R rows over a run, about equal
   struct Group {
     int run, m0, m1;                                       // members [m0, m1) of the run
